@@ -70,12 +70,12 @@ typedef enum {
 
 /* crb_frame.flags */
 #define CRB_FLAG_NO_EARLY_STOP 1   /* always run niter iterations */
-/* From iteration 2 on, re-run the detection only on the tiles whose codes can change: a
- * code depends on J within Chebyshev distance 4 (Section 5: S reads J within 2 pixels
- * through med5(J) and L+, S' reads S within 2 more, F^ reads med3 within 3, and med3
- * reads J within 1), and an iteration changes J only where its replacement wrote a new
- * value; the other tiles keep their codes.  The results are identical to the full
- * re-run. */
+/* From iteration 2 on the detection is re-evaluated only where a code can change, with or
+ * without this flag: a code depends on J within Chebyshev distance 4 (Section 5: S reads J
+ * within 2 pixels through med5(J) and L+, S' reads S within 2 more, F^ reads med3 within
+ * 3, and med3 reads J within 1), and an iteration changes J only at the pixels it replaces;
+ * the other pixels keep their codes.  The results are identical to a full re-run.  The flag
+ * says what a counting run counts (crb_plan_set_counting). */
 #define CRB_FLAG_INCREMENTAL 2
 
 /* Options for crb_set_option. */
@@ -85,9 +85,8 @@ typedef enum {
 /* Launch shapes of crb_lacosmic, crb_lacosmic_noalloc and crb_debug_* (see crb_tuning;
  * every shape gives identical results): */
 #define CRB_OPT_TILE_H 3           /* detection tile rows: 16, 32 (default) or 64        */
-#define CRB_OPT_FUSED 4            /* 0 (default) or 1: grow and replacement fused        */
-#define CRB_OPT_GROW_H 5           /* first-iteration grow strip rows: 0 (default), 8, 16
-                                      or 32                                              */
+#define CRB_OPT_FUSED 4            /* 0 (default) or 1: accepted, without effect          */
+#define CRB_OPT_GROW_H 5           /* 0 (default), 8, 16 or 32: accepted, without effect  */
 
 /*
  * Clean one frame (the method above).
@@ -170,8 +169,10 @@ void crb_plan_destroy(crb_plan *plan);
 /* Per-launch timing of a plan created without a graph: when enabled, every launch
  * of crb_plan_run is bracketed by a pair of HIP events on the plan's stream.
  * crb_plan_kernel_times waits for the recorded work and returns, per kernel class
- * (0 init, 1 detection, 2 grow/count, 3 replacement), the summed milliseconds and
- * the number of launches since timing was enabled (ms[4], launches[4]). */
+ * (0 init: copies of frames with niter 0; 1 the first iteration's detection; 2 the
+ * iterations: grow, count, replacement and the next iteration's detection where J changed;
+ * 3 always zero), the summed milliseconds and the number of launches since timing was
+ * enabled (ms[4], launches[4]). */
 crb_status crb_plan_set_timing(crb_plan *plan, int32_t enable);
 crb_status crb_plan_kernel_times(crb_plan *plan, double *ms, int64_t *launches);
 /* Work counters of the detection kernel (for roofline accounting).  The detection
@@ -182,8 +183,10 @@ crb_status crb_plan_kernel_times(crb_plan *plan, double *ms, int64_t *launches);
  * counting the med7 window of med3 against the test's switching value) only where
  * S' > sigclip.  A work-set pixel whose S' interval from the estimate straddles a
  * threshold is re-evaluated in binary64 from J.  With counting enabled every
- * detection launch adds, per frame, the size of its work set, its number of contrast
- * tests and its number of re-evaluations; crb_plan_set_counting (which waits for the
+ * detection adds, per frame, the size of its work set, its number of contrast tests and its
+ * number of re-evaluations -- of every pixel at every iteration, evaluated for the count,
+ * except for frames with CRB_FLAG_INCREMENTAL, which count what an uncounted run evaluates
+ * too; crb_plan_set_counting (which waits for the
  * plan's stream) clears the counters, crb_plan_work_counts waits for the stream and
  * returns the totals over all frames since then: counts[0] work-set pixels,
  * counts[1] contrast tests, counts[2] binary64 re-evaluations, counts[3] pixels whose
@@ -201,18 +204,16 @@ crb_status crb_plan_work_counts(crb_plan *plan, int64_t *counts);
  * (Section 6.3.1: a 6 x 6 split beats 1 x 36, and the slowest subimage sets the pace);
  * here the same trade-offs are the halo share of a tile or strip and how tiles are
  * handed to the compute units.  Every shape computes identical results.
- *   tile_h      detection tile rows, 16, 32 or 64 (64 columns; the halo is 4 rows and
+ *   tile_h      tile rows of the first iteration's detection, 16, 32 or 64 (64 columns; the halo is 4 rows and
  *               columns of J, 2 of S): taller tiles re-read less halo per pixel, shorter
  *               ones fit more blocks per compute unit;
  *   persistent  0: one block per (frame, tile); 1: about as many blocks as are resident
  *               at once, each taking tiles from 8 atomic ticket counters (one per XCD,
  *               each over a contiguous part of the tile list, a block helping the others
  *               once its part is used up), as CRBLASTER's actors take subimages;
- *   fused       0: grow/count, list prefix and replacement as three launches per
- *               iteration; 1: one launch, each 8-row strip recomputing its 2-row mask
- *               halo (rows its neighbours own) and replacing its own flagged pixels;
- *   grow_h      rows of a first-iteration grow strip when fused is 0 (8, 16 or 32; 0 =
- *               32 for batches), with a 2-row code halo above and below.
+ *   fused       0 or 1 and
+ *   grow_h      0, 8, 16 or 32: accepted, without effect (everything after the first
+ *               detection is one launch per iteration).
  * The default is {32, 0, 0, 0}.
  */
 typedef struct {
@@ -353,7 +354,8 @@ crb_status crb_set_stream(void *hip_stream);
 crb_status crb_set_option(int32_t key, int64_t value);
 /* Message of the calling thread's last error ("" if none). */
 const char *crb_last_error(void);
-/* Device workspace a frame of H x W needs beyond its input and outputs (bytes). */
+/* Device workspace to provide for a frame of H x W beyond its input and outputs (bytes):
+ * about 5 bytes per pixel (a frame uses less; budgets and limits go by this number). */
 size_t crb_workspace_bytes(int32_t H, int32_t W);
 /* Free the workspace cached for hip_stream (waits for the stream first). */
 crb_status crb_release_workspace(void *hip_stream);

@@ -195,7 +195,7 @@ def lacosmic(img: torch.Tensor, gain: float, readnoise: float, sky: float = 0.0,
              early_stop: bool = True, incremental: bool = False,
              stream: Optional[torch.cuda.Stream] = None):
     """crb_lacosmic on device tensors; returns (clean float32, mask uint8).
-    incremental: CRB_OPT_INCREMENTAL (identical results, less detection work)."""
+    incremental: CRB_OPT_INCREMENTAL (identical results)."""
     _dev2d(img, torch.float32, "img")
     H, W = img.shape
     if out_clean is None:

@@ -89,17 +89,25 @@ static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 FrameWs ws_layout(int32_t H, int32_t W) {
     const size_t n = (size_t)H * (size_t)W;
-    FrameWs L;
-    L.codes = 0;
-    L.list = align_up(L.codes + n, 256);
-    L.nnew = align_up(L.list + 4 * n, 256);
-    L.listlen = align_up(L.nnew + 8 * (size_t)kMaxIter, 256);
-    L.dirty = align_up(L.listlen + 4 * (size_t)kMaxIter, 256);
     const size_t ntiles = (size_t)((H + kSumTY - 1) / kSumTY) *
                           (size_t)((W + kSumTX - 1) / kSumTX);
-    L.tile_first = align_up(L.dirty + ntiles, 256);
-    L.tile_new = align_up(L.tile_first + 4 * ntiles, 256);
-    L.total = align_up(L.tile_new + 4 * ntiles, 256);
+    FrameWs L;
+    L.bits = 0;
+    L.mbits = align_up(L.bits + ntiles * (2 * 3 * kSumTY * 8), 256);
+    L.state = align_up(L.mbits + ntiles * (kSumTY * 8), 256);
+    L.mark = align_up(L.state + 4 * ntiles, 256);
+    L.count = align_up(L.mark + 4 * ntiles, 256);
+    L.any_new = align_up(L.count + 8 * (size_t)kCountSlots * kCountStride, 256);
+    L.lists = align_up(L.any_new + 4 * (size_t)kMaxIter, 256);
+    const size_t end = align_up(L.lists + 4 * list_words(ntiles), 256);
+    // Callers size budgets and refuse frames by the reported size, which stays what it was
+    // when a frame's workspace held a code byte and a 4-byte list entry per pixel (about
+    // five times what is used now): what fits a budget or the fixed scratch does not change.
+    const size_t reported = align_up(n, 256) + align_up(4 * n, 256) +
+                            align_up(8 * (size_t)kMaxIter, 256) +
+                            align_up(4 * (size_t)kMaxIter, 256) + align_up(ntiles, 256) +
+                            2 * align_up(4 * ntiles, 256);
+    L.total = end > reported ? end : reported;
     return L;
 }
 
@@ -113,13 +121,12 @@ DevFrame make_devframe(const float *img, float *J, uint8_t *mask, char *ws, cons
     f.mask = mask;
     f.g2 = nullptr;
     if (ws) {      // without a workspace every workspace pointer stays null
-        f.codes = reinterpret_cast<uint8_t *>(ws + L.codes);
-        f.list = reinterpret_cast<uint32_t *>(ws + L.list);
-        f.nnew = reinterpret_cast<unsigned long long *>(ws + L.nnew);
-        f.listlen = reinterpret_cast<unsigned int *>(ws + L.listlen);
-        f.dirty = reinterpret_cast<uint8_t *>(ws + L.dirty);
-        f.tile_first = reinterpret_cast<uint8_t *>(ws + L.tile_first);
-        f.tile_new = reinterpret_cast<unsigned int *>(ws + L.tile_new);
+        f.bits = reinterpret_cast<unsigned long long *>(ws + L.bits);
+        f.mbits = reinterpret_cast<unsigned long long *>(ws + L.mbits);
+        f.state = reinterpret_cast<unsigned int *>(ws + L.state);
+        f.mark = reinterpret_cast<unsigned int *>(ws + L.mark);
+        f.count = reinterpret_cast<unsigned long long *>(ws + L.count);
+        f.any_new = reinterpret_cast<unsigned int *>(ws + L.any_new);
     }
     f.H = H;
     f.W = W;
@@ -134,15 +141,6 @@ DevFrame make_devframe(const float *img, float *J, uint8_t *mask, char *ws, cons
     f.k = 0;
     derive_detect_consts(f);
     return f;
-}
-
-int replace_grid(size_t npix) {
-    size_t g = npix / 4096;
-    if (g < 1)
-        g = 1;
-    if (g > 2048)
-        g = 2048;
-    return (int)g;
 }
 
 crb_status hip_status(hipError_t e, const char *what) {
@@ -225,19 +223,21 @@ static LaunchCfg single_cfg() {
     return c;
 }
 
+// the lists of a frame run by itself on workspace ws
+static StepLists frame_lists(char *ws, const FrameWs &L, int32_t H, int32_t W) {
+    return make_lists(ws + L.lists, (size_t)detect_tiles(H, W, kSumTY));
+}
+
 // enqueue niter iterations for one frame whose DevFrame is complete
-static crb_status enqueue_single(const DevFrame &f, const LaunchCfg &cfg, hipStream_t s) {
-    const size_t npix = (size_t)f.H * (size_t)f.W;
-    const bool fused = cfg.fused && !f.g2;
-    // the init kernel touches pixels only for niter == 0 (a copy); else just counters
-    hipError_t e = launch_init(nullptr, 1, f, f.niter == 0 ? npix : 0, nullptr, 0, s);
-    for (int k = 1; e == hipSuccess && k <= f.niter; ++k) {
-        e = launch_detect(nullptr, nullptr, 0, f, k, cfg, nullptr, s);
-        if (e == hipSuccess)
-            e = launch_grow(nullptr, nullptr, 0, f, k, (f.flags & kFreshMask) != 0, cfg, s);
-        if (e == hipSuccess && !fused)
-            e = launch_replace(nullptr, 1, nullptr, f, k, replace_grid(npix), s);
-    }
+static crb_status enqueue_single(const DevFrame &f, const LaunchCfg &cfg, const StepLists &lists,
+                                 hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (f.niter == 0)
+        e = launch_init(nullptr, 1, f, (size_t)f.H * (size_t)f.W, s);
+    else
+        e = launch_detect(nullptr, nullptr, 0, f, cfg, lists, nullptr, s);
+    for (int k = 1; e == hipSuccess && k <= f.niter; ++k)
+        e = launch_step(nullptr, nullptr, 0, f, k, false, lists, nullptr, s);
     return hip_status(e, "kernel launch");
 }
 
@@ -381,7 +381,7 @@ crb_status crb_lacosmic_noalloc(const float *img, int32_t H, int32_t W, float ga
                       (g_incremental.load() ? kIncremental : 0) | kFreshMask;
     DevFrame f = make_devframe(img, out_clean, out_mask, base, L, H, W, gain, readnoise, sky,
                                sigclip, sigfrac, objlim, niter, flags);
-    if ((st = enqueue_single(f, single_cfg(), t_stream)) != CRB_OK)
+    if ((st = enqueue_single(f, single_cfg(), frame_lists(base, L, H, W), t_stream)) != CRB_OK)
         return st;
     return ok();
 }
@@ -407,7 +407,7 @@ crb_status crb_lacosmic(const float *img, int32_t H, int32_t W, float gain, floa
                       (g_incremental.load() ? kIncremental : 0) | kFreshMask;
     DevFrame f = make_devframe(img, out_clean, out_mask, ws->buf, L, H, W, gain, readnoise, sky,
                                sigclip, sigfrac, objlim, niter, flags);
-    if ((st = enqueue_single(f, single_cfg(), s)) != CRB_OK)
+    if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->buf, L, H, W), s)) != CRB_OK)
         return st;
     return ok();
 }
@@ -560,11 +560,11 @@ crb_status crb_debug_iterate(const float *J, const uint8_t *M_prev, int32_t H, i
     hipError_t e = hipMemcpyAsync(out_M, M_prev, npix, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess)
         return hip_status(e, "hipMemcpyAsync");
-    if ((st = enqueue_single(f, single_cfg(), s)) != CRB_OK)
+    if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->buf, L, H, W), s)) != CRB_OK)
         return st;
-    e = hipMemcpyAsync(out_n_new, f.nnew, sizeof(int64_t), hipMemcpyDeviceToDevice, s);
+    e = launch_count(f, reinterpret_cast<long long *>(out_n_new), s);
     if (e != hipSuccess)
-        return hip_status(e, "hipMemcpyAsync");
+        return hip_status(e, "kernel launch");
     return ok();
 }
 
@@ -580,7 +580,8 @@ static crb_status debug_detect(const float *J, const crb_frame *p, uint8_t *out_
                                p->H, p->W, p->gain, p->readnoise, p->sky, p->sigclip,
                                p->sigfrac, p->objlim, 1, kNoEarlyStop | flags);
     f.codes = out_codes;
-    return hip_status(launch_detect(nullptr, nullptr, 0, f, 1, single_cfg(), nullptr, t_stream),
+    const StepLists none = {};
+    return hip_status(launch_detect(nullptr, nullptr, 0, f, single_cfg(), none, nullptr, t_stream),
                       "kernel launch") == CRB_OK
                ? ok()
                : CRB_EDEVICE;
@@ -694,23 +695,21 @@ struct crb_plan {
     int n = 0;
     int kmax = 0;
     size_t max_pix = 0;
-    size_t init_pix = 0;                // largest frame with niter == 0 (0 if none)
+    size_t init_pix = 0;                // largest frame with niter == 0
+    bool any_copy = false;              // some frame has niter == 0
     size_t all_pix = 0;
     char *dmem = nullptr;
     DevFrame *d_frames = nullptr;
     TileRef *d_tdet[3] = {nullptr, nullptr, nullptr};   // per detection tile height
     int ntdet[3] = {0, 0, 0};
-    TileRef *d_tgrow = nullptr;
-    int ntgrow = 0;
     long long *d_stats = nullptr;
-    unsigned int *d_prefix = nullptr;   // flat offsets of the frames' flagged lists
+    StepLists lists = {};               // tiles each iteration visits
     unsigned long long *d_work = nullptr;   // per frame: kWorkCounters detection counters
-    unsigned int *d_tickets = nullptr;  // kTicketWords per iteration (persistent detection)
+    unsigned int *d_tickets = nullptr;  // kTicketWords (persistent detection)
     std::vector<DevFrame> hframes;      // host copy of the frame table
     std::string key;                    // tune-cache key of the batch layout
     crb::LaunchCfg cfg;                 // launch shapes of crb_plan_run
     bool counting = false;
-    int rgrid = 1;
     bool use_graph = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -759,57 +758,31 @@ static crb_status plan_enqueue(crb_plan *p) {
     const int ti = tile_h_index(cfg.tile_h);
     if (ti < 0)
         return fail(CRB_EINVAL, "detection tile height %d", cfg.tile_h);
-    // A plan of one frame passes the frame by value to one-block-per-tile and per-strip
-    // grids, as crb_lacosmic does (no work-list lookups, no list prefix), unless its
-    // detection is persistent, which needs the tile list.
-    if (p->n == 1 && !cfg.persistent) {
-        const DevFrame &f = p->hframes[0];
-        const size_t npix = (size_t)f.H * (size_t)f.W;
-        hipError_t e = tmark_begin(p, kKindInit);
+    // A plan of one frame passes the frame by value, as crb_lacosmic does (no work-list
+    // lookups), unless its detection is persistent, which needs the tile list.
+    const bool one = p->n == 1 && !cfg.persistent;
+    const DevFrame &f = one ? p->hframes[0] : none;
+    const DevFrame *df = one ? nullptr : p->d_frames;
+    const TileRef *tdet = one ? nullptr : p->d_tdet[ti];
+    const TileRef *tstep = one ? nullptr : p->d_tdet[tile_h_index(kSumTY)];
+    const int nstep = p->ntdet[tile_h_index(kSumTY)];
+    hipError_t e = hipSuccess;
+    if (p->any_copy) {
+        e = tmark_begin(p, kKindInit);
         if (e == hipSuccess)
-            e = launch_init(nullptr, 1, f, p->init_pix, nullptr, 0, s);
+            e = launch_init(df, p->n, f, p->init_pix, s);
         if (e == hipSuccess)
             e = tmark_end(p);
-        for (int k = 1; e == hipSuccess && k <= p->kmax; ++k) {
-            if ((e = tmark_begin(p, kKindDetect)) == hipSuccess &&
-                (e = launch_detect(nullptr, nullptr, 0, f, k, cfg, nullptr, s)) == hipSuccess &&
-                (e = tmark_end(p)) == hipSuccess &&
-                (e = tmark_begin(p, kKindGrow)) == hipSuccess &&
-                (e = launch_grow(nullptr, nullptr, 0, f, k, (f.flags & kFreshMask) != 0, cfg,
-                                 s)) == hipSuccess &&
-                (e = tmark_end(p)) == hipSuccess && !cfg.fused &&
-                (e = tmark_begin(p, kKindReplace)) == hipSuccess &&
-                (e = launch_replace(nullptr, 1, nullptr, f, k, replace_grid(npix), s)) ==
-                    hipSuccess)
-                e = tmark_end(p);
-        }
-        if (e == hipSuccess)
-            e = launch_stats(p->d_frames, p->n, p->d_stats, s);
-        return hip_status(e, "kernel launch");
     }
-    hipError_t e = tmark_begin(p, kKindInit);
-    if (e == hipSuccess)
-        e = launch_init(p->d_frames, p->n, none, p->init_pix, p->d_tickets,
-                        p->kmax * kTicketWords, s);
-    if (e == hipSuccess)
+    if (e == hipSuccess && p->kmax > 0 && (e = tmark_begin(p, kKindDetect)) == hipSuccess &&
+        (e = launch_detect(df, tdet, p->ntdet[ti], f, cfg, p->lists, p->d_tickets, s)) ==
+            hipSuccess)
         e = tmark_end(p);
-    for (int k = 1; e == hipSuccess && k <= p->kmax; ++k) {
-        if ((e = tmark_begin(p, kKindDetect)) == hipSuccess &&
-            (e = launch_detect(p->d_frames, p->d_tdet[ti], p->ntdet[ti], none, k, cfg,
-                               p->d_tickets + (size_t)(k - 1) * kTicketWords, s)) ==
-                hipSuccess &&
-            (e = tmark_end(p)) == hipSuccess &&
-            (e = tmark_begin(p, kKindGrow)) == hipSuccess &&
-            // every frame of a plan carries kFreshMask
-            (e = launch_grow(p->d_frames, p->d_tgrow, p->ntgrow, none, k, true, cfg, s)) ==
-                hipSuccess &&
-            (e = tmark_end(p)) == hipSuccess && !cfg.fused &&
-            (e = tmark_begin(p, kKindReplace)) == hipSuccess &&
-            (e = launch_list_prefix(p->d_frames, p->n, k, p->d_prefix, s)) == hipSuccess &&
-            (e = launch_replace(p->d_frames, p->n, p->d_prefix, none, k, p->rgrid, s)) ==
+    for (int k = 1; e == hipSuccess && k <= p->kmax; ++k)
+        if ((e = tmark_begin(p, kKindStep)) == hipSuccess &&
+            (e = launch_step(df, tstep, nstep, f, k, p->counting, p->lists, p->d_tickets, s)) ==
                 hipSuccess)
             e = tmark_end(p);
-    }
     if (e == hipSuccess)
         e = launch_stats(p->d_frames, p->n, p->d_stats, s);
     return hip_status(e, "kernel launch");
@@ -1028,7 +1001,7 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     std::vector<size_t> off(n);
     size_t total = 0, max_pix = 0, all_pix = 0, init_pix = 0;
     int kmax = 0;
-    size_t ntdet[3] = {0, 0, 0}, ntgrow = 0;
+    size_t ntdet[3] = {0, 0, 0};
     for (int i = 0; i < n; ++i) {
         const crb_frame &f = frames[i];
         st = check_frame_args(f.H, f.W, f.gain, f.readnoise, f.sky, f.sigclip, f.sigfrac,
@@ -1040,7 +1013,7 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
             return fail(st, "frame %d: %s", i, crb_last_error());
         lay[i] = ws_layout(f.H, f.W);
         off[i] = total;
-        total += lay[i].total;
+        total += lay[i].lists;
         max_pix = npix > max_pix ? npix : max_pix;
         if (f.niter == 0)      // the init kernel copies these frames
             init_pix = npix > init_pix ? npix : init_pix;
@@ -1048,9 +1021,8 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
         kmax = f.niter > kmax ? f.niter : kmax;
         for (int t = 0; t < 3; ++t)
             ntdet[t] += (size_t)detect_tiles(f.H, f.W, kTileHeights[t]);
-        ntgrow += (size_t)((f.H + kGrowTY - 1) / kGrowTY) * ((f.W + kGrowTX - 1) / kGrowTX);
     }
-    if (ntdet[0] > (size_t)INT32_MAX || ntgrow > (size_t)INT32_MAX / (kGrowTY / kGrowTYSmall))
+    if (ntdet[0] > (size_t)INT32_MAX)
         return fail(CRB_ETOOBIG, "batch too large");
     // also guard against buffers shared between frames
     for (int i = 0; i < n; ++i)
@@ -1068,12 +1040,12 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     o_tdet[0] = o_frames + al(n * sizeof(DevFrame));
     o_tdet[1] = o_tdet[0] + al(ntdet[0] * sizeof(TileRef));
     o_tdet[2] = o_tdet[1] + al(ntdet[1] * sizeof(TileRef));
-    const size_t o_tgrow = o_tdet[2] + al(ntdet[2] * sizeof(TileRef));
-    const size_t o_stats = o_tgrow + al(ntgrow * sizeof(TileRef));
-    const size_t o_prefix = o_stats + al(2 * n * sizeof(long long));
-    const size_t o_work = o_prefix + al((n + 1) * sizeof(unsigned int));
+    const size_t nsum = ntdet[tile_h_index(kSumTY)];
+    const size_t o_lists = o_tdet[2] + al(ntdet[2] * sizeof(TileRef));
+    const size_t o_stats = o_lists + al(4 * list_words(nsum));
+    const size_t o_work = o_stats + al(2 * n * sizeof(long long));
     const size_t o_tickets = o_work + al(kWorkCounters * n * sizeof(unsigned long long));
-    const size_t bytes = o_tickets + al((size_t)(kmax > 0 ? kmax : 1) * kTicketWords * 4);
+    const size_t bytes = o_tickets + al((size_t)kTicketWords * 4);
 
     crb_plan *p = new (std::nothrow) crb_plan();
     if (!p)
@@ -1103,24 +1075,22 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     p->kmax = kmax;
     p->max_pix = max_pix;
     p->init_pix = init_pix;
+    p->any_copy = init_pix > 0;
     p->all_pix = all_pix;
     p->d_frames = reinterpret_cast<DevFrame *>(p->dmem + o_frames);
     for (int t = 0; t < 3; ++t) {
         p->d_tdet[t] = reinterpret_cast<TileRef *>(p->dmem + o_tdet[t]);
         p->ntdet[t] = (int)ntdet[t];
     }
-    p->d_tgrow = reinterpret_cast<TileRef *>(p->dmem + o_tgrow);
+    p->lists = make_lists(p->dmem + o_lists, nsum);
     p->d_stats = reinterpret_cast<long long *>(p->dmem + o_stats);
-    p->d_prefix = reinterpret_cast<unsigned int *>(p->dmem + o_prefix);
     p->d_work = reinterpret_cast<unsigned long long *>(p->dmem + o_work);
     p->d_tickets = reinterpret_cast<unsigned int *>(p->dmem + o_tickets);
-    p->ntgrow = (int)ntgrow;
 
     std::vector<DevFrame> hf(n);
-    std::vector<TileRef> td[3], tg;
+    std::vector<TileRef> td[3];
     for (int t = 0; t < 3; ++t)
         td[t].reserve(ntdet[t]);
-    tg.reserve(ntgrow);
     for (int i = 0; i < n; ++i) {
         const crb_frame &f = frames[i];
         hf[i] = make_devframe(f.img, f.out_clean, f.out_mask, p->dmem + off[i], lay[i], f.H, f.W,
@@ -1130,15 +1100,12 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
                                   (f.flags & CRB_FLAG_INCREMENTAL ? kIncremental : 0) |
                                   kFreshMask);
         hf[i].work = p->d_work + kWorkCounters * (size_t)i;
+        hf[i].tile_base = (int)td[tile_h_index(kSumTY)].size();
         for (int t = 0; t < 3; ++t)
             for (int y = 0; y < f.H; y += kTileHeights[t])
                 for (int x = 0; x < f.W; x += kDetectTX)
                     td[t].push_back(TileRef{i, y, x, 0});
-        for (int y = 0; y < f.H; y += kGrowTY)
-            for (int x = 0; x < f.W; x += kGrowTX)
-                tg.push_back(TileRef{i, y, x, 0});
     }
-    p->rgrid = replace_grid(all_pix);
     // launch shapes: the tune cache's entry for this layout, if any, else the defaults
     const char *cache = getenv("CRB_TUNE_CACHE");
     if (cache && *cache) {
@@ -1158,9 +1125,8 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     for (int t = 0; t < 3 && e == hipSuccess; ++t)
         e = hipMemcpyAsync(p->d_tdet[t], td[t].data(), td[t].size() * sizeof(TileRef),
                            hipMemcpyHostToDevice, p->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p->d_tgrow, tg.data(), tg.size() * sizeof(TileRef),
-                           hipMemcpyHostToDevice, p->stream);
+    if (e == hipSuccess)       // (each run leaves the tickets at zero again)
+        e = hipMemsetAsync(p->d_tickets, 0, kTicketWords * 4, p->stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(p->stream);
     p->hframes = hf;
@@ -1259,11 +1225,8 @@ crb_status crb_plan_autotune(crb_plan *p, int32_t reps, int32_t use_cache, crb_t
             (void)hipEventDestroy(a);
         return hip_status(e, "hipEventCreate");
     }
-    // Stage 1: detection shapes (tile height x one block per tile or persistent) under
-    // the default grow; stage 2: grow shapes (three launches with first-iteration strips
-    // of 8, 16 or 32 rows, or the fused grow and replacement) under the best detection.
-    // The two stages time whole runs; detection and grow touch disjoint launches, so
-    // their choices combine.
+    // the shapes of the first iteration's detection: tile height x one block per tile or
+    // persistent
     crb_status st = CRB_OK;
     const LaunchCfg def;
     double t_def = 0.0;
@@ -1284,19 +1247,6 @@ crb_status crb_plan_autotune(crb_plan *p, int32_t reps, int32_t use_cache, crb_t
                 cur = c;
             }
         }
-    const int growh[4] = {8, 16, 32, -1};      // -1: fused
-    const LaunchCfg det = cur;
-    for (int gi = 0; st == CRB_OK && gi < 4; ++gi) {
-        LaunchCfg c = det;
-        c.fused = growh[gi] < 0 ? 1 : 0;
-        c.grow_h = growh[gi] < 0 ? 0 : growh[gi];
-        double t = 0.0;
-        st = time_cfg(p, c, reps, a, b, &t);
-        if (st == CRB_OK && t < t_cur) {
-            t_cur = t;
-            cur = c;
-        }
-    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     if (st != CRB_OK)
@@ -1344,8 +1294,9 @@ crb_status crb_plan_set_counting(crb_plan *p, int32_t enable) {
     if (e != hipSuccess)
         return hip_status(e, "counter setup");
     p->counting = enable != 0;
-    // a one-frame plan passes its frame by value: its graph holds the old flags
-    if (p->use_graph && p->n == 1) {
+    // a counting run visits other tiles, and a one-frame plan passes its frame by value: the
+    // graph holds the old launches
+    if (p->use_graph) {
         crb_status st = plan_capture(p);
         if (st != CRB_OK)
             return st;

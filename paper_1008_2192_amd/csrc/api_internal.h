@@ -9,7 +9,9 @@ namespace crb {
 
 // Byte offsets of one frame's workspace pieces (256-byte aligned).
 struct FrameWs {
-    size_t codes, list, nnew, listlen, dirty, tile_first, tile_new, total;
+    size_t bits, mbits, state, mark, count, any_new;
+    size_t lists;        // lists of a frame run by itself; the end of the pieces of any frame
+    size_t total;        // what crb_workspace_bytes reports: at least the end of the lists
 };
 
 crb_status fail(crb_status st, const char *fmt, ...);
@@ -23,6 +25,5 @@ FrameWs ws_layout(int32_t H, int32_t W);
 DevFrame make_devframe(const float *img, float *J, uint8_t *mask, char *ws, const FrameWs &L,
                        int32_t H, int32_t W, float gain, float readnoise, float sky,
                        float sigclip, float sigfrac, float objlim, int32_t niter, int32_t flags);
-int replace_grid(size_t npix);
 
 }  // namespace crb

@@ -18,15 +18,15 @@ __device__ __forceinline__ float med3f(float a, float b, float c) {
 __device__ __forceinline__ float min3f(float a, float b, float c) { return fminf(fminf(a, b), c); }
 __device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// Iteration k of frame f is skipped when k exceeds its niter, or (early stop) when
-// the previous iteration selected no new pixel: that iteration reproduced its input,
-// so every later one would too.
-__device__ __forceinline__ bool frame_skips(const DevFrame &f, int k) {
-    if (k < 1 || k > f.niter)
-        return true;
-    if (k == 1 || (f.flags & kNoEarlyStop))
-        return false;
-    return f.nnew[k - 2] == 0ull;
+// Clears the counters of the list of iteration k (by one block).
+__device__ __forceinline__ void lists_clear(const StepLists &l, int k, int tid) {
+    if (tid < l.nseg)
+        l.count[((k % 3) * l.nseg + tid) * kTicketStride] = 0u;
+}
+// Before iteration 1, which fills the list of iteration 2 and clears that of iteration 3.
+__device__ __forceinline__ void lists_start(const StepLists &l, int tid) {
+    if (l.list[0])
+        lists_clear(l, 2, tid);
 }
 
 }  // namespace crb

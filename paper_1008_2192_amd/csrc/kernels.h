@@ -10,9 +10,9 @@ namespace crb {
 // Upper bound on iterations per frame (sizes the per-frame counters).
 constexpr int kMaxIter = 1024;
 // Detection tiles are kDetectTX = 64 columns by 16, 32 (default) or 64 rows, one block of
-// 8 threads per row.  The per-tile records shared by detection, grow and replacement
-// (where A occurs, the last iteration with a new flag, the incremental-detection stamps)
-// live on a fixed grid of kSumTY x kSumTX summary tiles, whatever the detection tile.
+// 8 threads per row.  The state the iterations share (code planes, mask bitmap, where A
+// occurs, which tiles the next iteration visits) lives on a fixed grid of kSumTY x kSumTX
+// summary tiles, whatever the detection tile.
 constexpr int kDetectTX = 64;
 constexpr int kDetectTYDefault = 32;
 constexpr int kSumTY = 32;
@@ -22,16 +22,16 @@ constexpr int kSumTX = 64;
 constexpr int kDetectQueues = 8;
 constexpr int kTicketStride = 32;
 constexpr int kTicketWords = kDetectQueues * kTicketStride;   // per launch
-// Grow tile (outputs per wave: 62 groups of 16 pixels by kGrowTY rows).
-constexpr int kGrowTY = 32;
-constexpr int kGrowTYSmall = 8;     // strip height for single frames below 2^22 pixels and
-                                    // for every frame after iteration 1
-constexpr int kGrowTX = 992;
-static_assert(kGrowTY % kGrowTYSmall == 0, "a grow strip splits into short strips");
+// Counters a frame's blocks add their new flags to, each on its own 128-byte line.
+constexpr int kCountSlots = 32;
+constexpr int kCountStride = 16;
+// Segments of a list of tiles (StepLists): appends spread over that many counters.
+constexpr int kListSegments = 64;
 constexpr int kThreads = 256;
 
 // Kernel classes for per-launch timing (crb_plan_kernel_times order).
-constexpr int kKindInit = 0, kKindDetect = 1, kKindGrow = 2, kKindReplace = 3;
+// (kind 3, once the replacement, is never recorded: it is part of an iteration's launch)
+constexpr int kKindInit = 0, kKindDetect = 1, kKindStep = 2;
 constexpr int kNumKernelKinds = 4;
 
 // DevFrame::flags bits.  kNoEarlyStop has the value of CRB_FLAG_NO_EARLY_STOP;
@@ -44,43 +44,41 @@ constexpr int kNoEarlyStop = 1;
 constexpr int kFreshMask = 1 << 8;
 constexpr int kCountWork = 1 << 9;
 constexpr int kExactDetect = 1 << 10;
-// kIncremental (the value of CRB_FLAG_INCREMENTAL): from iteration 2 on, detection
-// re-evaluates only the tiles near a summary tile stamped in f.dirty with the previous
-// iteration (replacement stamps the summary tiles whose codes can change); the others
-// keep their codes, which the unchanged J determines.
+// kIncremental (the value of CRB_FLAG_INCREMENTAL): with kCountWork, count the detection
+// work that is done (only where J changed); without it a counting run re-evaluates every
+// pixel at every iteration.  Without counting, both do the former.
 constexpr int kIncremental = 2;
 constexpr int kWorkCounters = 4;
 
 // Everything a kernel needs to know about one frame.  All pointers are device
-// pointers; J is the image being cleaned in place (out_clean).
+// pointers; J is the image being cleaned in place (out_clean).  The per-tile arrays are
+// indexed by summary tile, row-major.
 struct DevFrame {
-    const float *img;             // input frame (copied into J by the init kernel)
+    const float *img;             // input frame (copied into J by the first detection)
     float *J;                     // working / output image, H x W
     uint8_t *mask;                // cumulative mask, H x W (0/1)
-    uint8_t *codes;               // detection codes, H x W (workspace)
+    uint8_t *codes;               // optional: detection codes as bytes (parity tests), or null
     uint8_t *g2;                  // optional: selection of this iteration (debug), or null
-    uint32_t *list;               // indices of flagged pixels, H x W capacity (workspace)
-    unsigned long long *nnew;     // n_k per iteration [kMaxIter] (workspace)
-    unsigned int *listlen;        // [0]: length of the flagged list, which holds the pixels of
-                                  // the mask in the order they were flagged (workspace)
+    // detection codes: per tile two buffers of three planes (A, [S' > sigclip], [S' >
+    // sigfrac sigclip]) of 32 rows, bit c of a row for column c
+    unsigned long long *bits;
+    unsigned long long *mbits;    // cumulative mask, per tile 32 rows of 64 bits
+    // per tile: 2 * s + b, codes in buffer b since the launch of iteration s - 1 (1: the
+    // first detection).  An iteration writes new codes to the other buffer, so that its
+    // neighbours still read the codes it started from
+    unsigned int *state;
+    // per tile: the last iteration it was listed for (each lists a tile once)
+    unsigned int *mark;
+    // flagged pixels: the sum of kCountSlots counters, kCountStride apart
+    unsigned long long *count;
+    unsigned int *any_new;        // per iteration: whether n_k > 0 [kMaxIter]
     unsigned long long *work;     // with kCountWork: kWorkCounters counters, or null
-    // per summary tile, row-major (kIncremental): the last iteration (mod 256) whose
-    // replacement changed J within 4 pixels of it, or null
-    uint8_t *dirty;
-    // 4 bytes per summary tile, row-major, written by detection (byte w for rows
-    // 8w .. 8w+7): bit 0 some pixel of those rows has A (the first selection), bit 1 one
-    // of the tile's first two rows, bit 2 one of its last two; the grow skips strips with
-    // no A within its 2-pixel reach.  Or null
-    uint8_t *tile_first;
-    // per summary tile: the last iteration whose grow flagged a new pixel in it (the
-    // replacement leaves alone pixels with no new flag within 2 pixels), or null
-    unsigned int *tile_new;
     int H, W;
     float gain, readnoise, sky, sigclip, sigfrac, objlim;
     int niter;
     int flags;
     int k;                        // current iteration when a kernel is launched with k = 0
-    int pad;
+    int tile_base;                // index of the frame's first tile in the launch's tiles
     // Detection constants, derived from the parameters above by derive_detect_consts (on
     // the host, in the operations the detection would otherwise repeat per tile): the
     // FP32 thresholds sigclip and sigfrac * sigclip widened and narrowed by 2^-20
@@ -116,58 +114,83 @@ struct TileRef {                  // one (frame, tile origin) work item
     int frame, y0, x0, pad;
 };
 
-// Clears the counters and the nticket launch tickets; for frames with niter == 0 also
-// copies img into J and clears the mask (otherwise iteration 1 does both: detection
-// copies img into J and, when kFreshMask is set, clears the mask).  max_pixels: the
-// largest frame with niter == 0 (0 if none), which sizes the grid.
+// Lists of the tiles (by index in the launch's tiles) that an iteration visits: iteration k
+// >= 2 reads list k & 1 and appends to list (k + 1) & 1.  A list has nseg segments of cap
+// entries, tile g in segment g % nseg, each with its own counter (kTicketStride words
+// apart); the counters of list k are set k % 3 of three, and iteration k clears the set that
+// iteration k + 1 fills.  list[0] null: no lists (the tiles' marks alone say what to visit).
+struct StepLists {
+    unsigned int *list[2];
+    unsigned int *count;
+    int nseg, cap;
+};
+// Segments and words of the lists of ntiles tiles.
+inline int list_segments(size_t ntiles) {
+    int n = 1;
+    while (n < kListSegments && (size_t)(2 * n) <= ntiles)
+        n *= 2;
+    return n;
+}
+inline size_t list_cap(size_t ntiles) {
+    const size_t n = (size_t)list_segments(ntiles);
+    return (ntiles + n - 1) / n;
+}
+inline size_t list_words(size_t ntiles) {
+    const size_t n = (size_t)list_segments(ntiles);
+    return 2 * n * list_cap(ntiles) + 3 * n * kTicketStride;
+}
+inline StepLists make_lists(void *p, size_t ntiles) {
+    StepLists l;
+    l.nseg = list_segments(ntiles);
+    l.cap = (int)list_cap(ntiles);
+    l.list[0] = static_cast<unsigned int *>(p);
+    l.list[1] = l.list[0] + (size_t)l.nseg * l.cap;
+    l.count = l.list[1] + (size_t)l.nseg * l.cap;
+    return l;
+}
+
+// For frames with niter == 0: copies img into J and clears the mask (otherwise the first
+// detection does both).  max_pixels: the largest such frame, which sizes the grid.
 hipError_t launch_init(const DevFrame *d_frames, int nframes, const DevFrame &single,
-                       size_t max_pixels, unsigned int *tickets, int nticket, hipStream_t s);
+                       size_t max_pixels, hipStream_t s);
 
 // How a pass is launched (the autotuner's choices; every choice gives identical
-// results).  tile_h: detection tile rows (16, 32 or 64); persistent: detection by
-// resident blocks taking tiles from ticket counters instead of one block per tile;
-// fused: grow, count and replacement in one launch per iteration (each strip recomputes
-// its 2-row mask halo) instead of grow, list prefix and replacement; grow_h: rows of a
-// first-iteration grow strip of the three-launch path (8, 16 or 32).
+// results).  tile_h: tile rows of the first detection (16, 32 or 64); persistent: that
+// detection by resident blocks taking tiles from ticket counters instead of one block per
+// tile.  fused and grow_h are kept as set and have no effect.
 struct LaunchCfg {
     int tile_h = kDetectTYDefault;
     int persistent = 0;
     int fused = 0;
-    int grow_h = 0;          // 0: 32 for batches and large frames, 8 for small frames
+    int grow_h = 0;
 };
 
-// Detection (codes) for one frame (d_tiles == null: tiles over `single`) or a work list
-// of (frame, tile) built for cfg.tile_h.  Persistent launches take kTicketWords zeroed
-// words of ticket counters.
+// The first iteration's detection for one frame (d_tiles == null: tiles over `single`) or a
+// work list of (frame, tile) built for cfg.tile_h.  Persistent launches take kTicketWords
+// zeroed words of ticket counters.
 hipError_t launch_detect(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
-                         const DevFrame &single, int k, const LaunchCfg &cfg,
+                         const DevFrame &single, const LaunchCfg &cfg, const StepLists &lists,
                          unsigned int *tickets, hipStream_t s);
 // Number of detection tiles of an H x W frame at tile height tile_h.
 inline int detect_tiles(int H, int W, int tile_h) {
     return ((H + tile_h - 1) / tile_h) * ((W + kDetectTX - 1) / kDetectTX);
 }
-// Two-stage grow, new-flag count, cumulative mask and flagged list; with cfg.fused (and
-// no debug G2 plane) also the replacement, in one launch (then no list prefix and
-// replacement launch follow).  d_tiles lists 32-row strips of kGrowTX columns.  fresh:
-// every frame of the launch carries kFreshMask (then iteration 1 reads no mask rows; the
-// frames without it are tested at run time either way).
-hipError_t launch_grow(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
-                       const DevFrame &single, int k, bool fresh, const LaunchCfg &cfg,
-                       hipStream_t s);
-// Offsets of each frame's flagged list in one flat index space (batched path):
-// d_prefix[i] = sum of the list lengths of frames before i; d_prefix[n] = total.
-hipError_t launch_list_prefix(const DevFrame *d_frames, int nframes, int k,
-                              unsigned int *d_prefix, hipStream_t s);
-// Masked-median replacement of every pixel on the flagged lists (d_prefix from
-// launch_list_prefix for a batch; null for `single`).
-hipError_t launch_replace(const DevFrame *d_frames, int nframes, const unsigned int *d_prefix,
-                          const DevFrame &single, int k, int grid, hipStream_t s);
+// Iteration k from its codes on: grow, new-flag count, cumulative mask, replacement, and
+// (before the last) the next iteration's codes.  d_tiles: the summary tiles of the launch
+// (null: those of `single`); k == 0: each frame's own f.k, with no lists.  all: visit every
+// tile at every iteration (frames that re-evaluate every pixel).  tickets, if not null:
+// kTicketWords words that iteration 1 zeroes.
+hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
+                       const DevFrame &single, int k, bool all, const StepLists &lists,
+                       unsigned int *tickets, hipStream_t s);
 // Per-frame (iters_run, n_flagged) into d_stats[2 * i].
 hipError_t launch_stats(const DevFrame *d_frames, int nframes, long long *d_stats,
                         hipStream_t s);
 
-// Serving rounds: per frame, n_k of the iteration f.k just run and the running total
-// of flagged pixels, into d_stats[2 * i] and d_stats[2 * i + 1].
+// Serving rounds: per frame, whether the iteration f.k just run flagged a new pixel, and the
+// flagged pixels so far, into d_stats[2 * i] and d_stats[2 * i + 1].
+// (launch_count: the flagged pixels of one frame into *out.)
+hipError_t launch_count(const DevFrame &f, long long *out, hipStream_t s);
 hipError_t launch_round_stats(const DevFrame *d_frames, int nframes, long long *d_stats,
                               hipStream_t s);
 

@@ -339,39 +339,49 @@ static crb_status ensure_tables(crb_server *s, size_t bytes) {
     return CRB_OK;
 }
 
+// The tables of a round over `members`: frames, the first detection's tiles (of the frames at
+// iteration 1), every frame's tiles, and the results.
+struct RoundTables {
+    size_t ntd = 0, nts = 0;
+    size_t o_td, o_ts, o_st, bytes;
+    explicit RoundTables(const std::vector<Request *> &members) {
+        const size_t n = members.size();
+        for (const Request *r : members) {
+            const size_t t = (size_t)detect_tiles(r->H, r->W, kSumTY);
+            nts += t;
+            ntd += r->k_next == 1 ? t : 0;
+        }
+        auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+        o_td = al(n * sizeof(DevFrame));
+        o_ts = o_td + al(ntd * sizeof(TileRef));
+        o_st = o_ts + al(nts * sizeof(TileRef));
+        bytes = o_st + al(2 * n * sizeof(long long));
+    }
+};
+
 // one iteration for every active frame, at its own iteration index
 static crb_status launch_round(crb_server *s) {
     const int n = (int)s->active.size();
     if (n == 0)
         return CRB_OK;
-    size_t ntd = 0, ntg = 0, pix = 0;
-    for (Request *r : s->active) {
-        ntd += (size_t)detect_tiles(r->H, r->W, kDetectTYDefault);
-        ntg += (size_t)((r->H + kGrowTY - 1) / kGrowTY) * ((r->W + kGrowTX - 1) / kGrowTX);
-        pix += (size_t)r->H * r->W;
-    }
-    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t o_fr = 0, o_td = al(n * sizeof(DevFrame)), o_tg = o_td + al(ntd * sizeof(TileRef));
-    const size_t o_pre = o_tg + al(ntg * sizeof(TileRef));
-    const size_t o_st = o_pre + al((n + 1) * sizeof(unsigned int));
-    const size_t bytes = o_st + al(2 * n * sizeof(long long));
-    crb_status st = ensure_tables(s, bytes);
+    const RoundTables t(s->active);
+    crb_status st = ensure_tables(s, t.bytes);
     if (st != CRB_OK)
         return st;
-    DevFrame *hf = reinterpret_cast<DevFrame *>(s->h_tab + o_fr);
-    TileRef *htd = reinterpret_cast<TileRef *>(s->h_tab + o_td);
-    TileRef *htg = reinterpret_cast<TileRef *>(s->h_tab + o_tg);
-    size_t itd = 0, itg = 0;
+    DevFrame *hf = reinterpret_cast<DevFrame *>(s->h_tab);
+    TileRef *htd = reinterpret_cast<TileRef *>(s->h_tab + t.o_td);
+    TileRef *hts = reinterpret_cast<TileRef *>(s->h_tab + t.o_ts);
+    size_t itd = 0, its = 0;
     for (int i = 0; i < n; ++i) {
         Request *r = s->active[i];
         hf[i] = r->df;
         hf[i].k = r->k_next;
-        for (int y = 0; y < r->H; y += kDetectTYDefault)
-            for (int x = 0; x < r->W; x += kDetectTX)
-                htd[itd++] = TileRef{i, y, x, 0};
-        for (int y = 0; y < r->H; y += kGrowTY)
-            for (int x = 0; x < r->W; x += kGrowTX)
-                htg[itg++] = TileRef{i, y, x, 0};
+        for (int y = 0; y < r->H; y += kSumTY)
+            for (int x = 0; x < r->W; x += kSumTX) {
+                hts[its++] = TileRef{i, y, x, 0};
+                if (r->k_next == 1)
+                    htd[itd++] = TileRef{i, y, x, 0};
+            }
         if (r->need_wait) {
             hipError_t e = hipStreamWaitEvent(s->compute, r->ev_h2d, 0);
             if (e != hipSuccess)
@@ -379,31 +389,25 @@ static crb_status launch_round(crb_server *s) {
             r->need_wait = false;
         }
     }
-    const DevFrame *dfr = reinterpret_cast<const DevFrame *>(s->d_tab + o_fr);
-    const TileRef *dtd = reinterpret_cast<const TileRef *>(s->d_tab + o_td);
-    const TileRef *dtg = reinterpret_cast<const TileRef *>(s->d_tab + o_tg);
-    unsigned int *dpre = reinterpret_cast<unsigned int *>(s->d_tab + o_pre);
-    long long *dst = reinterpret_cast<long long *>(s->d_tab + o_st);
+    const DevFrame *dfr = reinterpret_cast<const DevFrame *>(s->d_tab);
+    const TileRef *dtd = reinterpret_cast<const TileRef *>(s->d_tab + t.o_td);
+    const TileRef *dts = reinterpret_cast<const TileRef *>(s->d_tab + t.o_ts);
+    long long *dst = reinterpret_cast<long long *>(s->d_tab + t.o_st);
     DevFrame none;
     memset(&none, 0, sizeof(none));
-    hipError_t e = hipMemcpyAsync(s->d_tab, s->h_tab, o_pre, hipMemcpyHostToDevice, s->compute);
-    // rounds mix frames at different iterations: the default launch shapes (one block per
-    // 32 x 64 detection tile, separate grow, list prefix and replacement)
+    hipError_t e = hipMemcpyAsync(s->d_tab, s->h_tab, t.o_st, hipMemcpyHostToDevice, s->compute);
+    // rounds mix frames at different iterations, so no list says which tiles to visit: every
+    // tile's block looks at its mark
     const LaunchCfg cfg;
+    const StepLists lists = {};
+    if (e == hipSuccess && t.ntd)
+        e = launch_detect(dfr, dtd, (int)t.ntd, none, cfg, lists, nullptr, s->compute);
     if (e == hipSuccess)
-        e = launch_init(dfr, n, none, (size_t)kMaxIter, nullptr, 0, s->compute);
-    if (e == hipSuccess)
-        e = launch_detect(dfr, dtd, (int)ntd, none, 0, cfg, nullptr, s->compute);
-    if (e == hipSuccess)
-        e = launch_grow(dfr, dtg, (int)ntg, none, 0, false, cfg, s->compute);
-    if (e == hipSuccess)
-        e = launch_list_prefix(dfr, n, 0, dpre, s->compute);
-    if (e == hipSuccess)
-        e = launch_replace(dfr, n, dpre, none, 0, replace_grid(pix), s->compute);
+        e = launch_step(dfr, dts, (int)t.nts, none, 0, false, lists, nullptr, s->compute);
     if (e == hipSuccess)
         e = launch_round_stats(dfr, n, dst, s->compute);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(s->h_tab + o_st, dst, 2 * n * sizeof(long long),
+        e = hipMemcpyAsync(s->h_tab + t.o_st, dst, 2 * n * sizeof(long long),
                            hipMemcpyDeviceToHost, s->compute);
     if (e == hipSuccess)
         e = hipEventRecord(s->ev_round, s->compute);
@@ -417,15 +421,8 @@ static crb_status launch_round(crb_server *s) {
 // the round finished: advance frames, start downloads of finished ones
 static crb_status finish_round(crb_server *s) {
     const int n = (int)s->round_members.size();
-    size_t ntd = 0, ntg = 0;
-    for (Request *r : s->round_members) {
-        ntd += (size_t)detect_tiles(r->H, r->W, kDetectTYDefault);
-        ntg += (size_t)((r->H + kGrowTY - 1) / kGrowTY) * ((r->W + kGrowTX - 1) / kGrowTX);
-    }
-    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t o_st = al(n * sizeof(DevFrame)) + al(ntd * sizeof(TileRef)) +
-                        al(ntg * sizeof(TileRef)) + al((n + 1) * sizeof(unsigned int));
-    const long long *stats = reinterpret_cast<const long long *>(s->h_tab + o_st);
+    const long long *stats = reinterpret_cast<const long long *>(
+        s->h_tab + RoundTables(s->round_members).o_st);
     std::vector<Request *> still;
     for (int i = 0; i < n; ++i) {
         Request *r = s->round_members[i];
