@@ -39,7 +39,12 @@ __device__ __forceinline__ void detect_tile(const DevFrame &f, int y0, int x0, i
         return;
     const int H = f.H, W = f.W;
     detect_clear(s, tid);
-    stage_j(s, f.img, H, W, y0, x0, tid);
+    JStage<L, 4> stage;
+#pragma unroll
+    for (int b0 = 0; b0 < stage.kBlocks; b0 += stage.kRound) {
+        stage.load(f.img, H, W, y0, x0, tid, b0);
+        stage.store(s, tid, b0);
+    }
     if (f.count && y0 == 0 && x0 == 0) {
         for (int i = tid; i < f.niter; i += NT)
             f.any_new[i] = 0u;

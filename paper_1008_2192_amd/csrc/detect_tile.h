@@ -449,7 +449,7 @@ struct DetectLds {
     uint32_t u[kTileWords], upre[kTileWords + 1];   // pixels left to binary64
     // tile cells where S may exceed sigfrac*sigclip; after the work-set build, Q' itself
     uint32_t low[kTileWords];
-    unsigned int err_bits, contrast, uncertain, qcount, need, exact_cells, con_count;
+    unsigned int err_bits, contrast, uncertain, qcount, need, exact_cells, con_count, any_hot;
     uint16_t quads[kQuads];
     uint16_t list[kListMax];                    // work set Q' (up to kListMax)
     // pixels whose contrast test is left to the contrast phase: position, S' interval, N
@@ -468,13 +468,16 @@ struct DetectLds {
     __device__ __forceinline__ float *j4() { return &J[(AP - 4) * (JWP + 1)]; }
 };
 
-// Clears the bitmaps, the code planes and the counters of a tile (before the first barrier).
-template <class L>
-__device__ __forceinline__ void detect_clear(L &s, int tid) {
+// Clears the bitmaps and the counters of a tile, and its code planes (SPARSE: the caller
+// fills them with the codes that stay), before the first barrier.
+template <int TY, int AP, bool SPARSE>
+__device__ __forceinline__ void detect_clear(DetectLds<TY, AP, SPARSE> &s, int tid) {
+    using L = DetectLds<TY, AP, SPARSE>;
     for (int i = tid; i < L::HR * L::HWP + 1; i += L::NT)
         s.hotp[i] = 0u;
-    for (int i = tid; i < 3 * L::kTileWords; i += L::NT)
-        s.code[i] = 0u;
+    if constexpr (!SPARSE)
+        for (int i = tid; i < 3 * L::kTileWords; i += L::NT)
+            s.code[i] = 0u;
     for (int i = tid; i < L::kTileWords; i += L::NT) {
         s.u[i] = 0u;
         s.low[i] = 0u;
@@ -487,61 +490,58 @@ __device__ __forceinline__ void detect_clear(L &s, int tid) {
         s.need = 0u;
         s.exact_cells = 0u;
         s.con_count = 0u;
+        s.any_hot = 0u;
         s.ncells = 0u;
     }
 }
 
-// Stages J over [y0 - AP, y0 + TY + AP) x [x0 - AP, x0 + TX + AP), clamped reads.  Thread t
-// loads column t % JW of rows t / JW + kJStep * b, so its clamped column is computed once
-// and, on tiles whose rows are all inside the frame, each further row costs one address
-// step.  A thread's loads (all of them, or half when there are more than 16) are issued
-// before its first LDS store, so their latencies overlap.
-template <int TY, int AP, bool SPARSE>
-__device__ __forceinline__ void stage_j(DetectLds<TY, AP, SPARSE> &s, const float *__restrict__ J,
-                                        int H, int W, int y0, int x0, int tid) {
-    using L = DetectLds<TY, AP, SPARSE>;
-    constexpr int kJStep = L::NT / L::JW;
-    constexpr int NB = (L::JH + kJStep - 1) / kJStep;
-    constexpr int NC = NB > 16 ? (NB + 1) / 2 : NB;      // loads in flight per round
-    const int c = tid % L::JW, r0 = tid / L::JW;
-    if (r0 >= kJStep)
-        return;
-    const int cc = clampi(x0 - AP + c, W);
-    if (y0 >= AP && y0 + TY + AP <= H && (long long)L::JH * W * 4 <= 0x7fffffffll) {
-        // buffer loads over the JH staged rows (below 2^31 bytes, so the byte count, the
-        // lane offsets and the row steps below are exact in int): a per-lane byte offset
-        // and a uniform row step, so a further row costs no vector instruction
-        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(J + (size_t)(y0 - AP) * W), (short)0, L::JH * W * 4, kBufferWord3);
-        const int boff = (r0 * W + cc) * 4;
+// Staging of J over [y0 - AP, y0 + TY + AP) x [x0 - AP, x0 + TX + AP), clamped reads.
+// Thread t takes column t % JW of rows t / JW + kStep * b, so its clamped column is computed
+// once and, on tiles whose rows are all inside the frame, each further row costs one address
+// step.  A thread's loads (or a round of them, from row block b0) are all issued before its
+// first LDS store, so their latencies overlap.
+template <class L, int AP>
+struct JStage {
+    static constexpr int kStep = L::NT / L::JW;
+    static constexpr int kBlocks = (L::JH + kStep - 1) / kStep;
+    static constexpr int kRound = kBlocks > 16 ? (kBlocks + 1) / 2 : kBlocks;
+    float v[kRound];
+
+    __device__ __forceinline__ void load(const float *__restrict__ J, int H, int W, int y0, int x0,
+                                         int tid, int b0) {
+        const int c = tid % L::JW, r0 = tid / L::JW;
+        if (r0 >= kStep)
+            return;
+        const int cc = clampi(x0 - AP + c, W);
+        if (y0 >= AP && y0 - AP + L::JH <= H && (long long)L::JH * W * 4 <= 0x7fffffffll) {
+            // buffer loads over the JH staged rows (below 2^31 bytes, so the byte count, the
+            // lane offsets and the row steps below are exact in int): a per-lane byte offset
+            // and a uniform row step, so a further row costs no vector instruction
+            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(J + (size_t)(y0 - AP) * W), (short)0, L::JH * W * 4, kBufferWord3);
+            const int boff = (r0 * W + cc) * 4;
 #pragma unroll
-        for (int b0 = 0; b0 < NB; b0 += NC) {
-            float v[NC];
-#pragma unroll
-            for (int b = 0; b < NC; ++b)
-                if (b0 + b < NB && r0 + kJStep * (b0 + b) < L::JH)
+            for (int b = 0; b < kRound; ++b)
+                if (b0 + b < kBlocks && r0 + kStep * (b0 + b) < L::JH)
                     v[b] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                        rows, boff, kJStep * (b0 + b) * W * 4, 0));
+                        rows, boff, kStep * (b0 + b) * W * 4, 0));
+        } else {
 #pragma unroll
-            for (int b = 0; b < NC; ++b)
-                if (b0 + b < NB && r0 + kJStep * (b0 + b) < L::JH)
-                    s.J[(r0 + kJStep * (b0 + b)) * L::JWP + c] = v[b];
-        }
-    } else {
-#pragma unroll
-        for (int b0 = 0; b0 < NB; b0 += NC) {
-            float v[NC];
-#pragma unroll
-            for (int b = 0; b < NC; ++b)
-                if (b0 + b < NB && r0 + kJStep * (b0 + b) < L::JH)
-                    v[b] = J[(size_t)clampi(y0 - AP + r0 + kJStep * (b0 + b), H) * W + cc];
-#pragma unroll
-            for (int b = 0; b < NC; ++b)
-                if (b0 + b < NB && r0 + kJStep * (b0 + b) < L::JH)
-                    s.J[(r0 + kJStep * (b0 + b)) * L::JWP + c] = v[b];
+            for (int b = 0; b < kRound; ++b)
+                if (b0 + b < kBlocks && r0 + kStep * (b0 + b) < L::JH)
+                    v[b] = J[(size_t)clampi(y0 - AP + r0 + kStep * (b0 + b), H) * W + cc];
         }
     }
-}
+    __device__ __forceinline__ void store(L &s, int tid, int b0) const {
+        const int c = tid % L::JW, r0 = tid / L::JW;
+        if (r0 >= kStep)
+            return;
+#pragma unroll
+        for (int b = 0; b < kRound; ++b)
+            if (b0 + b < kBlocks && r0 + kStep * (b0 + b) < L::JH)
+                s.J[(r0 + kStep * (b0 + b)) * L::JWP + c] = v[b];
+    }
+};
 
 // Sets the code bits of tile position pos (r * 64 + c).
 template <class L>
@@ -556,26 +556,10 @@ __device__ __forceinline__ void set_code(L &s, int pos, bool first, bool high, b
         atomicOr(&s.code[2 * L::kTileWords + w], b);
 }
 
-// Where A lies in a summary tile, as one bit per direction: bit 3 (dy + 1) + dx + 1 is set
-// when A holds within 8 pixels of the neighbouring tile in direction (dy, dx) (bit 4: anywhere
-// in the tile), 8 pixels being the reach of an iteration.  m, left, right: bit r set when A
-// holds in row r of the tile (from its row 0), in its first or last 8 columns there.
-__device__ __forceinline__ uint32_t reach_bits(uint32_t m, uint32_t left, uint32_t right) {
-    uint32_t o = 0u;
-#pragma unroll
-    for (int dy = -1; dy <= 1; ++dy) {
-        const uint32_t rows = dy < 0 ? 0xFFu : (dy > 0 ? 0xFF000000u : 0xFFFFFFFFu);
-        o |= (left & rows) ? 1u << (3 * (dy + 1)) : 0u;
-        o |= (m & rows) ? 2u << (3 * (dy + 1)) : 0u;
-        o |= (right & rows) ? 4u << (3 * (dy + 1)) : 0u;
-    }
-    return o;
-}
-
 // The detection of one staged tile (origin y0, x0 of frame f), by the whole block: the code
-// bits of the tile's in-frame pixels into s.code (cleared by detect_clear; s.J staged, and
-// both visible to the block), visible to the whole block on return.
-// With SPARSE only the pixels of s.act are evaluated, from the S cells of s.reach (at
+// bits of the tile's in-frame pixels ORed into s.code (cleared; s.J staged, and both visible
+// to the block), visible to the whole block on return.
+// With SPARSE only the pixels of s.act are evaluated (s.code cleared there), from the S cells of s.reach (at
 // least the cells within 2 of s.act) and the cell tiles listed in s.cells.
 //
 // Which pixels need S', F^ and the threshold bits.  With H = {S > sigclip} (S' > t
@@ -668,6 +652,8 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
             const int gy = y0 - 2 + r5 + i;
             bits = (gy >= 0 && gy < H) ? bits & colmask : 0u;
             if (bits) {
+                if (SPARSE)
+                    s.any_hot = 1u;
                 const int w = c5 >> 5, sh = c5 & 31;
                 atomicOr(&sHot[(r5 + i) * L::HWP + w], bits << sh);
                 if (sh > 32 - TTX && (bits >> (32 - sh)))
@@ -676,6 +662,8 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
         }
     }
     __syncthreads();
+    if (SPARSE && !s.any_hot)
+        return;           // S <= sigclip at every pixel that matters: no code bit is set
     // The later stages read S (to within the block's largest error bound) and med5(J)
     // only within 4 cells of H': the work set lies within 2 of H', and med5(S) at a work
     // pixel reads 2 further (a clamped neighbour's cell is no farther).  That region, in
@@ -816,14 +804,19 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
     __syncthreads();
 
     // Region cells outside the image must hold the value of their clamped cell: the
-    // windows of the work set read S at clamped neighbour positions.
+    // windows of the work set read S at clamped neighbour positions, at most two rows and
+    // columns past the frame's edges.
     if (y0 < 2 || x0 < 2 || y0 + TY + 2 > H || x0 + TX + 2 > W) {
-        for (int i = tid; i < L::SH * L::SW; i += NT) {
-            const int r = i / L::SW, c = i - r * L::SW;
-            const int gy = y0 - 2 + r, gx = x0 - 2 + c;
-            if (gy < 0 || gy >= H || gx < 0 || gx >= W)
-                s.S[r * L::SWP + c] =
-                    s.S[(clampi(gy, H) - (y0 - 2)) * L::SWP + (clampi(gx, W) - (x0 - 2))];
+        for (int i = tid; i < 4 * (L::SW + L::SH); i += NT) {
+            // rows -2, -1, H, H + 1 of the frame, then its columns -2, -1, W, W + 1
+            const bool row = i < 4 * L::SW;
+            const int q = row ? i / L::SW : (i - 4 * L::SW) / L::SH;
+            const int o = row ? i - q * L::SW : i - 4 * L::SW - q * L::SH;
+            const int e = q < 2 ? q - 2 : (row ? H : W) + q - 2;
+            const int r = row ? e - (y0 - 2) : o, c = row ? o : e - (x0 - 2);
+            if (r >= 0 && r < L::SH && c >= 0 && c < L::SW)
+                s.S[r * L::SWP + c] = s.S[(clampi(y0 - 2 + r, H) - (y0 - 2)) * L::SWP +
+                                          (clampi(x0 - 2 + c, W) - (x0 - 2))];
         }
     }
     const float emax = __uint_as_float(s.err_bits);

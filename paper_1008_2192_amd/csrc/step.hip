@@ -14,6 +14,10 @@
 // ms, a 256 x 256 frame 84 -> 51 us, 61 x 67 68 -> 32 us, a 4096 x 4096 crowded field 0.43 ->
 // 0.38 ms, against three or four launches an iteration that each passed over the frame
 // (detection of every pixel, grow over code bytes, flagged list, replacement by gathers).
+// A tile is bound by the latency of its chain (waves wait 71% of their cycles, VALU issue is
+// at half its rate): with J's loads in flight during the grow, rows in 32-bit words and no
+// pass over the staged cells past the frame's edges, the first iteration of the batch took
+// 1.48 -> 1.11 ms, and the second, whose tile records now load as scalars, 0.24 -> 0.15 ms.
 //
 // Blocks share their halos without ordering.  Codes are double-buffered per tile.  The mask
 // bitmap of a neighbour may be read before or after its owner ORs G2 into it: the reader ORs
@@ -25,10 +29,11 @@
 
 namespace crb {
 
-// A row of 80 pixels, columns x0 - 8 .. x0 + 71 of a tile: bit j of lo, then of hi.
+// A row of 80 pixels, columns x0 - 8 .. x0 + 71 of a tile: bit j % 32 of word j / 32.  (A
+// dilation may spread into the unused bits 80 .. 95, and back no further than it would on a
+// longer row.)
 struct Row80 {
-    unsigned long long lo;
-    uint32_t hi;
+    uint32_t w[3];
 };
 
 __device__ __forceinline__ uint32_t lane_above(uint32_t v) {      // lane - 1 (0 at lane 0)
@@ -37,48 +42,52 @@ __device__ __forceinline__ uint32_t lane_above(uint32_t v) {      // lane - 1 (0
 __device__ __forceinline__ uint32_t lane_below(uint32_t v) {      // lane + 1 (0 at lane 63)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, false);
 }
-__device__ __forceinline__ unsigned long long pack64(uint32_t lo, uint32_t hi) {
-    return ((unsigned long long)hi << 32) | lo;
+// Bits s .. s + 31 of the pair (hi, lo), s < 32.
+__device__ __forceinline__ uint32_t bits_at(uint32_t hi, uint32_t lo, int s) {
+    return __builtin_amdgcn_alignbit(hi, lo, (uint32_t)s);
 }
 
-// 3x3 dilation of the 80-bit rows held one per lane (rows outside the lanes are empty; bits
-// past the ends of a row are lost).
+// 3x3 dilation of the rows held one per lane (rows outside the lanes are empty).
 __device__ __forceinline__ Row80 dilate(const Row80 &r) {
-    Row80 h;
-    h.lo = r.lo | (r.lo << 1) | (r.lo >> 1) | ((unsigned long long)r.hi << 63);
-    h.hi = (r.hi | (r.hi << 1) | (r.hi >> 1) | (uint32_t)(r.lo >> 63)) & 0xFFFFu;
-    const uint32_t a = (uint32_t)h.lo, b = (uint32_t)(h.lo >> 32);
+    const uint32_t a = r.w[0], b = r.w[1], c = r.w[2];
+    const uint32_t h[3] = {a | a << 1 | bits_at(b, a, 1), b | bits_at(b, a, 31) | bits_at(c, b, 1),
+                           c | bits_at(c, b, 31) | c >> 1};
     Row80 o;
-    o.lo = h.lo | pack64(lane_above(a), lane_above(b)) | pack64(lane_below(a), lane_below(b));
-    o.hi = h.hi | lane_above(h.hi) | lane_below(h.hi);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        o.w[i] = h[i] | lane_above(h[i]) | lane_below(h[i]);
     return o;
 }
 __device__ __forceinline__ Row80 row_and(const Row80 &a, const Row80 &b) {
-    return Row80{a.lo & b.lo, a.hi & b.hi};
+    return Row80{{a.w[0] & b.w[0], a.w[1] & b.w[1], a.w[2] & b.w[2]}};
 }
 __device__ __forceinline__ Row80 row_or(const Row80 &a, const Row80 &b) {
-    return Row80{a.lo | b.lo, a.hi | b.hi};
+    return Row80{{a.w[0] | b.w[0], a.w[1] | b.w[1], a.w[2] | b.w[2]}};
 }
-// Columns 64 .. 127 of a triple of 64-bit words with 8 bits of either neighbour.
+// A tile's 64 columns with 8 columns of either neighbour.
 __device__ __forceinline__ Row80 row80(unsigned long long left, unsigned long long mid,
                                        unsigned long long right) {
-    return Row80{(left >> 56) | (mid << 8),
-                 (uint32_t)(mid >> 56) | (uint32_t)(right & 0xFFull) << 8};
+    const uint32_t m0 = (uint32_t)mid, m1 = (uint32_t)(mid >> 32);
+    return Row80{{bits_at(m0, (uint32_t)(left >> 32), 24), bits_at(m1, m0, 24),
+                  bits_at((uint32_t)right, m1, 24) & 0xFFFFu}};
 }
 // The tile's own 64 columns of a row.
 __device__ __forceinline__ unsigned long long own64(const Row80 &r) {
-    return (r.lo >> 8) | ((unsigned long long)(r.hi & 0xFFu) << 56);
+    return (unsigned long long)bits_at(r.w[2], r.w[1], 8) << 32 | bits_at(r.w[1], r.w[0], 8);
+}
+// Bit c (0 .. 79) of a row.
+__device__ __forceinline__ uint32_t row_bit(const Row80 &r, int c) {
+    return (c < 32 ? r.w[0] : (c < 64 ? r.w[1] : r.w[2])) >> (c & 31) & 1u;
 }
 
 using StepLds = DetectLds<32, 6, true>;
 constexpr int kRepMax = 1024;       // listed pixels to replace; further ones from the bitmap
 struct StepShared {
     StepLds d;
-    // rows y0 - 8 .. y0 + 39: M_k (at clamped columns) and the pixels to replace (D4 of the
-    // tile); and G2 of the tile's own rows for the parity tests
-    unsigned long long m_lo[48], r_lo[48];
-    uint32_t m_hi[48], r_hi[48];
-    unsigned int nrep;
+    // rows y0 - 8 .. y0 + 39: M_k (at clamped columns; a fourth word for two-word reads) and
+    // the pixels to replace (within 4 of the tile)
+    uint32_t m[48][4], r[48][3];
+    unsigned int nrep, buf;
 };
 static_assert(kRepMax * 2 <= (int)sizeof(StepLds::S), "the replacement list in the S plane");
 static_assert(sizeof(StepShared) <= 32768, "five blocks per CU");
@@ -129,15 +138,18 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
     const bool last = k >= f.niter;
     // a counting run of a frame without kIncremental re-evaluates the whole tile
     const bool full = (f.flags & kCountWork) && !(f.flags & kIncremental);
-    const float *J = k == 1 ? f.img : f.J;
 
     detect_clear(s, tid);
+    JStage<L, 6> stage;
+    static_assert(stage.kRound == stage.kBlocks, "one round");
+    stage.load(k == 1 ? f.img : f.J, H, W, y0, x0, tid, 0);
     if (tid < 64) {
         // the grow: lane l holds row y0 - 8 + l
         const int y = y0 - 8 + lane, vt = ty + (lane < 8 ? -1 : (lane < 40 ? 0 : 1));
         const int rr = y & (kSumTY - 1);
         const bool row_ok = lane < 48 && y >= 0 && y < H;
         unsigned long long w[4][3];            // planes A, high, low; mask -- left, own, right
+        unsigned int own_buf = 0u;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const int vx = tx + d - 1;
@@ -159,14 +171,15 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
                 w[2][d] = b[2 * kSumTY];
                 if (k > 1 || !(f.flags & kFreshMask))
                     w[3][d] = f.mbits[t * kSumTY + rr];
+                own_buf = d == 1 ? buf : own_buf;
             }
         }
         const Row80 a = row80(w[0][0], w[0][1], w[0][2]), hi = row80(w[1][0], w[1][1], w[1][2]);
         const Row80 lo = row80(w[2][0], w[2][1], w[2][2]), mp = row80(w[3][0], w[3][1], w[3][2]);
         const Row80 g2 = row_and(dilate(row_and(dilate(a), hi)), lo);
         Row80 m = row_or(mp, g2);
-        const bool own = lane >= 8 && lane < 40 && y < H;
-        const unsigned long long nw = own ? own64(g2) & ~w[3][1] : 0ull;
+        const bool tile_row = lane >= 8 && lane < 40;
+        const unsigned long long nw = tile_row && y < H ? own64(g2) & ~w[3][1] : 0ull;
         if (nw)
             f.mbits[((size_t)ty * ntx + tx) * kSumTY + rr] = own64(m);
         const unsigned int n = __ockl_wfred_add_u32((unsigned int)__popcll(nw));
@@ -176,7 +189,7 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
             atomicAdd(&f.count[(blockIdx.x % kCountSlots) * kCountStride], (unsigned long long)n);
             f.any_new[k - 1] = 1u;
         }
-        if (f.g2 && own)       // parity tests
+        if (f.g2 && tile_row && y < H)       // parity tests
             for (int c = 0; c < kSumTX && x0 + c < W; ++c)
                 f.g2[(size_t)y * W + x0 + c] = (uint8_t)(own64(g2) >> c & 1ull);
         // The pixels to replace: at iteration 1 all of M_k; later those of M_k with a pixel
@@ -185,55 +198,67 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
         Row80 rp = k == 1 ? m : row_and(m, dilate(dilate(g2)));
         // within 4 of the tile: rows 4 .. 43, columns 4 .. 75 of the region
         const bool r4 = lane >= 4 && lane < 44;
-        rp.lo &= r4 ? ~0xFull : 0ull;
-        rp.hi &= r4 ? 0xFFFu : 0u;
-        // the codes that can change lie within 4 of those, and read S within 2 more
-        const bool tile_row = lane >= 8 && lane < 40;
-        Row80 act = full ? Row80{~0ull, 0xFFFFu} : dilate(dilate(dilate(dilate(rp))));
-        act.lo &= tile_row ? ~0xFFull : 0ull;
-        act.hi &= tile_row ? 0xFFu : 0u;
+        rp.w[0] &= r4 ? ~0xFu : 0u;
+        rp.w[1] &= r4 ? ~0u : 0u;
+        rp.w[2] &= r4 ? 0xFFFu : 0u;
+        // the tile's codes that can change lie within 4 of those, and read S within 2 more
+        Row80 act = full ? Row80{{~0u, ~0u, 0xFFFFu}} : dilate(dilate(dilate(dilate(rp))));
+        act.w[0] &= tile_row ? ~0xFFu : 0u;
+        act.w[1] &= tile_row ? ~0u : 0u;
+        act.w[2] &= tile_row ? 0xFFu : 0u;
         const Row80 reach = dilate(dilate(act));
         if (tile_row) {
             const unsigned long long c = own64(act);
-            s.act[2 * (lane - 8)] = (uint32_t)c;
-            s.act[2 * (lane - 8) + 1] = (uint32_t)(c >> 32);
+            const int q = 2 * (lane - 8);
+            s.act[q] = (uint32_t)c;
+            s.act[q + 1] = (uint32_t)(c >> 32);
+            // the codes that stay, to which the detection adds
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const unsigned long long v = w[p][1] & ~c;
+                s.code[p * L::kTileWords + q] = (uint32_t)v;
+                s.code[p * L::kTileWords + q + 1] = (uint32_t)(v >> 32);
+            }
         }
+        if (lane == 8)
+            sh.buf = own_buf;
         if (lane >= 6 && lane < 42) {          // the S region: rows 6 .. 41, columns 6 .. 73
             uint32_t *q = &s.reach[(lane - 6) * L::HW];
-            q[0] = (uint32_t)(reach.lo >> 6);
-            q[1] = (uint32_t)(reach.lo >> 38) | reach.hi << 26;
-            q[2] = (reach.hi >> 6) & 0xFu;
+            q[0] = bits_at(reach.w[1], reach.w[0], 6);
+            q[1] = bits_at(reach.w[2], reach.w[1], 6);
+            q[2] = (reach.w[2] >> 6) & 0xFu;
         }
         // M_k at clamped columns: the windows read it two columns past the frame's edges
         if (x0 == 0)
-            m.lo |= (m.lo >> 8 & 1ull) * 0xC0ull;
+            m.w[0] |= (m.w[0] >> 8 & 1u) * 0xC0u;
         const int e = W - 1 - x0 + 8;          // the region column of the last frame column
         if (e < 78) {
-            const uint32_t b = e < 64 ? (uint32_t)(m.lo >> e) & 1u : (m.hi >> (e - 64)) & 1u;
-            for (int c = e + 1; c <= e + 2; ++c) {
-                m.lo |= c < 64 ? (unsigned long long)b << c : 0ull;
-                m.hi |= c >= 64 ? b << (c - 64) : 0u;
-            }
+            const uint32_t b = row_bit(m, e);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int c = 1; c <= 2; ++c)
+                    m.w[i] |= (e + c) >> 5 == i ? b << ((e + c) & 31) : 0u;
         }
         if (lane < 48) {
-            sh.m_lo[lane] = m.lo;
-            sh.m_hi[lane] = m.hi;
-            sh.r_lo[lane] = rp.lo;
-            sh.r_hi[lane] = rp.hi;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                sh.m[lane][i] = m.w[i];
+                sh.r[lane][i] = rp.w[i];
+            }
         }
         // list them (in any order): region position row * 80 + column
-        const unsigned int cnt = (unsigned int)__popcll(rp.lo) + (unsigned int)__popc(rp.hi);
+        const unsigned int cnt = (unsigned int)(__popc(rp.w[0]) + __popc(rp.w[1]) + __popc(rp.w[2]));
         unsigned int at = __ockl_wfscan_add_u32(cnt, false);
         if (lane == 63)
             sh.nrep = at + cnt;
-        for (unsigned long long v = rp.lo; v; v &= v - 1ull, ++at)
-            if (at < (unsigned int)kRepMax)
-                rep[at] = (uint16_t)(lane * 80 + __ffsll((long long)v) - 1);
-        for (uint32_t v = rp.hi; v; v &= v - 1u, ++at)
-            if (at < (unsigned int)kRepMax)
-                rep[at] = (uint16_t)(lane * 80 + 64 + __ffs((int)v) - 1);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            for (uint32_t v = rp.w[i]; v; v &= v - 1u, ++at)
+                if (at < (unsigned int)kRepMax)
+                    rep[at] = (uint16_t)(lane * 80 + 32 * i + __ffs((int)v) - 1);
     }
-    stage_j(s, J, H, W, y0, x0, tid);
+    stage.store(s, tid, 0);
     __syncthreads();
     const int nrep = (int)sh.nrep;
     if (nrep == 0 && !full)
@@ -246,26 +271,28 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
     for (int i = tid; i < (listed ? nrep : 48 * 80); i += L::NT) {
         const int pos = listed ? (int)rep[i] : i;
         const int r = pos / 80, c = pos - r * 80;
-        const unsigned long long in = c < 64 ? sh.r_lo[r] >> c : sh.r_hi[r] >> (c - 64);
-        if (!listed && !(in & 1ull))
+        if (!listed && !(sh.r[r][c >> 5] >> (c & 31) & 1u))
             continue;
         const int y = y0 - 8 + r, x = x0 - 8 + c;
         uint32_t fl = 0u;
 #pragma unroll
         for (int i5 = 0; i5 < 5; ++i5) {
-            const int q = clampi(y + i5 - 2, H) - y0 + 8, sft = c - 2;
-            const unsigned long long lo = sh.m_lo[q];
-            const uint32_t hi = sh.m_hi[q];
-            const uint32_t b = sft < 64 ? (uint32_t)((lo >> sft) |
-                                                     (unsigned long long)hi << (64 - sft))
-                                        : hi >> (sft - 64);
-            fl |= (b & 31u) << (5 * i5);
+            const uint32_t *q = &sh.m[clampi(y + i5 - 2, H) - y0 + 8][(c - 2) >> 5];
+            fl |= (bits_at(q[1], q[0], (c - 2) & 31) & 31u) << (5 * i5);
         }
-        float *p = &s.J[(r - 2) * L::JWP + c - 2];
+        const int jr = r - 2, jc = c - 2;
         float nv;
         const bool mine = r >= 8 && r < 40 && c >= 8 && c < 72;
-        if (window_median(p, L::JWP, fl, nv)) {
-            *p = nv;
+        if (window_median(&s.J[jr * L::JWP + jc], L::JWP, fl, nv)) {
+            s.J[jr * L::JWP + jc] = nv;
+            // the staged cells past the frame's edges that repeat this pixel
+            if (y == 0 || y == H - 1 || x == 0 || x == W - 1) {
+                const int ra = y == 0 ? 0 : jr, rb = y == H - 1 ? L::JH - 1 : jr;
+                const int ca = x == 0 ? 0 : jc, cb = x == W - 1 ? L::JW - 1 : jc;
+                for (int q = ra; q <= rb; ++q)
+                    for (int p = ca; p <= cb; ++p)
+                        s.J[q * L::JWP + p] = nv;
+            }
             if (mine)
                 f.J[(size_t)y * W + x] = nv;
         }
@@ -280,45 +307,34 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
         const uint32_t *q = &s.reach[2 * rp * L::HW + w];
         const uint32_t lo = q[0] | q[L::HW];
         const uint32_t hi = w + 1 < L::HW ? q[1] | q[L::HW + 1] : 0u;
-        if ((uint32_t)(pack64(lo, hi) >> sft) & 31u)
+        if (bits_at(hi, lo, sft) & 31u)
             s.cells[atomicAdd(&s.ncells, 1u)] = (uint16_t)(rp * 16 + cx);
     }
     __syncthreads();
-    // staged cells outside the frame follow the pixel they repeat
-    if (y0 < 6 || x0 < 6 || y0 + kSumTY + 6 > H || x0 + kSumTX + 6 > W) {
-        for (int i = tid; i < L::JH * L::JW; i += L::NT) {
-            const int r = i / L::JW, c = i - r * L::JW;
-            const int gy = y0 - 6 + r, gx = x0 - 6 + c;
-            if (gy < 0 || gy >= H || gx < 0 || gx >= W)
-                s.J[r * L::JWP + c] =
-                    s.J[(clampi(gy, H) - y0 + 6) * L::JWP + clampi(gx, W) - x0 + 6];
-        }
-        __syncthreads();
-    }
     detect_staged(s, f, y0, x0, tid);
 
     // the tile's codes of iteration k + 1 into its other buffer, and the tiles it lists
     if (tid < 64) {
         const size_t t = (size_t)ty * ntx + tx;
-        const unsigned int buf = f.state[t] & 1u;
-        unsigned long long a = 0ull;
-        if (lane < kSumTY) {
-            const unsigned long long *code = reinterpret_cast<const unsigned long long *>(s.code);
-            const unsigned long long act = pack64(s.act[2 * lane], s.act[2 * lane + 1]);
-            const unsigned long long *b = f.bits + (t * 2 + buf) * (3 * kSumTY) + lane;
-            unsigned long long *o = f.bits + (t * 2 + (buf ^ 1u)) * (3 * kSumTY) + lane;
+        const unsigned int buf = sh.buf ^ 1u;
+        const unsigned long long *code = reinterpret_cast<const unsigned long long *>(s.code);
+        unsigned long long *o = f.bits + (t * 2 + buf) * (3 * kSumTY);
+        o[lane] = code[lane];
+        if (lane < kSumTY)
+            o[64 + lane] = code[64 + lane];
+        // where A lies: bit 3 (dy + 1) + dx + 1 when it is within 8 pixels (an iteration's
+        // reach) of the neighbour in direction (dy, dx)
+        const unsigned long long a = lane < kSumTY ? code[lane] : 0ull;
+        const uint32_t all = (uint32_t)__ballot(a != 0ull);
+        const uint32_t left = (uint32_t)__ballot((a & 0xFFull) != 0ull);
+        const uint32_t right = (uint32_t)__ballot((a >> 56) != 0ull);
+        uint32_t dirs = 0u;
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const unsigned long long v =
-                    y0 + lane < H ? (b[p * kSumTY] & ~act) | code[p * kSumTY + lane] : 0ull;
-                o[p * kSumTY] = v;
-                if (p == 0)
-                    a = v;
-            }
+        for (int q = 0; q < 3; ++q) {
+            const uint32_t rows = q == 0 ? 0xFFu : (q == 1 ? ~0u : 0xFF000000u);
+            dirs |= ((left & rows) ? 1u : 0u) << (3 * q) | ((all & rows) ? 2u : 0u) << (3 * q) |
+                    ((right & rows) ? 4u : 0u) << (3 * q);
         }
-        const uint32_t dirs = reach_bits((uint32_t)__ballot(a != 0ull),
-                                         (uint32_t)__ballot((a & 0xFFull) != 0ull),
-                                         (uint32_t)__ballot((a >> 56) != 0ull));
         // The next iteration has work only within reach of A.  Every tile that holds A now
         // was re-evaluated in this launch (a tile with A at iteration k replaces pixels, A
         // being part of G2), so each lists the tiles that its own A reaches
@@ -327,7 +343,7 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
         const bool there = lane < 9 && vy >= 0 && vy < nty && vx >= 0 && vx < ntx;
         const size_t v = (size_t)(there ? vy : ty) * ntx + (there ? vx : tx);
         if (lane == 0)
-            f.state[t] = 2u * (unsigned int)(k + 1) | (buf ^ 1u);
+            f.state[t] = 2u * (unsigned int)(k + 1) | buf;
         if (there && (dirs >> lane & 1u) &&
             atomicMax(&f.mark[v], (unsigned int)(k + 1)) < (unsigned int)(k + 1) && lists.list[0])
             list_tile(lists, k + 1, f.tile_base + (int)v);
@@ -399,7 +415,9 @@ void k_step_listed(const DevFrame *__restrict__ frames, const TileRef *__restric
         // as in the persistent detection, thread-derived values are not held across tiles
         int tid = (int)threadIdx.x;
         asm volatile("" : "+v"(tid));
-        step_one(frames, tiles, single, (int)list[e], kiter, false, lists, sh, tid);
+        // (uniform: the tile and frame records then load into scalar registers)
+        const int g = __builtin_amdgcn_readfirstlane((int)list[e]);
+        step_one(frames, tiles, single, g, kiter, false, lists, sh, tid);
         __syncthreads();       // the tile is done with the LDS
     }
 }
