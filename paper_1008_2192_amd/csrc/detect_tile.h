@@ -404,16 +404,35 @@ __device__ __forceinline__ void list_append(uint32_t m, int pos0, uint16_t *list
             list[at] = (uint16_t)(pos0 + __ffs(mm) - 1);
 }
 
+// Contrast tests that a block takes with one wave per pixel (94 instructions each, four at a
+// time); more of them share their windows' med3 values, at three more barriers.  The first
+// detection took 116 -> 98 us on a crowded 4096 x 4096 field (28 tests a tile), 30 -> 25 us on
+// the 800 x 800 frame (46) and 1.28 -> 1.24 ms on the mixed batch (13); with the line at 4, 8,
+// 24 tests the batch took 1.29, 1.28 and 1.27 ms, the field the same to 1%.
+constexpr int kConWaves = 16;
+
 // Work shapes inside a detection block: a lower bound of med5(J), L+ and an upper bound
 // of S in 2 x 5 thread tiles over the whole tile and its 2-pixel apron; med5(J) and the S
 // estimate in 2 x 2 quads near where S may exceed sigclip.  The remaining statistics,
 // med3 among them, are evaluated only where a code bit can matter.
 
+// The maps of a tile that is re-evaluated only in places: its pixels whose code is (bitmap),
+// the S cells they read (bitmap rows over the S region), and the listed 2 x 5 cell tiles that
+// meet those.
+template <int TY, bool SPARSE>
+struct DetectMaps {};
+template <int TY>
+struct DetectMaps<TY, true> {
+    uint32_t act[2 * TY], reach[3 * (TY + 4)];
+    uint16_t cells[(TY + 5) / 2 * 14];
+    unsigned int ncells;
+};
+
 // The LDS of a detection tile: TY rows of 64 columns, one block of 8 * TY threads.  AP is
 // the apron of the staged J (at least 4, the reach of a code into J); SPARSE adds the maps
 // of a tile that is re-evaluated only in places.
 template <int TY, int AP, bool SPARSE>
-struct DetectLds {
+struct DetectLds : DetectMaps<TY, SPARSE> {
     static constexpr int TX = 64, NT = 8 * TY, NW = NT / 64;
     // logical extents of the planes and their row pitches; the pitches spread the dense
     // and exact passes' scalar accesses over the LDS banks
@@ -432,35 +451,41 @@ struct DetectLds {
     static constexpr int NP = SH / 2, kQuads = NP * SW / 2;
     // pixels per round of the binary64 re-evaluation (25 threads each)
     static constexpr int kExactBatch = NT / 25;
-    // pixels whose contrast test a block lists for its contrast phase (one wave each);
-    // further ones take the same test in their own lanes
-    static constexpr int kConMax = TY;
+    // pixels whose contrast test a block lists for its contrast phase; further ones take the
+    // same test in their own lanes
+    static constexpr int kConMax = kQuads * 2 / 16;
+    // med3 plane of the contrast phase: the tile with an apron of 3
+    static constexpr int MH = TY + 6, MW = TX + 6;
+    static constexpr int kSPlane = SH * SWP > MH * MW ? SH * SWP : MH * MW;
     // work-set pixels a block lists; a larger work set is taken from its bitmap instead
     static constexpr int kListMax = 8 * TY;
     static_assert(AP >= 4 && NW * 64 == NT && QW == 2, "whole waves; two bitmap words per row");
     static_assert(QW + 1 <= HW, "dilation reads two bitmap words per work word");
-    static_assert(SH * SWP * 4 >= kExactBatch * 26 * 8, "re-evaluation buffer in the S plane");
+    static_assert(kSPlane * 4 >= kExactBatch * 26 * 8, "re-evaluation buffer in the S plane");
+    static_assert((kTileWords + 1) * 4 <= kListMax * 2, "bitmap prefix in the work list");
     static_assert(SH % 2 == 0 && SW % 2 == 0, "whole quads");
+    static_assert(SW == 68 && HW == 3 && NTX == 14, "the sizes of DetectMaps");
 
     __align__(16) float J[JH * JWP];            // J at clamped positions
-    __align__(16) float S[SH * SWP];            // later: re-evaluation buffer
+    // S; after the work set, med3 near the contrast pixels; then the re-evaluation buffer
+    __align__(16) float S[kSPlane];
     __align__(8) uint32_t code[3 * kTileWords]; // code planes A, [S' > sigclip], [S' > low]
     uint32_t hotp[HR * HWP + 1];                // H', apron 2, in-frame
-    uint32_t u[kTileWords], upre[kTileWords + 1];   // pixels left to binary64
+    uint32_t u[kTileWords];                     // pixels left to binary64
+    uint32_t con_map[kTileWords];               // pixels listed for the contrast phase
     // tile cells where S may exceed sigfrac*sigclip; after the work-set build, Q' itself
     uint32_t low[kTileWords];
     unsigned int err_bits, contrast, uncertain, qcount, need, exact_cells, con_count, any_hot;
-    uint16_t quads[kQuads];
-    uint16_t list[kListMax];                    // work set Q' (up to kListMax)
-    // pixels whose contrast test is left to the contrast phase: position, S' interval, N
-    uint32_t con_info[kConMax];
-    float con_lo[kConMax], con_hi[kConMax], con_n[kConMax];
-    // SPARSE: tile pixels whose code is re-evaluated (bitmap), S cells they read (bitmap
-    // rows over the S region), and the listed 2 x 5 cell tiles that meet those
-    uint32_t act[SPARSE ? kTileWords : 1];
-    uint32_t reach[SPARSE ? SH * HW : 1];
-    uint16_t cells[SPARSE ? NTY * NTX : 1];
-    unsigned int ncells;
+    union {
+        uint16_t quads[kQuads];
+        // (once the quads are done) the contrast phase's pixels: position, S' interval, N
+        struct {
+            uint32_t con_info[kConMax];
+            float con_lo[kConMax], con_hi[kConMax], con_n[kConMax];
+        };
+    };
+    // work set Q' (up to kListMax); then runs of med3 cells; then the prefix of u
+    __align__(4) uint16_t list[kListMax];
 
     // word w of region row r of H' (r in [-4, SH + 4), w in [-1, HW]; zero outside)
     __device__ __forceinline__ uint32_t *hot() { return &hotp[4 * HWP + 1]; }
@@ -481,6 +506,7 @@ __device__ __forceinline__ void detect_clear(DetectLds<TY, AP, SPARSE> &s, int t
     for (int i = tid; i < L::kTileWords; i += L::NT) {
         s.u[i] = 0u;
         s.low[i] = 0u;
+        s.con_map[i] = 0u;
     }
     if (tid == 0) {
         s.err_bits = 0u;
@@ -491,7 +517,8 @@ __device__ __forceinline__ void detect_clear(DetectLds<TY, AP, SPARSE> &s, int t
         s.exact_cells = 0u;
         s.con_count = 0u;
         s.any_hot = 0u;
-        s.ncells = 0u;
+        if constexpr (SPARSE)
+            s.ncells = 0u;
     }
 }
 
@@ -601,7 +628,9 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
     constexpr int TTY = 2, TTX = 5, PW = TTX + 4;
     constexpr int NTY = L::NTY, NTX = L::NTX;
     const SEstParams sp = sest_params(f);
-    const int ncells = SPARSE ? (int)s.ncells : NTY * NTX;
+    int ncells = NTY * NTX;
+    if constexpr (SPARSE)
+        ncells = (int)s.ncells;
 #pragma unroll 1
     for (int ti = tid; ti < ncells; ti += NT) {
         // column-major over the 2 x 5 tiles in groups of 16 row pairs, then the remaining
@@ -900,6 +929,7 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
                         s.con_lo[slot] = lo;
                         s.con_hi[slot] = hi;
                         s.con_n[slot] = nz;
+                        atomicOr(&s.con_map[pos >> 5], 1u << (pos & 31));
                         listed = true;
                     } else {
                         const int t = contrast_by_count_lane(sJ, L::JWP, y0, x0, H, W, r, c,
@@ -926,25 +956,119 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
     }
     __syncthreads();
 
-    // contrast tests of the listed pixels (S' > sigclip certain), one wave per pixel
+    // contrast tests of the listed pixels (S' > sigclip certain)
     const int ncon = min((int)s.con_count, kConMax);
     if (ncon) {
         const float inv_olim = f.inv_olim;
         unsigned int ncontrast = 0u, nunc = 0u;
-        for (int it = tid >> 6; it < ncon; it += L::NW) {
-            const uint32_t info = s.con_info[it];
+        auto result = [&](uint32_t info, int t) {
             const int pos = (int)(info & 0xFFFFu);
-            const int r = pos / TX, c = pos - r * TX;
-            const int t = contrast_by_count(sJ, L::JWP, y0, x0, H, W, r, c, s.con_n[it],
-                                            s.con_lo[it], s.con_hi[it], inv_olim, lane);
-            if (lane == 0) {
-                if (t < 0) {
-                    atomicOr(&s.u[pos >> 5], 1u << (pos & 31));
-                    ++nunc;
-                } else {
-                    set_code(s, pos, t > 0, true, (info >> 16) != 0u);
-                    ++ncontrast;
+            if (t < 0)
+                atomicOr(&s.u[pos >> 5], 1u << (pos & 31));
+            else
+                set_code(s, pos, t > 0, true, (info >> 16) != 0u);
+            // (sums, not a branch: that became one counter chosen in scratch memory)
+            nunc += t < 0 ? 1u : 0u;
+            ncontrast += t < 0 ? 0u : 1u;
+        };
+        if (ncon <= kConWaves) {
+            // a few: one wave per pixel, its lanes the 49 window cells
+            for (int it = tid >> 6; it < ncon; it += L::NW) {
+                const uint32_t info = s.con_info[it];
+                const int pos = (int)(info & 0xFFFFu);
+                const int r = pos / TX, c = pos - r * TX;
+                const int t = contrast_by_count(sJ, L::JWP, y0, x0, H, W, r, c, s.con_n[it],
+                                                s.con_lo[it], s.con_hi[it], inv_olim, lane);
+                if (lane == 0)
+                    result(info, t);
+            }
+        } else {
+            // more: med3 once on the union of the windows (hits are runs of neighbours, whose
+            // windows share most cells), then the counts by 8 lanes per pixel.  The plane
+            // holds, at (r, c), med3 at tile position (r - 3, c - 3) clamped to the frame.
+            // First the 4-cell runs of plane rows that some window meets, one row per lane.
+            constexpr int MH = L::MH, MW = L::MW, kRuns = (MW + 3) / 4;
+            unsigned int &nruns = s.qcount;
+            if (tid == 0)
+                nruns = 0u;          // (read by all before the barrier that precedes)
+            __syncthreads();
+            if (tid < (MH + 63) / 64 * 64) {
+                const unsigned long long *map =
+                    reinterpret_cast<const unsigned long long *>(s.con_map);
+                unsigned long long x = 0ull;
+#pragma unroll
+                for (int d = 0; d < 7; ++d) {
+                    const int q = tid - 6 + d;
+                    x |= q >= 0 && q < TY && tid < MH ? map[q] : 0ull;
                 }
+                // a window of tile column c covers plane columns c .. c + 6
+                uint32_t w[3] = {(uint32_t)x, (uint32_t)(x >> 32), 0u};
+#pragma unroll
+                for (int sh = 1; sh <= 3; ++sh) {
+                    w[2] |= w[2] << sh | w[1] >> (32 - sh);
+                    w[1] |= w[1] << sh | w[0] >> (32 - sh);
+                    w[0] |= w[0] << sh;
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    list_append((w[i] | w[i] >> 1 | w[i] >> 2 | w[i] >> 3) & 0x11111111u,
+                                tid * 4 * kRuns + 32 * i, s.list, &nruns, (unsigned int)kListMax,
+                                lane);
+            }
+            __syncthreads();
+            const int nr = (int)nruns;
+            const bool interior = y0 >= 3 && x0 >= 3 && y0 + TY + 3 <= H && x0 + TX + 3 <= W;
+            for (int i = tid; i < (nr <= kListMax ? nr : MH * kRuns); i += NT) {
+                const int pos = nr <= kListMax ? (int)s.list[i] : 4 * i;
+                const int pr = pos / (4 * kRuns), pc = min(pos - pr * (4 * kRuns), MW - 4);
+                float o[4];
+                if (interior) {
+                    float v[3][6];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+#pragma unroll
+                        for (int j = 0; j < 6; ++j)
+                            v[q][j] = sJ[(pr + q) * L::JWP + pc + j];
+                    med3_run<4>(v[0], v[1], v[2], o);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        o[j] = med3_at(med3_cell(sJ, L::JWP, y0, x0, H, W, pr - 3, pc - 3 + j, 0,
+                                                 0), L::JWP);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    s.S[pr * MW + pc + j] = o[j];
+            }
+            __syncthreads();
+            const int sub = tid & 7;
+            int off[7];
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                const int j = min(sub + 8 * i, 48);
+                off[i] = j / 7 * MW + j % 7;
+            }
+            for (int b = (tid >> 6) * 8; b < ncon; b += NT / 8) {
+                const int it = min(b + (lane >> 3), ncon - 1);
+                const uint32_t info = s.con_info[it];
+                const int pos = (int)(info & 0xFFFFu);
+                const int r = pos / TX, c = pos - r * TX;
+                const float *m = &s.S[r * MW + c];
+                float t_sure, t_maybe;
+                contrast_thresholds(m[3 * MW + 3], s.con_n[it], s.con_lo[it], s.con_hi[it],
+                                    inv_olim, t_sure, t_maybe);
+                int n = 0;               // certain values, and possible ones << 8
+#pragma unroll
+                for (int i = 0; i < 7; ++i) {
+                    const float x = m[off[i]];
+                    const bool in = i < 6 || sub == 0;
+                    n += (in && x > t_sure ? 1 : 0) + (in && x >= t_maybe ? 256 : 0);
+                }
+                n += __shfl_xor(n, 1);
+                n += __shfl_xor(n, 2);
+                n += __shfl_xor(n, 4);
+                if (sub == 0 && b + (lane >> 3) < ncon)
+                    result(info, (n & 255) >= 25 ? 1 : ((n >> 8) < 25 ? 0 : -1));
             }
         }
         if (ncontrast && (f.flags & kCountWork))
@@ -962,14 +1086,15 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
         const double gain = f.gain, sky = f.sky, rn = f.readnoise;
         const double rn2 = rn * rn, sigclip = f.sigclip, objlim = f.objlim;
         const double lowlim = (double)f.sigfrac * (double)f.sigclip;
+        uint32_t *const upre = reinterpret_cast<uint32_t *>(s.list);
         if (tid < 64)
-            bitmap_prefix<L::kTileWords>(s.u, s.upre);
+            bitmap_prefix<L::kTileWords>(s.u, upre);
         __syncthreads();
         unsigned int ncontrast = 0u;
         for (int base = 0; base < nunc; base += kExactBatch) {
             const int slot = tid / 25, cell = tid - slot * 25;
             if (slot < kExactBatch && base + slot < nunc) {
-                const int pos = bitmap_select<L::kTileWords>(s.u, s.upre, base + slot);
+                const int pos = bitmap_select<L::kTileWords>(s.u, upre, base + slot);
                 const int r = pos / TX, c = pos - r * TX;
                 const int i = cell / 5, j = cell - i * 5;
                 // window cell in frame coordinates, clamped
@@ -994,7 +1119,7 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
             }
             __syncthreads();
             if (tid < kExactBatch && base + tid < nunc) {
-                const int pos = bitmap_select<L::kTileWords>(s.u, s.upre, base + tid);
+                const int pos = bitmap_select<L::kTileWords>(s.u, upre, base + tid);
                 const int r = pos / TX, c = pos - r * TX;
                 const double spr = sX[tid * 25 + 12] - sX[kExactBatch * 25 + tid];
                 const bool hbit = spr > sigclip, lbit = spr > lowlim;

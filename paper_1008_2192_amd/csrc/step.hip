@@ -17,7 +17,7 @@
 // A tile is bound by the latency of its chain (waves wait 71% of their cycles, VALU issue is
 // at half its rate): with J's loads in flight during the grow, rows in 32-bit words and no
 // pass over the staged cells past the frame's edges, the first iteration of the batch took
-// 1.48 -> 1.11 ms, and the second, whose tile records now load as scalars, 0.24 -> 0.15 ms.
+// 1.48 -> 1.11 ms; the second, on the listed tiles, takes 0.24 ms.
 //
 // Blocks share their halos without ordering.  Codes are double-buffered per tile.  The mask
 // bitmap of a neighbour may be read before or after its owner ORs G2 into it: the reader ORs
