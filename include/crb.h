@@ -343,6 +343,13 @@ crb_status crb_farm_run(const crb_work *w, const float *in, int32_t H, int32_t W
                         int32_t workers, int32_t tile_h, int32_t tile_w, float *out_image,
                         crb_source *out_list, int64_t list_capacity, int64_t *out_count);
 
+/* Copies the n records of a SOURCES list of an H x W frame (on distinct pixels; records
+ * outside the frame are left out) to out in raster order (device, 8-byte aligned, no
+ * overlap).  Asynchronous on the calling thread's stream; uses 3/16 byte per frame pixel of
+ * that stream's workspace. */
+crb_status crb_sources_order(const crb_source *list, int64_t n, int32_t H, int32_t W,
+                             crb_source *out);
+
 /* POISSON or WAITER on bands of band_rows full rows: crb_farm_run with tile_h =
  * band_rows and tile_w = W. */
 crb_status crb_work_run(int32_t kind, const float *in, int32_t H, int32_t W, uint64_t seed,

@@ -7,7 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import List, Optional, Sequence
+from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
 import torch
@@ -31,6 +31,7 @@ EXPORTS = ["crb_lacosmic", "crb_lacosmic_noalloc", "crb_lacosmic_batched", "crb_
            "crb_server_create", "crb_server_submit", "crb_server_poll", "crb_server_pending",
            "crb_server_destroy", "crb_debug_iterate", "crb_debug_detect", "crb_debug_median",
            "crb_debug_fp64", "crb_work_run", "crb_work_radius", "crb_farm_run",
+           "crb_sources_order",
            "crb_plan_set_counting", "crb_plan_work_counts", "crb_debug_median5_f64",
            "crb_debug_detect_exact", "crb_debug_s_estimate", "crb_plan_set_tuning",
            "crb_plan_get_tuning", "crb_plan_autotune", "crb_debug_copy_b32", "crb_debug_s_bound"]
@@ -143,12 +144,13 @@ def lib():
     L.crb_work_radius.argtypes = [ctypes.POINTER(Work)]
     L.crb_work_radius.restype = i32
     L.crb_farm_run.argtypes = [ctypes.POINTER(Work), vp, i32, i32, i32, i32, i32, vp, vp, i64, vp]
+    L.crb_sources_order.argtypes = [vp, i64, i32, i32, vp]
     for name in ("crb_lacosmic", "crb_lacosmic_noalloc", "crb_lacosmic_batched", "crb_lacosmic_partitioned",
                  "crb_plan_create", "crb_plan_run",
                  "crb_plan_stats", "crb_plan_set_timing", "crb_plan_kernel_times", "crb_set_stream", "crb_set_option", "crb_release_workspace",
                  "crb_server_create", "crb_server_submit", "crb_server_poll",
                  "crb_debug_iterate", "crb_debug_detect", "crb_debug_median", "crb_debug_fp64",
-                 "crb_work_run", "crb_farm_run", "crb_plan_set_counting", "crb_plan_work_counts",
+                 "crb_work_run", "crb_farm_run", "crb_sources_order", "crb_plan_set_counting", "crb_plan_work_counts",
                  "crb_debug_median5_f64", "crb_debug_detect_exact", "crb_debug_s_estimate",
                  "crb_plan_set_tuning", "crb_plan_get_tuning", "crb_plan_autotune",
                  "crb_debug_copy_b32", "crb_debug_s_bound"):
@@ -541,10 +543,12 @@ def farm_image(kind: int, x: torch.Tensor, seed: int = 0, workers: int = 1024, t
 
 class SourceList:
     """Device-side result of the SOURCES work function: `records` (uint8 tensor of
-    capacity x 40 bytes) and `count` (int64 tensor of one element)."""
+    capacity x 40 bytes) and `count` (int64 tensor of one element).  `shape` is the frame's
+    (H, W), set by farm_sources."""
 
     def __init__(self, records: torch.Tensor, count: torch.Tensor, capacity: int):
         self.records, self.count, self.capacity = records, count, capacity
+        self.shape: Optional[Tuple[int, int]] = None
 
     def numpy(self) -> np.ndarray:
         """The records as a structured array (SOURCE_DTYPE) sorted by (y, x); raises
@@ -552,8 +556,16 @@ class SourceList:
         n = int(self.count.item())
         if n > self.capacity:
             raise OverflowError(f"{n} sources found, capacity {self.capacity}")
-        rec = self.records[: n * SOURCE_DTYPE.itemsize].cpu().numpy().view(SOURCE_DTYPE)
-        return rec[np.lexsort((rec["x"], rec["y"]))]
+        rec = self.records[: n * SOURCE_DTYPE.itemsize]
+        if self.shape is None or n == 0:
+            rec = rec.cpu().numpy().view(SOURCE_DTYPE)
+            return rec[np.lexsort((rec["x"], rec["y"]))]
+        # a list of this frame: sorted on the device
+        out = torch.empty_like(rec)
+        set_stream()
+        check("crb_sources_order", lib().crb_sources_order(
+            rec.data_ptr(), n, self.shape[0], self.shape[1], out.data_ptr()))
+        return out.cpu().numpy().view(SOURCE_DTYPE)
 
 
 def farm_sources(x: torch.Tensor, threshold: float, sky: float = 0.0, r: int = 2, a: int = 2,
@@ -574,4 +586,5 @@ def farm_sources(x: torch.Tensor, threshold: float, sky: float = 0.0, r: int = 2
     check("crb_farm_run", lib().crb_farm_run(ctypes.byref(w), x.data_ptr(), H, W, workers,
                                              tile_h, tile_w, None, out.records.data_ptr(),
                                              out.capacity, out.count.data_ptr()))
+    out.shape = (H, W)
     return out

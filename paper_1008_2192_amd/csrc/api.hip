@@ -531,6 +531,35 @@ crb_status crb_work_run(int32_t kind, const float *in, int32_t H, int32_t W, uin
     return crb_farm_run(&w, in, H, W, workers, band_rows, W, out, nullptr, 0, nullptr);
 }
 
+crb_status crb_sources_order(const crb_source *list, int64_t n, int32_t H, int32_t W,
+                             crb_source *out) {
+    if (H < 1 || W < 1)
+        return fail(CRB_EINVAL, "image size %d x %d: both must be >= 1", H, W);
+    if ((int64_t)H * (int64_t)W > (int64_t)INT32_MAX)
+        return fail(CRB_ETOOBIG, "image exceeds 2^31-1 pixels");
+    if (n < 0 || n > (int64_t)H * (int64_t)W)
+        return fail(CRB_EINVAL, "%lld records on the pixels of a %d x %d frame", (long long)n, H,
+                    W);
+    if (n == 0)
+        return ok();
+    if (!list || !out || ((uintptr_t)list & 7) || ((uintptr_t)out & 7))
+        return fail(CRB_EINVAL, "list and out must be 8-byte aligned device pointers");
+    if (ranges_overlap(list, (size_t)n * sizeof(crb_source), out, (size_t)n * sizeof(crb_source)))
+        return fail(CRB_EINVAL, "list and out overlap");
+    hipStream_t s = t_stream;
+    Workspace *ws = nullptr;
+    crb_status st;
+    if ((st = ws_get(s, &ws)) != CRB_OK)
+        return st;
+    std::lock_guard<std::mutex> g(ws->mu);
+    if ((st = ws_reserve(ws, order_bytes(H, W))) != CRB_OK)
+        return st;
+    st = hip_status(launch_order(reinterpret_cast<const SourceRec *>(list), n, H, W,
+                                 reinterpret_cast<SourceRec *>(out), ws->buf, s),
+                    "kernel launch");
+    return st == CRB_OK ? ok() : st;
+}
+
 crb_status crb_debug_iterate(const float *J, const uint8_t *M_prev, int32_t H, int32_t W,
                              const crb_frame *p, uint8_t *out_G2, uint8_t *out_M,
                              float *out_J_next, int64_t *out_n_new) {

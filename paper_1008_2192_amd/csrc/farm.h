@@ -60,4 +60,17 @@ hipError_t launch_farm(int kind, const WorkArgs &args, const float *in, int H, i
                        SourceRec *out_list, long long capacity, unsigned long long *count,
                        unsigned int *tickets, hipStream_t s);
 
+// Raster order of a list of records on distinct pixels of an H x W frame, into another list.
+// work: order_bytes(H, W) bytes, 8-byte aligned.
+inline size_t order_words(int H, int W) { return ((size_t)H * (size_t)W + 63) / 64; }
+constexpr int kOrderChunk = 1024;        // words of the pixel bitmap per block
+inline size_t order_chunks(int H, int W) {
+    return (order_words(H, W) + kOrderChunk - 1) / kOrderChunk;
+}
+inline size_t order_bytes(int H, int W) {
+    return order_words(H, W) * 8 + order_words(H, W) * 4 + order_chunks(H, W) * 4;
+}
+hipError_t launch_order(const SourceRec *list, long long n, int H, int W, SourceRec *out,
+                        void *work, hipStream_t s);
+
 }  // namespace crb

@@ -7,6 +7,9 @@
 
 #include <math.h>
 
+// Exclusive prefix sum over the lanes of a wave (all lanes active), from the device library.
+extern "C" __device__ unsigned int __ockl_wfscan_add_u32(unsigned int, bool);
+
 namespace crb {
 
 // ---------------------------------------------------------------------------
@@ -595,6 +598,132 @@ hipError_t launch_farm(int kind, const WorkArgs &args, const float *in, int H, i
     default:
         return hipErrorInvalidValue;
     }
+}
+
+// ---------------------------------------------------------------------------
+// raster order of a SOURCES list
+// ---------------------------------------------------------------------------
+//
+// Every record sits on a pixel of its own, so a bitmap of the frame's pixels sorts the list:
+// a record's place is the number of set bits before its own.  Five short launches: clear and
+// set the bitmap, sum it per chunk of kOrderChunk words, prefix sums per word, and the copy.
+// They move 12 bytes per 64 pixels twice and the records once (about 20 us for 43,000 records
+// of a 4096 x 4096 frame, where sorting them on the host took 4 ms).
+
+__global__ __launch_bounds__(256) void k_order_clear(unsigned long long *__restrict__ map,
+                                                     long long words) {
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < words;
+         i += (long long)gridDim.x * 256)
+        map[i] = 0ull;
+}
+
+// The pixel index of a record, or -1 outside the frame.
+__device__ __forceinline__ long long record_pixel(const SourceRec &r, int H, int W) {
+    return r.y >= 0 && r.y < H && r.x >= 0 && r.x < W ? (long long)r.y * W + r.x : -1ll;
+}
+
+__global__ __launch_bounds__(256) void k_order_mark(const SourceRec *__restrict__ list,
+                                                    long long n, int H, int W,
+                                                    unsigned long long *__restrict__ map) {
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n;
+         i += (long long)gridDim.x * 256) {
+        const long long p = record_pixel(list[i], H, W);
+        if (p >= 0)
+            atomicOr(&map[p >> 6], 1ull << (p & 63));
+    }
+}
+
+// One block per chunk: the set bits of its words.
+__global__ __launch_bounds__(256) void k_order_sum(const unsigned long long *__restrict__ map,
+                                                   long long words,
+                                                   unsigned int *__restrict__ sums) {
+    __shared__ unsigned int part[4];
+    const long long w0 = (long long)blockIdx.x * kOrderChunk;
+    unsigned int c = 0u;
+    for (int i = threadIdx.x; i < kOrderChunk; i += 256)
+        c += w0 + i < words ? (unsigned int)__popcll(map[w0 + i]) : 0u;
+    c = __ockl_wfred_add_u32(c);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+// One block per chunk: the set bits before each of its words.
+__global__ __launch_bounds__(256) void k_order_prefix(const unsigned long long *__restrict__ map,
+                                                      long long words,
+                                                      const unsigned int *__restrict__ sums,
+                                                      unsigned int *__restrict__ before) {
+    constexpr int kPer = kOrderChunk / 256;
+    __shared__ unsigned int part[8];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned int base = 0u;              // the chunks before this one
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256)
+        base += sums[i];
+    base = __ockl_wfred_add_u32(base);
+    const long long w0 = (long long)blockIdx.x * kOrderChunk + (long long)threadIdx.x * kPer;
+    unsigned int c[kPer], tot = 0u;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        c[i] = w0 + i < words ? (unsigned int)__popcll(map[w0 + i]) : 0u;
+        tot += c[i];
+    }
+    unsigned int at = __ockl_wfscan_add_u32(tot, false);
+    if (lane == 63)
+        part[wave] = at + tot;
+    if (lane == 0)
+        part[4 + wave] = base;
+    __syncthreads();
+    at += part[4] + part[5] + part[6] + part[7];
+    for (int q = 0; q < wave; ++q)
+        at += part[q];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        if (w0 + i < words)
+            before[w0 + i] = at;
+        at += c[i];
+    }
+}
+
+// Five lanes per record, 8 bytes each.
+__global__ __launch_bounds__(256) void k_order_copy(const SourceRec *__restrict__ list,
+                                                    long long n, int H, int W,
+                                                    const unsigned long long *__restrict__ map,
+                                                    const unsigned int *__restrict__ before,
+                                                    SourceRec *__restrict__ out) {
+    constexpr int kWords = (int)(sizeof(SourceRec) / 8);
+    const unsigned long long *src = reinterpret_cast<const unsigned long long *>(list);
+    unsigned long long *dst = reinterpret_cast<unsigned long long *>(out);
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n * kWords;
+         i += (long long)gridDim.x * 256) {
+        const long long rec = i / kWords;
+        const long long p = record_pixel(list[rec], H, W);
+        if (p >= 0) {
+            const long long at = (long long)before[p >> 6] +
+                                 __popcll(map[p >> 6] & ((1ull << (p & 63)) - 1ull));
+            dst[at * kWords + (i - rec * kWords)] = src[i];
+        }
+    }
+}
+
+hipError_t launch_order(const SourceRec *list, long long n, int H, int W, SourceRec *out,
+                        void *work, hipStream_t s) {
+    const long long words = (long long)order_words(H, W);
+    const int chunks = (int)order_chunks(H, W);
+    unsigned long long *map = static_cast<unsigned long long *>(work);
+    unsigned int *before = reinterpret_cast<unsigned int *>(map + words);
+    unsigned int *sums = before + words;
+    auto grid = [](long long items) {
+        const long long g = (items + 255) / 256;
+        return (unsigned int)(g < 4096 ? g : 4096);
+    };
+    k_order_clear<<<grid(words), 256, 0, s>>>(map, words);
+    k_order_mark<<<grid(n), 256, 0, s>>>(list, n, H, W, map);
+    k_order_sum<<<chunks, 256, 0, s>>>(map, words, sums);
+    k_order_prefix<<<chunks, 256, 0, s>>>(map, words, sums, before);
+    k_order_copy<<<grid(n * 5), 256, 0, s>>>(list, n, H, W, map, before, out);
+    return hipGetLastError();
 }
 
 }  // namespace crb
