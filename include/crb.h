@@ -379,8 +379,11 @@ crb_status crb_release_workspace(void *hip_stream);
  *     completion; returns CRB_EBUSY when the request can never fit the budget.
  *     Requests wait in FIFO order until slots and memory allow.  The image and both
  *     outputs are all host memory or all device memory of the server's device
- *     (CRB_EINVAL otherwise).  Device buffers are copied on the device (the caller
- *     makes the input ready before submitting, e.g. by synchronizing its stream);
+ *     (CRB_EINVAL otherwise).  Device requests are cleaned in the caller's buffers (the
+ *     outputs change from admission on; the caller makes the input ready before
+ *     submitting, e.g. by synchronizing its stream), or copied in and out where those
+ *     overlap each other or another request's, or the calling thread's stream
+ *     (crb_set_stream) has unfinished work at submit;
  *     page-locked host buffers (hipHostMalloc) are transferred directly; pageable ones
  *     pass through the server's pinned staging buffers.
  *   crb_server_poll: enqueue the next round when the previous one has finished,

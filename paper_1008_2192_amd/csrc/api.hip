@@ -20,6 +20,7 @@ namespace crb {
 
 static thread_local std::string t_err;
 static thread_local hipStream_t t_stream = nullptr;
+hipStream_t thread_stream() { return t_stream; }
 static std::atomic<int> g_early_stop{1};
 static std::atomic<int> g_incremental{0};
 

@@ -14,6 +14,7 @@ struct FrameWs {
     size_t total;        // what crb_workspace_bytes reports: at least the end of the lists
 };
 
+hipStream_t thread_stream();       // set by crb_set_stream
 crb_status fail(crb_status st, const char *fmt, ...);
 crb_status ok();
 crb_status hip_status(hipError_t e, const char *what);

@@ -79,6 +79,8 @@ struct DevFrame {
     int flags;
     int k;                        // current iteration when a kernel is launched with k = 0
     int tile_base;                // index of the frame's first tile in the launch's tiles
+    int list_base[3];             // its first entry in the lists of k_tiles, per tile height
+                                  // 16, 32, 64 (-1: not listed)
     // Detection constants, derived from the parameters above by derive_detect_consts (on
     // the host, in the operations the detection would otherwise repeat per tile): the
     // FP32 thresholds sigclip and sigfrac * sigclip widened and narrowed by 2^-20
@@ -149,6 +151,26 @@ inline StepLists make_lists(void *p, size_t ntiles) {
     return l;
 }
 
+// A list of some tiles of a launch, built by launch_tiles: nseg segments of cap entries with a
+// counter each (kTicketStride words apart, zero before).
+struct TileList {
+    unsigned int *list;
+    unsigned int *count;
+    int nseg, cap;
+};
+// (64 consecutive tiles share a segment; the frames' tile_base are multiples of 64)
+inline size_t tile_list_cap(size_t ntiles) {
+    return ((ntiles + 63) / 64 + kListSegments - 1) / kListSegments * 64;
+}
+
+// Builds the (frame, tile) lists of a table of frames on the device: out[h] (may be null), the
+// tiles of height 16, 32, 64 of the frames with list_base[h] >= 0; step (may be null), the
+// summary tiles of the frames at iteration f.k >= 2 from f.tile_base on, and in `active` those
+// that the previous iteration marked.  Clears zero_words words at `zero`.
+hipError_t launch_tiles(const DevFrame *d_frames, int nframes, size_t max_tiles, TileRef *out16,
+                        TileRef *out32, TileRef *out64, TileRef *step, const TileList &active,
+                        unsigned int *zero, int zero_words, hipStream_t s);
+
 // For frames with niter == 0: copies img into J and clears the mask (otherwise the first
 // detection does both).  max_pixels: the largest such frame, which sizes the grid.
 hipError_t launch_init(const DevFrame *d_frames, int nframes, const DevFrame &single,
@@ -172,7 +194,7 @@ hipError_t launch_detect(const DevFrame *d_frames, const TileRef *d_tiles, int n
                          const DevFrame &single, const LaunchCfg &cfg, const StepLists &lists,
                          unsigned int *tickets, hipStream_t s);
 // Number of detection tiles of an H x W frame at tile height tile_h.
-inline int detect_tiles(int H, int W, int tile_h) {
+__host__ __device__ inline int detect_tiles(int H, int W, int tile_h) {
     return ((H + tile_h - 1) / tile_h) * ((W + kDetectTX - 1) / kDetectTX);
 }
 // Iteration k from its codes on: grow, new-flag count, cumulative mask, replacement, and
@@ -183,6 +205,9 @@ inline int detect_tiles(int H, int W, int tile_h) {
 hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
                        const DevFrame &single, int k, bool all, const StepLists &lists,
                        unsigned int *tickets, hipStream_t s);
+// Each frame's own iteration f.k on the tiles of a list built by launch_tiles.
+hipError_t launch_step_active(const DevFrame *d_frames, const TileRef *d_tiles, size_t ntiles,
+                              const TileList &active, hipStream_t s);
 // Per-frame (iters_run, n_flagged) into d_stats[2 * i].
 hipError_t launch_stats(const DevFrame *d_frames, int nframes, long long *d_stats,
                         hipStream_t s);
@@ -191,8 +216,9 @@ hipError_t launch_stats(const DevFrame *d_frames, int nframes, long long *d_stat
 // flagged pixels so far, into d_stats[2 * i] and d_stats[2 * i + 1].
 // (launch_count: the flagged pixels of one frame into *out.)
 hipError_t launch_count(const DevFrame &f, long long *out, hipStream_t s);
+// Clears the counters of the round's active list for the next one.
 hipError_t launch_round_stats(const DevFrame *d_frames, int nframes, long long *d_stats,
-                              hipStream_t s);
+                              const TileList &active, hipStream_t s);
 
 // Subimage of a frame: the extended rectangle [a0, a0+h) x [b0, b0+w) is copied into
 // sub (pitch w); its interior [y0, y1) x [x0, x1) (image coordinates) is written back.

@@ -31,6 +31,52 @@ __global__ __launch_bounds__(kThreads) void k_init(const DevFrame *__restrict__ 
     }
 }
 
+// Grid rows (blockIdx.y) take the frames in turn, a block's threads 256 consecutive tiles.
+__global__ __launch_bounds__(kThreads) void k_tiles(const DevFrame *__restrict__ frames,
+                                                    int nframes, TileRef *__restrict__ out16,
+                                                    TileRef *__restrict__ out32,
+                                                    TileRef *__restrict__ out64,
+                                                    TileRef *__restrict__ step, TileList active,
+                                                    unsigned int *__restrict__ zero,
+                                                    int zero_words) {
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = threadIdx.x; i < zero_words; i += kThreads)
+            zero[i] = 0u;
+    const int t0 = blockIdx.x * kThreads + threadIdx.x, stride = gridDim.x * kThreads;
+    for (int fi = blockIdx.y; fi < nframes; fi += gridDim.y) {
+        const DevFrame &f = frames[fi];
+        const int ntx = (f.W + kDetectTX - 1) / kDetectTX;
+        for (int h = 0; h < 3; ++h) {
+            TileRef *out = h == 0 ? out16 : (h == 1 ? out32 : out64);
+            const int ty = 16 << h, n = detect_tiles(f.H, f.W, ty);
+            if (out && f.list_base[h] >= 0)
+                for (int t = t0; t < n; t += stride)
+                    out[f.list_base[h] + t] = TileRef{fi, t / ntx * ty, t % ntx * kDetectTX, 0};
+        }
+        if (!step || f.k < 2)
+            continue;
+        const int n = detect_tiles(f.H, f.W, kSumTY), lane = threadIdx.x & 63;
+        for (int b = t0 - lane; b < n; b += stride) {       // (uniform in a wave)
+            const int t = b + lane;
+            const bool on = t < n && f.mark[t < n ? t : 0] >= (unsigned int)f.k;
+            if (t < n)
+                step[f.tile_base + t] = TileRef{fi, t / ntx * kSumTY, t % ntx * kSumTX, 0};
+            // a wave's 64 tiles go to one segment, with one atomic
+            const unsigned long long m = __ballot(on);
+            if (!m)
+                continue;
+            const int seg = (f.tile_base + b) / 64 % active.nseg;
+            unsigned int at = 0u;
+            if (lane == 0)
+                at = atomicAdd(&active.count[seg * kTicketStride], (unsigned int)__popcll(m));
+            at = (unsigned int)__builtin_amdgcn_readfirstlane((int)at) +
+                 (unsigned int)__popcll(m & ((1ull << lane) - 1ull));
+            if (on && at < (unsigned int)active.cap)
+                active.list[(size_t)seg * active.cap + at] = (unsigned int)(f.tile_base + t);
+        }
+    }
+}
+
 __device__ __forceinline__ long long flagged(const DevFrame &f) {
     unsigned long long n = 0ull;
     for (int i = 0; i < kCountSlots; ++i)
@@ -55,8 +101,11 @@ __global__ void k_stats(const DevFrame *__restrict__ frames, int nframes,
 }
 
 __global__ void k_round_stats(const DevFrame *__restrict__ frames, int nframes,
-                              long long *__restrict__ stats) {
+                              long long *__restrict__ stats, TileList active) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0)
+        for (int q = threadIdx.x; q < active.nseg; q += blockDim.x)
+            active.count[q * kTicketStride] = 0u;
     if (i >= nframes)
         return;
     const DevFrame &f = frames[i];
@@ -166,9 +215,19 @@ hipError_t launch_count(const DevFrame &f, long long *out, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_tiles(const DevFrame *d_frames, int nframes, size_t max_tiles, TileRef *out16,
+                        TileRef *out32, TileRef *out64, TileRef *step, const TileList &active,
+                        unsigned int *zero, int zero_words, hipStream_t s) {
+    const int rows = nframes < 65535 ? nframes : 65535;
+    const unsigned int cap = 2048u / (unsigned int)rows > 4u ? 2048u / (unsigned int)rows : 4u;
+    k_tiles<<<dim3(grid_for(max_tiles, cap), rows), kThreads, 0, s>>>(
+        d_frames, nframes, out16, out32, out64, step, active, zero, zero_words);
+    return hipGetLastError();
+}
+
 hipError_t launch_round_stats(const DevFrame *d_frames, int nframes, long long *d_stats,
-                              hipStream_t s) {
-    k_round_stats<<<(nframes + 63) / 64, 64, 0, s>>>(d_frames, nframes, d_stats);
+                              const TileList &active, hipStream_t s) {
+    k_round_stats<<<(nframes + 63) / 64, 64, 0, s>>>(d_frames, nframes, d_stats, active);
     return hipGetLastError();
 }
 

@@ -3,14 +3,15 @@
 // (Section 6.2: the director collects subimages as actors finish, without a
 // barrier).
 //
-// Requests wait FIFO in pinned host staging.  A request is admitted when a slot is
-// free and its device footprint (image, mask, workspace) fits the HBM budget; its
-// upload runs on a copy stream.  Each round runs ONE iteration for every admitted
-// frame, each at its own iteration index, with the batched kernels over a
-// descriptor table rebuilt per round, so frames that arrive while others are on the
-// GPU join at the next round.  A frame leaves after niter iterations or when an
-// iteration selects no new pixel (early stop, result-neutral); its cleaned image
-// and mask are copied back on the copy stream.  Progress is observed only by
+// Requests wait FIFO.  A request is admitted when a slot is free and its device footprint
+// (image, mask, workspace) fits the HBM budget; one from host memory is uploaded on a copy
+// stream, one from device memory is cleaned in the caller's buffers.  Each round runs ONE
+// iteration for every admitted frame, each at its own iteration index, with the batched
+// kernels over a descriptor table rebuilt per round (its tile lists on the device: writing
+// those of 24 frames on the host took 70 us a round), so frames that arrive while others are
+// on the GPU join at the next round.  A frame leaves after niter iterations or when an
+// iteration selects no new pixel (early stop, result-neutral); results for host memory are
+// copied back on the copy stream.  Progress is observed only by
 // polling events: no call blocks on the device.  A server is used from one thread.
 #include "api_internal.h"
 
@@ -122,6 +123,9 @@ struct Request {
     bool direct = false;               // caller's buffers are pinned or on the device:
                                        // transferred without staging copies
     bool on_device = false;            // caller's buffers are device memory
+    bool idle = false;                 // the caller's stream was idle at submit
+    bool in_buffers = false;           // cleaned in the caller's device buffers, no copies
+    size_t alloc_bytes = 0;            // device memory taken from the server
     float *host_clean = nullptr;
     uint8_t *host_mask = nullptr;
     double t_submit = 0;
@@ -245,7 +249,7 @@ static size_t frame_dev_bytes(int32_t H, int32_t W) {
 
 static void release_request(crb_server *s, Request *r) {
     if (r->dev) {
-        s->dev_free.emplace(r->dev_bytes, r->dev);
+        s->dev_free.emplace(r->alloc_bytes, r->dev);
         s->in_use -= r->dev_bytes;
         r->dev = nullptr;
     }
@@ -256,6 +260,40 @@ static void release_request(crb_server *s, Request *r) {
     put_event(s, r->ev_h2d);
     put_event(s, r->ev_d2h);
     delete r;
+}
+
+static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + nb && pb < pa + na;
+}
+
+// Whether a device request can be cleaned in the caller's own buffers: they must not overlap
+// (in place is fine), no other request in the server may share a buffer that either writes,
+// and no work that the caller's stream still held at submit may use the outputs' memory (an
+// allocator hands a block on as soon as work on its former tensor is enqueued).  Otherwise the
+// request is copied in and out, its outputs written at completion.
+static bool clean_in_buffers(const crb_server *s, const Request *r) {
+    if (!r->on_device || !r->idle)
+        return false;
+    const size_t n = (size_t)r->H * (size_t)r->W;
+    if ((r->host_img != r->host_clean && overlap(r->host_img, 4 * n, r->host_clean, 4 * n)) ||
+        overlap(r->host_mask, n, r->host_img, 4 * n) ||
+        overlap(r->host_mask, n, r->host_clean, 4 * n))
+        return false;
+    for (const std::vector<Request *> *v : {&s->active, &s->draining})
+        for (const Request *q : *v) {
+            const size_t m = (size_t)q->H * (size_t)q->W;
+            const struct { const void *p; size_t b; } mine[3] = {
+                {r->host_clean, 4 * n}, {r->host_mask, n}, {r->host_img, 4 * n}};
+            const struct { const void *p; size_t b; } theirs[3] = {
+                {q->host_clean, 4 * m}, {q->host_mask, m}, {q->host_img, 4 * m}};
+            for (int i = 0; i < 3; ++i)
+                for (int j = 0; j < 3; ++j)
+                    if ((i < 2 || j < 2) &&      // (both may read one image)
+                        overlap(mine[i].p, mine[i].b, theirs[j].p, theirs[j].b))
+                        return false;
+        }
+    return true;
 }
 
 // Admit waiting requests (FIFO) while slots and budget allow, at most a few per
@@ -270,43 +308,49 @@ static crb_status admit(crb_server *s) {
         const int held = (int)(s->active.size() + s->draining.size());
         if (held >= s->max_slots || s->in_use + r->dev_bytes > s->budget)
             return CRB_OK;
+        const size_t n = (size_t)r->H * (size_t)r->W;
+        const size_t img = (4 * n + 255) / 256 * 256;
+        const size_t msk = (n + 255) / 256 * 256;
+        const FrameWs L = ws_layout(r->H, r->W);
+        r->in_buffers = clean_in_buffers(s, r);
+        r->alloc_bytes = r->in_buffers ? L.lists : r->dev_bytes;
         char *dev = nullptr;
-        crb_status st = dev_alloc(s, r->dev_bytes, &dev);
+        crb_status st = dev_alloc(s, r->alloc_bytes, &dev);
         if (st == CRB_EBUSY)
             return CRB_OK;
         if (st != CRB_OK)
             return st;
-        if ((st = get_event(s, &r->ev_h2d)) != CRB_OK) {
-            s->dev_free.emplace(r->dev_bytes, dev);
+        if (!r->in_buffers && (st = get_event(s, &r->ev_h2d)) != CRB_OK) {
+            s->dev_free.emplace(r->alloc_bytes, dev);
             return st;
         }
         if (!r->direct) {
             if ((st = pin_alloc(s, r->pin_bytes, &r->pin)) != CRB_OK) {
-                s->dev_free.emplace(r->dev_bytes, dev);
+                s->dev_free.emplace(r->alloc_bytes, dev);
                 return st;
             }
-            s->copies->copy(r->pin, r->host_img, 4 * (size_t)r->H * r->W);
+            s->copies->copy(r->pin, r->host_img, 4 * n);
             ++staged;
         }
-        const size_t n = (size_t)r->H * (size_t)r->W;
-        const size_t img = (4 * n + 255) / 256 * 256;
-        const size_t msk = (n + 255) / 256 * 256;
-        float *J = reinterpret_cast<float *>(dev);
-        uint8_t *mask = reinterpret_cast<uint8_t *>(dev + img);
+        float *J = r->in_buffers ? r->host_clean : reinterpret_cast<float *>(dev);
+        uint8_t *mask = r->in_buffers ? r->host_mask : reinterpret_cast<uint8_t *>(dev + img);
         r->dev = dev;
         s->in_use += r->dev_bytes;
-        r->df = make_devframe(J, J, mask, dev + img + msk, ws_layout(r->H, r->W), r->H, r->W,
-                              r->gain, r->readnoise, r->sky, r->sigclip, r->sigfrac, r->objlim,
-                              r->niter, kFreshMask);
-        hipError_t e = hipMemcpyAsync(J, r->direct ? (const void *)r->host_img : r->pin, 4 * n,
-                                      r->on_device ? hipMemcpyDeviceToDevice
-                                                   : hipMemcpyHostToDevice,
-                                      s->copy);
-        if (e == hipSuccess)
-            e = hipEventRecord(r->ev_h2d, s->copy);
-        if (e != hipSuccess)
-            return hip_status(e, "upload");
-        r->need_wait = true;
+        r->df = make_devframe(r->in_buffers ? r->host_img : J, J, mask,
+                              r->in_buffers ? dev : dev + img + msk, L, r->H, r->W, r->gain,
+                              r->readnoise, r->sky, r->sigclip, r->sigfrac, r->objlim, r->niter,
+                              kFreshMask);
+        if (!r->in_buffers) {
+            hipError_t e = hipMemcpyAsync(J, r->direct ? (const void *)r->host_img : r->pin, 4 * n,
+                                          r->on_device ? hipMemcpyDeviceToDevice
+                                                       : hipMemcpyHostToDevice,
+                                          s->copy);
+            if (e == hipSuccess)
+                e = hipEventRecord(r->ev_h2d, s->copy);
+            if (e != hipSuccess)
+                return hip_status(e, "upload");
+        }
+        r->need_wait = !r->in_buffers;
         r->k_next = 1;
         r->state = kActive;
         s->waiting.pop_front();
@@ -335,26 +379,36 @@ static crb_status ensure_tables(crb_server *s, size_t bytes) {
         (void)hipGetLastError();
         return fail(CRB_ENOMEM, "round tables of %zu bytes: %s", cap, hipGetErrorString(e));
     }
+    // the active list's counters: each round leaves them at zero
+    e = hipMemsetAsync(s->d_tab, 0, (size_t)kListSegments * kTicketStride * 4, s->compute);
+    if (e != hipSuccess)
+        return hip_status(e, "hipMemsetAsync");
     s->tab_cap = cap;
     return CRB_OK;
 }
 
-// The tables of a round over `members`: frames, the first detection's tiles (of the frames at
-// iteration 1), every frame's tiles, and the results.
+// The tables of a round over `members`, on the device: the active list's counters (at the
+// start, whatever the round), the frames (from the host), the tiles of the frames at iteration
+// 1 and of the others, the list of those that have work, and the results (back to the host).
 struct RoundTables {
-    size_t ntd = 0, nts = 0;
-    size_t o_td, o_ts, o_st, bytes;
+    static constexpr size_t kCounters = (size_t)kListSegments * kTicketStride * 4;
+    size_t nnew = 0, nold = 0, max_tiles = 0;      // tiles of either kind
+    size_t o_frames = kCounters, o_new, o_old, o_active, o_st, bytes;
     explicit RoundTables(const std::vector<Request *> &members) {
         const size_t n = members.size();
         for (const Request *r : members) {
             const size_t t = (size_t)detect_tiles(r->H, r->W, kSumTY);
-            nts += t;
-            ntd += r->k_next == 1 ? t : 0;
+            if (r->k_next == 1)
+                nnew += t;
+            else
+                nold += (t + 63) / 64 * 64;        // (launch_tiles: in groups of 64)
+            max_tiles = t > max_tiles ? t : max_tiles;
         }
         auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-        o_td = al(n * sizeof(DevFrame));
-        o_ts = o_td + al(ntd * sizeof(TileRef));
-        o_st = o_ts + al(nts * sizeof(TileRef));
+        o_new = o_frames + al(n * sizeof(DevFrame));
+        o_old = o_new + al(nnew * sizeof(TileRef));
+        o_active = o_old + al(nold * sizeof(TileRef));
+        o_st = o_active + al(kListSegments * tile_list_cap(nold) * 4);
         bytes = o_st + al(2 * n * sizeof(long long));
     }
 };
@@ -368,20 +422,21 @@ static crb_status launch_round(crb_server *s) {
     crb_status st = ensure_tables(s, t.bytes);
     if (st != CRB_OK)
         return st;
-    DevFrame *hf = reinterpret_cast<DevFrame *>(s->h_tab);
-    TileRef *htd = reinterpret_cast<TileRef *>(s->h_tab + t.o_td);
-    TileRef *hts = reinterpret_cast<TileRef *>(s->h_tab + t.o_ts);
-    size_t itd = 0, its = 0;
+    DevFrame *hf = reinterpret_cast<DevFrame *>(s->h_tab + t.o_frames);
+    size_t inew = 0, iold = 0;
     for (int i = 0; i < n; ++i) {
         Request *r = s->active[i];
         hf[i] = r->df;
         hf[i].k = r->k_next;
-        for (int y = 0; y < r->H; y += kSumTY)
-            for (int x = 0; x < r->W; x += kSumTX) {
-                hts[its++] = TileRef{i, y, x, 0};
-                if (r->k_next == 1)
-                    htd[itd++] = TileRef{i, y, x, 0};
-            }
+        const size_t nt = (size_t)detect_tiles(r->H, r->W, kSumTY);
+        hf[i].list_base[0] = hf[i].list_base[1] = hf[i].list_base[2] = -1;
+        if (r->k_next == 1) {
+            hf[i].list_base[1] = (int)inew;
+            inew += nt;
+        } else {
+            hf[i].tile_base = (int)iold;
+            iold += (nt + 63) / 64 * 64;
+        }
         if (r->need_wait) {
             hipError_t e = hipStreamWaitEvent(s->compute, r->ev_h2d, 0);
             if (e != hipSuccess)
@@ -389,23 +444,32 @@ static crb_status launch_round(crb_server *s) {
             r->need_wait = false;
         }
     }
-    const DevFrame *dfr = reinterpret_cast<const DevFrame *>(s->d_tab);
-    const TileRef *dtd = reinterpret_cast<const TileRef *>(s->d_tab + t.o_td);
-    const TileRef *dts = reinterpret_cast<const TileRef *>(s->d_tab + t.o_ts);
+    const DevFrame *dfr = reinterpret_cast<const DevFrame *>(s->d_tab + t.o_frames);
+    TileRef *dnew = reinterpret_cast<TileRef *>(s->d_tab + t.o_new);
+    TileRef *dold = reinterpret_cast<TileRef *>(s->d_tab + t.o_old);
     long long *dst = reinterpret_cast<long long *>(s->d_tab + t.o_st);
+    const TileList active = {reinterpret_cast<unsigned int *>(s->d_tab + t.o_active),
+                             reinterpret_cast<unsigned int *>(s->d_tab), kListSegments,
+                             (int)tile_list_cap(t.nold)};
     DevFrame none;
     memset(&none, 0, sizeof(none));
-    hipError_t e = hipMemcpyAsync(s->d_tab, s->h_tab, t.o_st, hipMemcpyHostToDevice, s->compute);
-    // rounds mix frames at different iterations, so no list says which tiles to visit: every
-    // tile's block looks at its mark
+    hipError_t e = hipMemcpyAsync(s->d_tab + t.o_frames, hf, n * sizeof(DevFrame),
+                                  hipMemcpyHostToDevice, s->compute);
+    // Rounds mix frames at different iterations.  Those at iteration 1 take the first detection
+    // and then every tile; the others the tiles their marks name.
     const LaunchCfg cfg;
     const StepLists lists = {};
-    if (e == hipSuccess && t.ntd)
-        e = launch_detect(dfr, dtd, (int)t.ntd, none, cfg, lists, nullptr, s->compute);
     if (e == hipSuccess)
-        e = launch_step(dfr, dts, (int)t.nts, none, 0, false, lists, nullptr, s->compute);
+        e = launch_tiles(dfr, n, t.max_tiles, nullptr, dnew, nullptr, dold, active, nullptr, 0,
+                         s->compute);
+    if (e == hipSuccess && t.nnew)
+        e = launch_detect(dfr, dnew, (int)t.nnew, none, cfg, lists, nullptr, s->compute);
+    if (e == hipSuccess && t.nnew)
+        e = launch_step(dfr, dnew, (int)t.nnew, none, 1, false, lists, nullptr, s->compute);
+    if (e == hipSuccess && t.nold)
+        e = launch_step_active(dfr, dold, t.nold, active, s->compute);
     if (e == hipSuccess)
-        e = launch_round_stats(dfr, n, dst, s->compute);
+        e = launch_round_stats(dfr, n, dst, active, s->compute);
     if (e == hipSuccess)
         e = hipMemcpyAsync(s->h_tab + t.o_st, dst, 2 * n * sizeof(long long),
                            hipMemcpyDeviceToHost, s->compute);
@@ -433,6 +497,10 @@ static crb_status finish_round(crb_server *s) {
             still.push_back(r);
             continue;
         }
+        r->state = kDraining;
+        s->draining.push_back(r);
+        if (r->in_buffers)
+            continue;                  // (no event: the results are where they belong)
         // download the cleaned image and the mask once the round is complete
         crb_status st = get_event(s, &r->ev_d2h);
         if (st != CRB_OK)
@@ -450,8 +518,6 @@ static crb_status finish_round(crb_server *s) {
             e = hipEventRecord(r->ev_d2h, s->copy);
         if (e != hipSuccess)
             return hip_status(e, "download");
-        r->state = kDraining;
-        s->draining.push_back(r);
     }
     // frames admitted while the round ran were appended after its members
     for (size_t i = s->round_members.size(); i < s->active.size(); ++i)
@@ -459,6 +525,32 @@ static crb_status finish_round(crb_server *s) {
     s->active.swap(still);
     s->round_members.clear();
     s->round_busy = false;
+    return CRB_OK;
+}
+
+// completed requests: results in place, or their download finished
+static crb_status collect(crb_server *s, int64_t *done_ids, double *done_latency,
+                          int32_t max_done, int32_t *n_done) {
+    for (size_t i = 0; i < s->draining.size() && *n_done < max_done;) {
+        Request *r = s->draining[i];
+        const hipError_t q = r->in_buffers ? hipSuccess : hipEventQuery(r->ev_d2h);
+        if (q == hipErrorNotReady) {
+            ++i;
+            continue;
+        }
+        if (q != hipSuccess)
+            return hip_status(q, "download event");
+        const size_t npx = (size_t)r->H * r->W;
+        if (!r->direct) {
+            s->copies->copy(r->host_clean, r->pin, 4 * npx);
+            s->copies->copy(r->host_mask, r->pin + 4 * npx, npx);
+        }
+        done_ids[*n_done] = r->id;
+        done_latency[*n_done] = now_s() - r->t_submit;
+        ++*n_done;
+        s->draining.erase(s->draining.begin() + i);
+        release_request(s, r);
+    }
     return CRB_OK;
 }
 
@@ -544,6 +636,13 @@ crb_status crb_server_submit(crb_server *s, const float *host_img, int32_t H, in
     }
     r->on_device = ki == 2;
     r->direct = ki > 0 && kc > 0 && km > 0;
+    if (r->on_device) {
+        const hipStream_t ts = thread_stream();
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        r->idle = hipStreamIsCapturing(ts, &cap) == hipSuccess &&
+                  cap == hipStreamCaptureStatusNone && hipStreamQuery(ts) == hipSuccess;
+        (void)hipGetLastError();
+    }
     if (niter == 0 && r->on_device) {
         // nothing to compute: the result is the input, copied on the device
         hipError_t e = hipMemcpyAsync(host_clean, host_img, 4 * npx, hipMemcpyDeviceToDevice,
@@ -585,27 +684,8 @@ crb_status crb_server_poll(crb_server *s, int64_t *done_ids, double *done_latenc
             ++it;
         }
     }
-    // finished downloads
-    for (size_t i = 0; i < s->draining.size() && *n_done < max_done;) {
-        Request *r = s->draining[i];
-        hipError_t q = hipEventQuery(r->ev_d2h);
-        if (q == hipErrorNotReady) {
-            ++i;
-            continue;
-        }
-        if (q != hipSuccess)
-            return hip_status(q, "download event");
-        const size_t npx = (size_t)r->H * r->W;
-        if (!r->direct) {
-            s->copies->copy(r->host_clean, r->pin, 4 * npx);
-            s->copies->copy(r->host_mask, r->pin + 4 * npx, npx);
-        }
-        done_ids[*n_done] = r->id;
-        done_latency[*n_done] = now_s() - r->t_submit;
-        ++*n_done;
-        s->draining.erase(s->draining.begin() + i);
-        release_request(s, r);
-    }
+    if ((st = collect(s, done_ids, done_latency, max_done, n_done)) != CRB_OK)
+        return st;
     // the round in flight
     if (s->round_busy) {
         hipError_t q = hipEventQuery(s->ev_round);
@@ -616,7 +696,8 @@ crb_status crb_server_poll(crb_server *s, int64_t *done_ids, double *done_latenc
         }
         if (q != hipSuccess)
             return hip_status(q, "round event");
-        if ((st = finish_round(s)) != CRB_OK)
+        if ((st = finish_round(s)) != CRB_OK ||
+            (st = collect(s, done_ids, done_latency, max_done, n_done)) != CRB_OK)
             return st;
     }
     if ((st = admit(s)) != CRB_OK)

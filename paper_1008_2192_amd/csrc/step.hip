@@ -399,19 +399,18 @@ void k_step(const DevFrame *__restrict__ frames, const TileRef *__restrict__ til
     step_one(frames, tiles, single, (int)blockIdx.x, kiter, true, lists, sh, tid);
 }
 
-// Iteration k on the tiles listed for it: block b takes entries b / nseg, b / nseg + stride,
-// ... of segment b % nseg.
+// The tiles of a list: block b takes entries b / nseg, b / nseg + stride, ... of segment
+// b % nseg.  kiter: the iteration (0: each frame's own).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
 void k_step_listed(const DevFrame *__restrict__ frames, const TileRef *__restrict__ tiles,
-                   DevFrame single, int kiter, StepLists lists) {
+                   DevFrame single, int kiter, TileList in, StepLists lists) {
     __shared__ StepShared sh;
-    if (blockIdx.x == 0)
+    if (blockIdx.x == 0 && lists.list[0])
         lists_clear(lists, kiter + 2, (int)threadIdx.x);
-    const int seg = (int)blockIdx.x & (lists.nseg - 1), stride = (int)gridDim.x / lists.nseg;
-    const unsigned int *list = lists.list[kiter & 1] + (size_t)seg * lists.cap;
-    const int n = min((int)lists.count[((kiter % 3) * lists.nseg + seg) * kTicketStride],
-                      lists.cap);
-    for (int e = (int)blockIdx.x / lists.nseg; e < n; e += stride) {
+    const int seg = (int)blockIdx.x & (in.nseg - 1), stride = (int)gridDim.x / in.nseg;
+    const unsigned int *list = in.list + (size_t)seg * in.cap;
+    const int n = min((int)in.count[seg * kTicketStride], in.cap);
+    for (int e = (int)blockIdx.x / in.nseg; e < n; e += stride) {
         // as in the persistent detection, thread-derived values are not held across tiles
         int tid = (int)threadIdx.x;
         asm volatile("" : "+v"(tid));
@@ -420,6 +419,12 @@ void k_step_listed(const DevFrame *__restrict__ frames, const TileRef *__restric
         step_one(frames, tiles, single, g, kiter, false, lists, sh, tid);
         __syncthreads();       // the tile is done with the LDS
     }
+}
+
+// Blocks of a listed launch: a multiple of the segments, about as many as the device holds.
+static int listed_grid(size_t ntiles, int nseg) {
+    const size_t per = (ntiles + nseg - 1) / nseg, most = 1280 / nseg;
+    return (int)(per < most ? per : most) * nseg;
 }
 
 hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
@@ -432,12 +437,21 @@ hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int nti
     if (k <= 1 || all || !lists.list[0]) {
         k_step<<<ntiles, 256, 0, s>>>(d_frames, d_tiles, single, k, lists, tickets);
     } else {
-        // a multiple of the segments, about as many blocks as the device holds
-        int per = (ntiles + lists.nseg - 1) / lists.nseg;
-        const int most = 1280 / lists.nseg;
-        per = per < most ? per : most;
-        k_step_listed<<<per * lists.nseg, 256, 0, s>>>(d_frames, d_tiles, single, k, lists);
+        const TileList in = {lists.list[k & 1],
+                             lists.count + (size_t)(k % 3) * lists.nseg * kTicketStride,
+                             lists.nseg, lists.cap};
+        k_step_listed<<<listed_grid((size_t)ntiles, in.nseg), 256, 0, s>>>(d_frames, d_tiles,
+                                                                           single, k, in, lists);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_step_active(const DevFrame *d_frames, const TileRef *d_tiles, size_t ntiles,
+                              const TileList &active, hipStream_t s) {
+    DevFrame none = {};
+    const StepLists lists = {};
+    k_step_listed<<<listed_grid(ntiles, active.nseg), 256, 0, s>>>(d_frames, d_tiles, none, 0,
+                                                                   active, lists);
     return hipGetLastError();
 }
 

@@ -40,6 +40,7 @@ class Server:
                 raise ValueError("img must be a contiguous 2-D float32 tensor")
             H, W = img.shape
             if img.is_cuda:
+                _lib.set_stream()         # (its unfinished work may still use a recycled output)
                 clean = torch.empty((H, W), dtype=torch.float32, device=img.device)
                 mask = torch.empty((H, W), dtype=torch.uint8, device=img.device)
             else:
