@@ -146,9 +146,9 @@ typedef struct {
  * to actors (Section 6.2), here whole frames of uneven size sharing each launch.
  * Each frame's outputs are bit-identical to a crb_lacosmic call with the same
  * parameters (Section 5 for the method).  Synchronous, unlike the other cleaning
- * calls: it writes the host fields iters_run and n_flagged of frames[] at completion
- * and frees its per-call workspace before returning, so it waits for the batch on
- * hip_stream (NULL: default stream).  The stream-ordered, asynchronous form is the
+ * calls: it writes the host fields iters_run and n_flagged of frames[] at completion,
+ * so it waits for the batch on hip_stream (NULL: default stream).  Its workspace is the
+ * stream's (kept until crb_release_workspace), or freed before returning above 1 GiB.  The stream-ordered, asynchronous form is the
  * batch plan below (crb_plan_run, then crb_plan_stats for the per-frame results).
  */
 crb_status crb_lacosmic_batched(crb_frame *frames, int32_t n, void *hip_stream);
@@ -257,8 +257,8 @@ crb_status crb_plan_autotune(crb_plan *plan, int32_t reps, int32_t use_cache, cr
  * dependency radius is 8 pixels); smaller borders show the subimage edge effects
  * the paper's 6-pixel border trades against overlap.  border = -1 takes the declared
  * radius of the cleaning pass, 8 * niter (crb_work_radius of CRB_WORK_LACOSMIC).
- * Synchronous on the calling thread's stream; allocates temporary device memory for
- * the subimages.
+ * Synchronous on the calling thread's stream, whose workspace holds the subimages (above
+ * 1 GiB: memory allocated and freed by the call).
  *   ny, nx >= 1 with ny <= H and nx <= W; border >= -1; other arguments as crb_lacosmic.
  */
 crb_status crb_lacosmic_partitioned(const float *img, int32_t H, int32_t W, float gain,

@@ -729,6 +729,7 @@ struct crb_plan {
     bool any_copy = false;              // some frame has niter == 0
     size_t all_pix = 0;
     char *dmem = nullptr;
+    bool own_mem = true;                // dmem is the plan's (else a stream's workspace)
     DevFrame *d_frames = nullptr;
     TileRef *d_tdet[3] = {nullptr, nullptr, nullptr};   // per detection tile height
     int ntdet[3] = {0, 0, 0};
@@ -857,7 +858,7 @@ static void plan_free(crb_plan *p) {
     if (!p)
         return;
     plan_drop_graph(p);
-    if (p->dmem) {
+    if (p->dmem && p->own_mem) {
         (void)hipStreamSynchronize(p->stream);
         (void)hipFree(p->dmem);
     }
@@ -1017,21 +1018,54 @@ static crb_status time_cfg(crb_plan *p, const LaunchCfg &c, int reps, hipEvent_t
 
 }  // namespace crb
 
-extern "C" {
+namespace crb {
 
-crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
-                           int32_t use_graph, crb_plan **out_plan) {
-    if (!out_plan)
-        return fail(CRB_EINVAL, "null out_plan");
-    *out_plan = nullptr;
-    if (!frames || n < 1)
-        return fail(CRB_EINVAL, "need at least one frame");
+// Device memory of a plan: the frames' workspaces, then its tables.
+struct PlanLayout {
+    std::vector<FrameWs> ws;
+    std::vector<size_t> off;            // of each frame's workspace
+    size_t ntiles[3] = {0, 0, 0};       // per detection tile height
+    size_t max_tiles = 0;               // of one frame, at the smallest height
+    size_t o_frames, o_tdet[3], o_lists, o_stats, o_work, o_tickets, bytes;
+};
+
+static size_t al256(size_t x) { return (x + 255) / 256 * 256; }
+
+// Sizes only (pointers may still be null); the frames' H and W are valid.
+static PlanLayout plan_layout(const crb_frame *frames, int32_t n) {
+    PlanLayout L;
+    L.ws.resize(n);
+    L.off.resize(n);
+    size_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        const int H = frames[i].H, W = frames[i].W;
+        L.ws[i] = ws_layout(H, W);
+        L.off[i] = total;
+        total += L.ws[i].lists;
+        for (int t = 0; t < 3; ++t)
+            L.ntiles[t] += (size_t)detect_tiles(H, W, kTileHeights[t]);
+        const size_t most = (size_t)detect_tiles(H, W, kTileHeights[0]);
+        L.max_tiles = most > L.max_tiles ? most : L.max_tiles;
+    }
+    L.o_frames = total;
+    L.o_tdet[0] = L.o_frames + al256(n * sizeof(DevFrame));
+    L.o_tdet[1] = L.o_tdet[0] + al256(L.ntiles[0] * sizeof(TileRef));
+    L.o_tdet[2] = L.o_tdet[1] + al256(L.ntiles[1] * sizeof(TileRef));
+    L.o_lists = L.o_tdet[2] + al256(L.ntiles[2] * sizeof(TileRef));
+    L.o_stats = L.o_lists + al256(4 * list_words(L.ntiles[tile_h_index(kSumTY)]));
+    L.o_work = L.o_stats + al256(2 * n * sizeof(long long));
+    L.o_tickets = L.o_work + al256(kWorkCounters * n * sizeof(unsigned long long));
+    L.bytes = L.o_tickets + al256((size_t)kTicketWords * 4);
+    return L;
+}
+
+// A plan on `mem` (layout.bytes bytes that outlive it), or on memory of its own (mem null).
+// On memory of its own the tables have been written on return; else they are on the stream.
+static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stream,
+                            bool use_graph, char *mem, crb_plan **out_plan) {
     crb_status st;
-    std::vector<FrameWs> lay(n);
-    std::vector<size_t> off(n);
-    size_t total = 0, max_pix = 0, all_pix = 0, init_pix = 0;
+    size_t all_pix = 0, max_pix = 0, init_pix = 0;
     int kmax = 0;
-    size_t ntdet[3] = {0, 0, 0};
     for (int i = 0; i < n; ++i) {
         const crb_frame &f = frames[i];
         st = check_frame_args(f.H, f.W, f.gain, f.readnoise, f.sky, f.sigclip, f.sigfrac,
@@ -1041,18 +1075,14 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
         const size_t npix = (size_t)f.H * (size_t)f.W;
         if ((st = check_buffers(f.img, f.out_clean, f.out_mask, npix)) != CRB_OK)
             return fail(st, "frame %d: %s", i, crb_last_error());
-        lay[i] = ws_layout(f.H, f.W);
-        off[i] = total;
-        total += lay[i].lists;
         max_pix = npix > max_pix ? npix : max_pix;
         if (f.niter == 0)      // the init kernel copies these frames
             init_pix = npix > init_pix ? npix : init_pix;
         all_pix += npix;
         kmax = f.niter > kmax ? f.niter : kmax;
-        for (int t = 0; t < 3; ++t)
-            ntdet[t] += (size_t)detect_tiles(f.H, f.W, kTileHeights[t]);
     }
-    if (ntdet[0] > (size_t)INT32_MAX)
+    const PlanLayout L = plan_layout(frames, n);
+    if (L.ntiles[0] > (size_t)INT32_MAX)
         return fail(CRB_ETOOBIG, "batch too large");
     // also guard against buffers shared between frames
     for (int i = 0; i < n; ++i)
@@ -1064,19 +1094,6 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
                 ranges_overlap(frames[j].out_clean, nj * 4, frames[i].img, ni * 4))
                 return fail(CRB_EINVAL, "frames %d and %d share output memory", i, j);
         }
-    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t o_frames = total;
-    size_t o_tdet[3];
-    o_tdet[0] = o_frames + al(n * sizeof(DevFrame));
-    o_tdet[1] = o_tdet[0] + al(ntdet[0] * sizeof(TileRef));
-    o_tdet[2] = o_tdet[1] + al(ntdet[1] * sizeof(TileRef));
-    const size_t nsum = ntdet[tile_h_index(kSumTY)];
-    const size_t o_lists = o_tdet[2] + al(ntdet[2] * sizeof(TileRef));
-    const size_t o_stats = o_lists + al(4 * list_words(nsum));
-    const size_t o_work = o_stats + al(2 * n * sizeof(long long));
-    const size_t o_tickets = o_work + al(kWorkCounters * n * sizeof(unsigned long long));
-    const size_t bytes = o_tickets + al((size_t)kTicketWords * 4);
-
     crb_plan *p = new (std::nothrow) crb_plan();
     if (!p)
         return fail(CRB_ENOMEM, "host allocation failed");
@@ -1085,7 +1102,7 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
         delete p;
         return hip_status(e, "hipGetDevice");
     }
-    p->stream = (hipStream_t)hip_stream;
+    p->stream = stream;
     if (!p->stream && use_graph) {
         e = hipStreamCreateWithFlags(&p->stream, hipStreamNonBlocking);
         if (e != hipSuccess) {
@@ -1094,12 +1111,18 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
         }
         p->own_stream = true;
     }
-    e = hipMalloc((void **)&p->dmem, bytes);
-    if (e != hipSuccess) {
-        p->dmem = nullptr;
-        plan_free(p);
-        (void)hipGetLastError();
-        return fail(CRB_ENOMEM, "batch workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
+    if (mem) {
+        p->dmem = mem;
+        p->own_mem = false;
+    } else {
+        e = hipMalloc((void **)&p->dmem, L.bytes);
+        if (e != hipSuccess) {
+            p->dmem = nullptr;
+            plan_free(p);
+            (void)hipGetLastError();
+            return fail(CRB_ENOMEM, "batch workspace of %zu bytes: %s", L.bytes,
+                        hipGetErrorString(e));
+        }
     }
     p->n = n;
     p->kmax = kmax;
@@ -1107,34 +1130,33 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     p->init_pix = init_pix;
     p->any_copy = init_pix > 0;
     p->all_pix = all_pix;
-    p->d_frames = reinterpret_cast<DevFrame *>(p->dmem + o_frames);
+    p->d_frames = reinterpret_cast<DevFrame *>(p->dmem + L.o_frames);
     for (int t = 0; t < 3; ++t) {
-        p->d_tdet[t] = reinterpret_cast<TileRef *>(p->dmem + o_tdet[t]);
-        p->ntdet[t] = (int)ntdet[t];
+        p->d_tdet[t] = reinterpret_cast<TileRef *>(p->dmem + L.o_tdet[t]);
+        p->ntdet[t] = (int)L.ntiles[t];
     }
-    p->lists = make_lists(p->dmem + o_lists, nsum);
-    p->d_stats = reinterpret_cast<long long *>(p->dmem + o_stats);
-    p->d_work = reinterpret_cast<unsigned long long *>(p->dmem + o_work);
-    p->d_tickets = reinterpret_cast<unsigned int *>(p->dmem + o_tickets);
+    p->lists = make_lists(p->dmem + L.o_lists, L.ntiles[tile_h_index(kSumTY)]);
+    p->d_stats = reinterpret_cast<long long *>(p->dmem + L.o_stats);
+    p->d_work = reinterpret_cast<unsigned long long *>(p->dmem + L.o_work);
+    p->d_tickets = reinterpret_cast<unsigned int *>(p->dmem + L.o_tickets);
 
-    std::vector<DevFrame> hf(n);
-    std::vector<TileRef> td[3];
-    for (int t = 0; t < 3; ++t)
-        td[t].reserve(ntdet[t]);
+    std::vector<DevFrame> &hf = p->hframes;
+    hf.resize(n);
+    int base[3] = {0, 0, 0};
     for (int i = 0; i < n; ++i) {
         const crb_frame &f = frames[i];
-        hf[i] = make_devframe(f.img, f.out_clean, f.out_mask, p->dmem + off[i], lay[i], f.H, f.W,
-                              f.gain, f.readnoise, f.sky, f.sigclip, f.sigfrac, f.objlim,
+        hf[i] = make_devframe(f.img, f.out_clean, f.out_mask, p->dmem + L.off[i], L.ws[i], f.H,
+                              f.W, f.gain, f.readnoise, f.sky, f.sigclip, f.sigfrac, f.objlim,
                               f.niter,
                               (f.flags & CRB_FLAG_NO_EARLY_STOP ? kNoEarlyStop : 0) |
                                   (f.flags & CRB_FLAG_INCREMENTAL ? kIncremental : 0) |
                                   kFreshMask);
         hf[i].work = p->d_work + kWorkCounters * (size_t)i;
-        hf[i].tile_base = (int)td[tile_h_index(kSumTY)].size();
-        for (int t = 0; t < 3; ++t)
-            for (int y = 0; y < f.H; y += kTileHeights[t])
-                for (int x = 0; x < f.W; x += kDetectTX)
-                    td[t].push_back(TileRef{i, y, x, 0});
+        hf[i].tile_base = base[tile_h_index(kSumTY)];
+        for (int t = 0; t < 3; ++t) {
+            hf[i].list_base[t] = base[t];
+            base[t] += detect_tiles(f.H, f.W, kTileHeights[t]);
+        }
     }
     // launch shapes: the tune cache's entry for this layout, if any, else the defaults
     const char *cache = getenv("CRB_TUNE_CACHE");
@@ -1144,25 +1166,22 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
         if (tune_cache_lookup(p->key, &cached))
             p->cfg = cached;
     }
-    // Tables and counters are written on the plan's stream and waited for: a
-    // null-stream copy or memset is not ordered before work on a non-blocking stream,
-    // and a pageable copy may return before its data has landed.
+    // The frame table is copied on the plan's stream (a null-stream copy is not ordered before
+    // work on a non-blocking stream) and the tile lists, the work counters and the tickets are
+    // written from it there (each run leaves the tickets at zero again).
     e = hipMemcpyAsync(p->d_frames, hf.data(), n * sizeof(DevFrame), hipMemcpyHostToDevice,
                        p->stream);
+    const TileList none = {};
     if (e == hipSuccess)
-        e = hipMemsetAsync(p->d_work, 0, kWorkCounters * (size_t)n * sizeof(unsigned long long),
-                           p->stream);
-    for (int t = 0; t < 3 && e == hipSuccess; ++t)
-        e = hipMemcpyAsync(p->d_tdet[t], td[t].data(), td[t].size() * sizeof(TileRef),
-                           hipMemcpyHostToDevice, p->stream);
-    if (e == hipSuccess)       // (each run leaves the tickets at zero again)
-        e = hipMemsetAsync(p->d_tickets, 0, kTicketWords * 4, p->stream);
-    if (e == hipSuccess)
+        e = launch_tiles(p->d_frames, n, L.max_tiles, p->d_tdet[0], p->d_tdet[1], p->d_tdet[2],
+                         nullptr, none, reinterpret_cast<unsigned int *>(p->d_work),
+                         (int)((L.bytes - L.o_work) / 4), p->stream);
+    if (e == hipSuccess && p->own_mem)
         e = hipStreamSynchronize(p->stream);
-    p->hframes = hf;
     if (e != hipSuccess) {
+        (void)hipStreamSynchronize(p->stream);     // (the copy may still read the host table)
         plan_free(p);
-        return hip_status(e, "hipMemcpy");
+        return hip_status(e, "plan tables");
     }
     if (use_graph) {
         p->use_graph = true;
@@ -1173,6 +1192,53 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     }
     *out_plan = p;
     return ok();
+}
+
+// Memory of a synchronous call: the stream's workspace (kept until crb_release_workspace, so
+// that a call after the first allocates nothing), or, above this size, freed by the call.
+constexpr size_t kKeepBytes = (size_t)1 << 30;
+
+struct CallMemory {
+    Workspace *ws = nullptr;
+    std::unique_lock<std::mutex> lock;
+    char *mem = nullptr;
+
+    crb_status reserve(hipStream_t s, size_t bytes) {
+        if (bytes > kKeepBytes) {
+            const hipError_t e = hipMalloc((void **)&mem, bytes);
+            if (e == hipSuccess)
+                return CRB_OK;
+            mem = nullptr;
+            (void)hipGetLastError();
+            return fail(CRB_ENOMEM, "%zu bytes: %s", bytes, hipGetErrorString(e));
+        }
+        crb_status st = ws_get(s, &ws);
+        if (st != CRB_OK)
+            return st;
+        lock = std::unique_lock<std::mutex>(ws->mu);
+        if ((st = ws_reserve(ws, bytes)) == CRB_OK)
+            mem = ws->buf;
+        return st;
+    }
+    // (the caller has waited for the stream)
+    ~CallMemory() {
+        if (mem && !ws)
+            (void)hipFree(mem);
+    }
+};
+
+}  // namespace crb
+
+extern "C" {
+
+crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
+                           int32_t use_graph, crb_plan **out_plan) {
+    if (!out_plan)
+        return fail(CRB_EINVAL, "null out_plan");
+    *out_plan = nullptr;
+    if (!frames || n < 1)
+        return fail(CRB_EINVAL, "need at least one frame");
+    return plan_make(frames, n, (hipStream_t)hip_stream, use_graph != 0, nullptr, out_plan);
 }
 
 crb_status crb_plan_run(crb_plan *p) {
@@ -1377,13 +1443,29 @@ crb_status crb_plan_kernel_times(crb_plan *p, double *ms, int64_t *launches) {
 }
 
 crb_status crb_lacosmic_batched(crb_frame *frames, int32_t n, void *hip_stream) {
-    crb_plan *p = nullptr;
-    crb_status st = crb_plan_create(frames, n, hip_stream, 0, &p);
+    if (!frames || n < 1)
+        return fail(CRB_EINVAL, "need at least one frame");
+    for (int i = 0; i < n; ++i) {        // (the sizes, before anything is measured by them)
+        const crb_status st = check_frame_args(frames[i].H, frames[i].W, frames[i].gain,
+                                               frames[i].readnoise, frames[i].sky,
+                                               frames[i].sigclip, frames[i].sigfrac,
+                                               frames[i].objlim, frames[i].niter);
+        if (st != CRB_OK)
+            return fail(st, "frame %d: %s", i, crb_last_error());
+    }
+    hipStream_t s = (hipStream_t)hip_stream;
+    CallMemory mem;
+    crb_status st = mem.reserve(s, plan_layout(frames, n).bytes);
     if (st != CRB_OK)
+        return st;
+    crb_plan *p = nullptr;
+    if ((st = plan_make(frames, n, s, false, mem.mem, &p)) != CRB_OK)
         return st;
     st = crb_plan_run(p);
     if (st == CRB_OK)
         st = crb_plan_stats(p, frames, n);
+    if (st != CRB_OK)
+        (void)hipStreamSynchronize(s);
     plan_free(p);
     return st == CRB_OK ? ok() : st;
 }
@@ -1436,28 +1518,12 @@ extern "C" crb_status crb_lacosmic_partitioned(const float *img, int32_t H, int3
             max_sub = n > max_sub ? n : max_sub;
         }
     }
-    const size_t o_tab = total;
-    const size_t bytes = o_tab + al(nsub * sizeof(SubRect));
-    char *tmp = nullptr;
-    hipError_t e = hipMalloc((void **)&tmp, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(CRB_ENOMEM, "subimages of %zu bytes: %s", bytes, hipGetErrorString(e));
-    }
     std::vector<crb_frame> frames(nsub);
     for (int q = 0; q < nsub; ++q) {
-        SubRect &r = subs[q];
-        const size_t n = (size_t)r.h * r.w;
-        r.sub_img = reinterpret_cast<float *>(tmp + off[q]);
-        r.sub_clean = reinterpret_cast<float *>(tmp + off[q] + al(4 * n));
-        r.sub_mask = reinterpret_cast<uint8_t *>(tmp + off[q] + 2 * al(4 * n));
         crb_frame &f = frames[q];
         memset(&f, 0, sizeof(f));
-        f.img = r.sub_img;
-        f.out_clean = r.sub_clean;
-        f.out_mask = r.sub_mask;
-        f.H = r.h;
-        f.W = r.w;
+        f.H = subs[q].h;
+        f.W = subs[q].w;
         f.gain = gain;
         f.readnoise = readnoise;
         f.sky = sky;
@@ -1467,32 +1533,42 @@ extern "C" crb_status crb_lacosmic_partitioned(const float *img, int32_t H, int3
         f.niter = niter;
         f.flags = g_incremental.load() ? CRB_FLAG_INCREMENTAL : 0;
     }
-    SubRect *d_subs = reinterpret_cast<SubRect *>(tmp + o_tab);
+    const size_t o_tab = total;
+    const size_t o_plan = o_tab + al(nsub * sizeof(SubRect));
+    CallMemory mem;
+    if ((st = mem.reserve(s, o_plan + plan_layout(frames.data(), nsub).bytes)) != CRB_OK)
+        return st;
+    for (int q = 0; q < nsub; ++q) {
+        SubRect &r = subs[q];
+        const size_t n = (size_t)r.h * r.w;
+        r.sub_img = reinterpret_cast<float *>(mem.mem + off[q]);
+        r.sub_clean = reinterpret_cast<float *>(mem.mem + off[q] + al(4 * n));
+        r.sub_mask = reinterpret_cast<uint8_t *>(mem.mem + off[q] + 2 * al(4 * n));
+        frames[q].img = r.sub_img;
+        frames[q].out_clean = r.sub_clean;
+        frames[q].out_mask = r.sub_mask;
+    }
+    SubRect *d_subs = reinterpret_cast<SubRect *>(mem.mem + o_tab);
     crb_plan *plan = nullptr;
-    // the table goes in on the launch stream (ordered before the extraction on any
-    // stream kind) and is waited for before `subs` can go out of scope
-    e = hipMemcpyAsync(d_subs, subs.data(), nsub * sizeof(SubRect), hipMemcpyHostToDevice, s);
+    // everything on the launch stream, which is waited for before `subs`, the plan's host
+    // tables and the memory can go away
+    hipError_t e = hipMemcpyAsync(d_subs, subs.data(), nsub * sizeof(SubRect),
+                                  hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = launch_extract(img, W, d_subs, nsub, max_sub, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        (void)hipFree(tmp);
-        return hip_status(e, "subimage extraction");
-    }
-    st = crb_plan_create(frames.data(), nsub, s, 0, &plan);
+    st = hip_status(e, "subimage extraction");
+    if (st == CRB_OK)
+        st = plan_make(frames.data(), nsub, s, false, mem.mem + o_plan, &plan);
     if (st == CRB_OK)
         st = crb_plan_run(plan);
-    if (st == CRB_OK) {
-        e = launch_stitch(out_clean, out_mask, W, d_subs, nsub, max_sub, s);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(s);
+    if (st == CRB_OK)
+        st = hip_status(launch_stitch(out_clean, out_mask, W, d_subs, nsub, max_sub, s),
+                        "subimage stitching");
+    e = hipStreamSynchronize(s);
+    if (st == CRB_OK)
         st = hip_status(e, "subimage stitching");
-    }
     if (plan)
         crb_plan_destroy(plan);
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(tmp);
     return st == CRB_OK ? ok() : st;
 }
 
