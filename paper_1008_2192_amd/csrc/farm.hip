@@ -7,6 +7,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 // Exclusive prefix sum over the lanes of a wave (all lanes active), from the device library.
 extern "C" __device__ unsigned int __ockl_wfscan_add_u32(unsigned int, bool);
 
@@ -22,9 +24,11 @@ namespace crb {
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int i = 0; i < 10; ++i) {
-        const uint32_t lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
-        const uint32_t lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
-        c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
+        // (one 64-bit product each: half the multiply instructions of a low and a high one)
+        const unsigned long long p0 = (unsigned long long)0xD2511F53u * c.x;
+        const unsigned long long p1 = (unsigned long long)0xCD9E8D57u * c.z;
+        c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k0, (uint32_t)p1,
+                       (uint32_t)(p0 >> 32) ^ c.w ^ k1, (uint32_t)p0);
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -52,30 +56,14 @@ __device__ __forceinline__ double exp_neg(double x) {
     return ldexp(p, (int)kf);
 }
 
-// Poisson deviate with mean `mean` by multiplying uniforms until the product drops
-// to e^-mean (Knuth's method); uniform j of pixel i comes from word j%4 of the
-// generator at counter (i_lo, i_hi, j/4, 0).
-__device__ __forceinline__ float poisson_deviate(float mean_f, size_t i, uint32_t k0,
-                                                 uint32_t k1) {
+// The limit e^-mean of Knuth's method for a pixel's mean (clamped to [0, 500]; non-finite: 0).
+__device__ __forceinline__ double poisson_limit(float mean_f) {
     double mean = (double)mean_f;
     if (!(mean > 0.0))
         mean = 0.0;
     if (mean > 500.0)
         mean = 500.0;
-    const double limit = exp_neg(mean);
-    double prod = 1.0;
-    unsigned int k = 0;
-    for (uint32_t blk = 0;; ++blk) {
-        const uint4 w = philox4x32_10(make_uint4((uint32_t)i, (uint32_t)(i >> 32), blk, 0u), k0, k1);
-        const uint32_t words[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            prod = prod * (((double)words[q] + 0.5) * (1.0 / 4294967296.0));
-            if (!(prod > limit))
-                return (float)k;
-            ++k;
-        }
-    }
+    return exp_neg(mean);
 }
 
 // A float in the global address space: loads through it are global (not flat) loads.
@@ -91,13 +79,82 @@ struct FarmCtx {
     int y, x, H, W;       // the pixel's frame coordinates, frame size
 };
 
+// POISSON: deviates by multiplying uniforms until the product drops to e^-mean (Knuth's
+// method); uniform j of pixel i comes from word j % 4 of the generator at counter (i_lo, i_hi,
+// j / 4, 0).  A wave takes a tile in chunks of kChunk pixels per lane: the lanes form their
+// pixels' limits together, and then each goes through its own pixels without waiting for the
+// others' -- with one pixel per lane at a time a wave drew for the largest of 64 deviates (10
+// blocks of four uniforms at mean 24.3, where a pixel needs 6.8).  Bound by the generator's
+// multiplies at one wave per SIMD: 750 x 750 pixels of mean 24.3 in rows on 1024 actors took
+// 60.7 us, with 64-bit products and this order 52.8 (two pixels of a lane at once: 52.3).
 struct WorkPoisson {
     static constexpr bool kList = false;
     static constexpr bool kNeighbours = false;
+    static constexpr int kChunk = 16;
     __host__ __device__ static int radius(const WorkArgs &) { return 0; }
-    __device__ static float pixel(const FarmCtx &c, const WorkArgs &a) {
-        const size_t i = (size_t)c.y * c.W + c.x;
-        return poisson_deviate(c.in[i], i, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+    // The tile of tw columns and n pixels at (y0, x0); limits: the wave's kChunk x 64 doubles.
+    __device__ static void tile(const float *__restrict__ in, float *__restrict__ out, int W,
+                                const WorkArgs &a, int y0, int x0, int tw, long long n,
+                                double *limits) {
+        const int lane = __lane_id();
+        const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+        const int q = 64 / tw, rem = 64 - q * tw;     // a step of 64 pixels
+        int ly = lane / tw, lx = lane - ly * tw;
+        for (long long j0 = 0; j0 < n; j0 += 64 * kChunk) {
+            int my = 0;                               // the lane's pixels of the chunk
+            int y = ly, x = lx;                       // (the first of them)
+            float mean[kChunk];
+#pragma unroll
+            for (int p = 0; p < kChunk; ++p) {
+                const bool on = j0 + 64 * p + lane < n;
+                my += on ? 1 : 0;
+                mean[p] = on ? in[(size_t)(y0 + ly) * W + x0 + lx] : 0.0f;
+                ly += q;
+                lx += rem;
+                if (lx >= tw) {
+                    lx -= tw;
+                    ++ly;
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < kChunk; ++p)
+                if (j0 + 64 * p < n)                  // (uniform)
+                    limits[p * 64 + lane] = poisson_limit(mean[p]);
+            // (each lane reads only what it wrote)
+            size_t i = (size_t)(y0 + y) * W + x0 + x;
+            double limit = limits[lane], prod = 1.0;
+            unsigned int k = 0;
+            uint32_t blk = 0;
+            for (int p = 0; p < my;) {
+                const uint4 w = philox4x32_10(make_uint4((uint32_t)i, (uint32_t)(i >> 32), blk, 0u),
+                                              k0, k1);
+                ++blk;
+                const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+                bool done = false;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double next = prod * (((double)words[u] + 0.5) * (1.0 / 4294967296.0));
+                    prod = done ? prod : next;
+                    done = done || !(prod > limit);
+                    k += done ? 0u : 1u;
+                }
+                if (done) {
+                    out[i] = (float)k;
+                    ++p;
+                    y += q;
+                    x += rem;
+                    if (x >= tw) {
+                        x -= tw;
+                        ++y;
+                    }
+                    i = (size_t)(y0 + y) * W + x0 + x;
+                    limit = limits[(p < kChunk ? p : 0) * 64 + lane];
+                    prod = 1.0;
+                    k = 0;
+                    blk = 0;
+                }
+            }
+        }
     }
 };
 
@@ -368,6 +425,8 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
     constexpr int kBufBatch = 16;   // rows of 64 pixels per batch of the buffer scan
     __shared__ int sCand[WF::kList ? 4 * kFarmCandidates : 1];
     __shared__ SourceRec sRec[WF::kList ? 4 * kFarmWaveRecords : 1];
+    constexpr bool kTiles = std::is_same<WF, WorkPoisson>::value;
+    __shared__ double sLimits[kTiles ? 4 * WorkPoisson::kChunk * 64 : 1];
     const int wave = threadIdx.x >> 6, lane = __lane_id();
     const int gwave = blockIdx.x * 4 + wave;
     if (gwave >= waves)
@@ -393,7 +452,10 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
             const long long n = (long long)th * tw;
             const int q = 64 / tw, rem = 64 - q * tw;
             int ly = lane / tw, lx = lane - ly * tw;
-            if constexpr (!WF::kList) {
+            if constexpr (kTiles) {
+                WF::tile(in, out_img, W, args, y0, x0, tw, n,
+                         sLimits + wave * WorkPoisson::kChunk * 64);
+            } else if constexpr (!WF::kList) {
                 for (long long j0 = 0; j0 < n; j0 += 64) {
                     if (j0 + lane < n) {
                         c.y = y0 + ly;
