@@ -508,15 +508,14 @@ crb_status crb_farm_run(const crb_work *w, const float *in, int32_t H, int32_t W
     if ((st = ws_get(s, &ws)) != CRB_OK)
         return st;
     std::lock_guard<std::mutex> g(ws->mu);
-    if ((st = ws_reserve(ws, 256)) != CRB_OK)
+    if ((st = ws_reserve(ws, kFarmTicketWords * 4)) != CRB_OK)
         return st;
     unsigned int *tickets = reinterpret_cast<unsigned int *>(ws->buf);
     unsigned long long *count = reinterpret_cast<unsigned long long *>(out_count);
-    hipError_t e = launch_farm_reset(tickets, count, s);
-    if (e == hipSuccess)
-        e = launch_farm(w->kind, a2, in, H, W, workers, tile_h, tile_w, out_image,
-                        reinterpret_cast<SourceRec *>(out_list), (long long)list_capacity, count,
-                        tickets, s);
+    const hipError_t e =
+        launch_farm(w->kind, a2, in, H, W, workers, tile_h, tile_w, out_image,
+                    reinterpret_cast<SourceRec *>(out_list), (long long)list_capacity, count,
+                    tickets, s);
     st = hip_status(e, "kernel launch");
     return st == CRB_OK ? ok() : st;
 }

@@ -28,7 +28,9 @@ namespace crb {
 
 constexpr int kWorkLacosmic = 0, kWorkPoisson = 1, kWorkWaiter = 2, kWorkSources = 3;
 constexpr int kMaxWorkRadius = 8;        // largest radius a work function may declare
-constexpr int kFarmQueues = 32;          // ticket counters (one tile range each)
+constexpr int kFarmQueues = 32;          // ticket counters (one tile range each),
+constexpr int kFarmStride = 32;          // each on its own 128-byte line
+constexpr int kFarmTicketWords = kFarmQueues * kFarmStride;
 constexpr int kFarmCandidates = 1024;    // candidates a wave collects before running them
 constexpr int kFarmWaveRecords = 128;    // records a wave buffers before moving them
 
@@ -50,11 +52,9 @@ struct SourceRec {
 // Declared dependency radius of a work function (host side); -1 for an unknown kind.
 int work_radius(int kind, const WorkArgs &a, int niter);
 
-// Clears the kFarmQueues ticket counters and, if count is not null, the record counter.
-hipError_t launch_farm_reset(unsigned int *tickets, unsigned long long *count, hipStream_t s);
 // Runs work function `kind` over the frame with `workers` persistent waves (actors).
 // Image kinds write out_img (H x W); list kinds append to out_list (at most capacity
-// records are stored, *count receives the total).  The tickets (and *count) must be zero.
+// records are stored, *count receives the total).  tickets: kFarmTicketWords words of scratch.
 hipError_t launch_farm(int kind, const WorkArgs &args, const float *in, int H, int W,
                        int workers, int tile_h, int tile_w, float *out_img,
                        SourceRec *out_list, long long capacity, unsigned long long *count,

@@ -86,7 +86,8 @@ struct FarmCtx {
 // others' -- with one pixel per lane at a time a wave drew for the largest of 64 deviates (10
 // blocks of four uniforms at mean 24.3, where a pixel needs 6.8).  Bound by the generator's
 // multiplies at one wave per SIMD: 750 x 750 pixels of mean 24.3 in rows on 1024 actors took
-// 60.7 us, with 64-bit products and this order 52.8 (two pixels of a lane at once: 52.3).
+// 60.7 us, with 64-bit products and this order 52.8 (two pixels of a lane at once: 52.3), and
+// with the farm's tickets on lines of their own 37.1.
 struct WorkPoisson {
     static constexpr bool kList = false;
     static constexpr bool kNeighbours = false;
@@ -333,64 +334,93 @@ struct WorkSources {
     }
 };
 
-__global__ void k_farm_reset(unsigned int *tickets, unsigned long long *count) {
-    if (threadIdx.x < kFarmQueues)
-        tickets[threadIdx.x] = 0u;
-    if (threadIdx.x == 0 && count)
+// A queue's line of tickets: [0] the tiles handed out, [1] a copy of the mask of drained
+// queues.  The first run of each wave needs no ticket (wave g takes run g / kFarmQueues of queue
+// g % kFarmQueues), so the counters start behind these runs.
+__global__ void k_farm_reset(unsigned int *tickets, long long ntiles, int waves, int chunk,
+                             unsigned long long *count) {
+    const int q = (int)threadIdx.x;               // one wave
+    const long long size = ntiles * (q + 1) / kFarmQueues - ntiles * q / kFarmQueues;
+    const long long start = (long long)((waves - q + kFarmQueues - 1) / kFarmQueues) * chunk;
+    const unsigned int drained = (unsigned int)__ballot(q < kFarmQueues && start >= size);
+    if (q < kFarmQueues) {
+        tickets[q * kFarmStride] = (unsigned int)start;
+        tickets[q * kFarmStride + 1] = drained;
+    }
+    if (q == 0 && count)
         *count = 0ull;
 }
 
+// The value of the lane before and of the lane after (-inf at the wave's ends).
+__device__ __forceinline__ float lane_before(float v) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+        (int)0xff800000, (int)__float_as_uint(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_after(float v) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+        (int)0xff800000, (int)__float_as_uint(v), 0x130, 0xf, 0xf, false));
+}
+
 // The next run of tiles for the calling wave, or t0 = -1 when every queue is drained.
-// Lane 0 takes a ticket from the wave's current queue; once that range is exhausted,
-// lanes 0..kFarmQueues-1 read all counters at once and the wave moves to the next
-// queue (in cyclic order) that still has tiles.
+// The wave's first run is `first` of its queue (then first is -1); after that lane 0 takes a
+// ticket from the wave's current queue, and once that queue is drained the wave moves to the
+// next one (in cyclic order) that it does not know to be.  The wave that draws the first ticket
+// past a queue's end says so in every line's mask; the others read the mask in the line they
+// draw from.  (Atomics, and reads past the L2s, of one line serialise at about 11 ns: with all
+// counters in one line, and each wave reading all of them at its end, SOURCES on a 4096 x 4096
+// frame took 206 us on 4096 actors and POISSON on 750 x 750 pixels in rows 49 on 1024; with a
+// line for each, the first runs without tickets and the masks, 59 and 33.)
 __device__ __forceinline__ void next_tiles(unsigned int *__restrict__ tickets, long long ntiles,
-                                           int chunk, int &queue, long long &t0, long long &t1) {
+                                           int chunk, int &first, unsigned int &drained,
+                                           int &queue, long long &t0, long long &t1) {
     const int lane = __lane_id();
     for (;;) {
         const long long q0 = ntiles * queue / kFarmQueues;
         const long long q1 = ntiles * (queue + 1) / kFarmQueues;
-        int got = 0;
-        if (lane == 0)
-            got = (int)atomicAdd(&tickets[queue], (unsigned int)chunk);
-        got = __shfl(got, 0);
+        unsigned int *const line = tickets + queue * kFarmStride;
+        const bool ticket = first < 0;
+        unsigned int got = ticket ? 0u : (unsigned int)first * (unsigned int)chunk;
+        if (ticket && lane == 0)
+            got = atomicAdd(&line[0], (unsigned int)chunk);
+        first = -1;
+        got = __builtin_amdgcn_readfirstlane(got);
         if (q0 + got < q1) {
             t0 = q0 + got;
             t1 = min(q1, t0 + chunk);
             return;
         }
-        bool open = false;
-        if (lane < kFarmQueues) {
-            const long long a = ntiles * lane / kFarmQueues;
-            const long long b = ntiles * (lane + 1) / kFarmQueues;
-            const unsigned int seen = __hip_atomic_load(&tickets[lane], __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
-            open = a + (long long)seen < b;
-        }
-        const unsigned long long m = __ballot(open) & ((1ull << kFarmQueues) - 1ull);
-        if (!m) {
+        if (ticket && q0 + got - chunk < q1 && lane < kFarmQueues)
+            atomicOr(&tickets[lane * kFarmStride + 1], 1u << queue);
+        unsigned int seen = 0u;
+        if (lane == 0)
+            seen = __hip_atomic_load(&line[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        drained |= __builtin_amdgcn_readfirstlane(seen) | 1u << queue;
+        const unsigned int open = ~drained;
+        if (!open) {
             t0 = t1 = -1;
             return;
         }
-        const unsigned long long after = m & ~((2ull << queue) - 1ull);
-        queue = __ffsll((long long)(after ? after : m)) - 1;
+        const unsigned int after = open & ~((2u << queue) - 1u);
+        queue = __ffs((int)(after ? after : open)) - 1;
     }
 }
 
-// Moves a wave's buffered records to the caller's list: one atomic on the counter
-// reserves their slots, then the wave copies them as 8-byte words.
+// The first of n slots of the caller's list, reserved for the wave by one atomic on the counter.
+__device__ __forceinline__ unsigned long long reserve_records(int n,
+                                                              unsigned long long *count) {
+    unsigned long long base = 0ull;
+    if (__lane_id() == 0)
+        base = atomicAdd(count, (unsigned long long)n);
+    const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)base);
+    const unsigned int hi = __builtin_amdgcn_readfirstlane((unsigned int)(base >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+// Moves n buffered records to the slots from base on, by the wave, as 8-byte words.
 __device__ __forceinline__ void flush_records(const SourceRec *__restrict__ buf, int n,
                                               SourceRec *__restrict__ out_list,
-                                              long long capacity,
-                                              unsigned long long *__restrict__ count) {
+                                              long long capacity, unsigned long long base) {
     constexpr int kWords = (int)(sizeof(SourceRec) / 8);
     const int lane = __lane_id();
-    unsigned long long base = 0ull;
-    if (lane == 0)
-        base = atomicAdd(count, (unsigned long long)n);
-    const unsigned int lo = __shfl((unsigned int)base, 0);
-    const unsigned int hi = __shfl((unsigned int)(base >> 32), 0);
-    base = ((unsigned long long)hi << 32) | lo;
     const unsigned long long *src = reinterpret_cast<const unsigned long long *>(buf);
     unsigned long long *dst = reinterpret_cast<unsigned long long *>(out_list);
     for (int i = lane; i < n * kWords; i += 64)
@@ -429,6 +459,13 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
     __shared__ double sLimits[kTiles ? 4 * WorkPoisson::kChunk * 64 : 1];
     const int wave = threadIdx.x >> 6, lane = __lane_id();
     const int gwave = blockIdx.x * 4 + wave;
+    __shared__ int sLeft[4];                // records a wave leaves at its end
+    __shared__ unsigned int sEnded;         // waves that have ended
+    if constexpr (WF::kList) {
+        if (threadIdx.x == 0)
+            sEnded = 0u;
+        __syncthreads();
+    }
     if (gwave >= waves)
         return;
     int *cand = sCand + (WF::kList ? wave * kFarmCandidates : 0);
@@ -436,14 +473,15 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
     int nrec = 0;
     const int ntx = (W - 1) / tile_w + 1;
     const long long ntiles = (long long)ntx * ((H - 1) / tile_h + 1);
-    int queue = gwave % kFarmQueues;
+    int queue = gwave % kFarmQueues, first = gwave / kFarmQueues;
+    unsigned int drained = 0u;
     FarmCtx c;
     c.in = in;
     c.H = H;
     c.W = W;
     for (;;) {
         long long t0, t1;
-        next_tiles(tickets, ntiles, chunk, queue, t0, t1);
+        next_tiles(tickets, ntiles, chunk, first, drained, queue, t0, t1);
         if (t0 < 0)
             break;
         for (long long t = t0; t < t1; ++t) {
@@ -487,7 +525,8 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
                             rbuf[nrec + __popcll(m & ((1ull << lane) - 1ull))] = rec;
                         nrec += __popcll(m);
                         if (nrec > kFarmWaveRecords - 64) {
-                            flush_records(rbuf, nrec, out_list, capacity, count);
+                            flush_records(rbuf, nrec, out_list, capacity,
+                                          reserve_records(nrec, count));
                             nrec = 0;
                         }
                     }
@@ -531,7 +570,7 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
                                 // direct neighbours this batch holds (same row: adjacent
                                 // lanes; rows above and below: adjacent batch entries
                                 // when a row is one segment)
-                                const float lf = __shfl_up(v[b], 1), rt = __shfl_down(v[b], 1);
+                                const float lf = lane_before(v[b]), rt = lane_after(v[b]);
                                 float up = -INFINITY, dn = -INFINITY;
                                 if (nseg == 1) {
                                     up = b > 0 ? v[b > 0 ? b - 1 : 0] : carry;
@@ -539,9 +578,8 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
                                         dn = v[b + 1 < kBufBatch ? b + 1 : b];
                                 }
                                 hit = hit && WF::neighbours(v[b], up, dn,
-                                                           lane > 0 ? lf : -INFINITY,
-                                                           lane < 63 && col + 1 < tw
-                                                               ? rt : -INFINITY, args);
+                                                           lf, col + 1 < tw ? rt : -INFINITY,
+                                                           args);
                             }
                             const unsigned long long m = __ballot(hit);
                             if (hit)
@@ -602,8 +640,26 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
         }
     }
     if constexpr (WF::kList) {
-        if (nrec)
-            flush_records(rbuf, nrec, out_list, capacity, count);
+        // the records left over go out together, by the block's last wave to end: the
+        // reservations of all waves are atomics on one address, which take 11 ns each
+        unsigned int ended = 0u;
+        if (lane == 0) {
+            sLeft[wave] = nrec;
+            __threadfence_block();
+            ended = atomicAdd(&sEnded, 1u);
+            __threadfence_block();
+        }
+        const int nw = min(4, waves - (int)blockIdx.x * 4);
+        if (__builtin_amdgcn_readfirstlane(ended) + 1u == (unsigned int)nw) {
+            int total = 0;
+            for (int w = 0; w < nw; ++w)
+                total += sLeft[w];
+            unsigned long long base = total ? reserve_records(total, count) : 0ull;
+            for (int w = 0; w < nw; ++w) {
+                flush_records(sRec + w * kFarmWaveRecords, sLeft[w], out_list, capacity, base);
+                base += (unsigned long long)sLeft[w];
+            }
+        }
     }
 }
 
@@ -618,6 +674,7 @@ hipError_t launch_kind(const WorkArgs &args, const float *in, int H, int W, int 
     long long chunk = ntiles / ((long long)workers * 2);
     chunk = chunk < 1 ? 1 : (chunk > 64 ? 64 : chunk);
     const int blocks = (workers + 3) / 4;
+    k_farm_reset<<<1, 64, 0, s>>>(tickets, ntiles, workers, (int)chunk, count);
     k_farm<WF><<<blocks, 256, 0, s>>>(in, H, W, args, tile_h, tile_w, (int)chunk, workers,
                                       out_img, out_list, capacity, count, tickets);
     return hipGetLastError();
@@ -636,11 +693,6 @@ int work_radius(int kind, const WorkArgs &a, int niter) {
     default:
         return -1;
     }
-}
-
-hipError_t launch_farm_reset(unsigned int *tickets, unsigned long long *count, hipStream_t s) {
-    k_farm_reset<<<1, 64, 0, s>>>(tickets, count);
-    return hipGetLastError();
 }
 
 hipError_t launch_farm(int kind, const WorkArgs &args, const float *in, int H, int W,
