@@ -775,37 +775,49 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
             if (counting)
                 ncells += tile_row ? 2u : 0u;
         };
-        // Wave w takes the list's entries 64 w, 64 w + 256, ...: one quad per lane (the
-        // 2 x 2 network) while more than 32 remain, and a last run of at most 32 quads
-        // two lanes per quad, one row each (the 1 x 2 network and two estimates, about
-        // 60% of a quad's instructions), as most tiles end their list with such a run.
-#pragma unroll 1
-        for (int q0 = tid - lane; q0 < nquads; q0 += NT) {
-            const int left = nquads - q0;                 // uniform in the wave
-            if (left > 32) {
-                if (lane < left) {
-                    const int q = (int)s.quads[q0 + lane];
-                    const int pr = q / L::SW, cc = q - pr * L::SW, r0 = 2 * pr;
-                    float v[6 * 6];
+        // One cell alone, as above.
+        auto exact_cell = [&](int rr, int cc, float u0, float l, float c0, float r, float d0,
+                              float m0) {
+            const int cx = cc - 2, cy = rr - 2;
+            const bool tile_row = cx >= 0 && cx < TX && cy >= 0 && cy < TY;
+            float e0;
+            const float s0 = s_estimate(c0, u0, d0, l, r, m0, sp, e0);
+            s.S[rr * L::SWP + cc] = s0;
+            emax = fmaxf(emax, e0);
+            uint32_t *hw = &sHot[rr * L::HWP + (cc >> 5)];
+            const uint32_t bit = 1u << (cc & 31);
+            if (!(s0 + e0 > sc_lo) && (bit & *hw))
+                atomicAnd(hw, ~bit);
+            if (tile_row && s0 + e0 > ll_lo)
+                atomicOr(&s.low[cy * L::QW + (cx >> 5)], 1u << (cx & 31));
+            if (counting)
+                ncells += tile_row ? 1u : 0u;
+        };
+        // As few quads per lane as the block's lanes allow, since a wave with work in few lanes
+        // takes as long as a full one.  Up to NT / 4 quads: four lanes per quad, a cell each (the
+        // 1 x 1 network).  Up to NT / 2: two lanes per quad, a row each (the 1 x 2 network and
+        // two estimates, about 60% of a quad's instructions).  Else one quad per lane (the 2 x 2
+        // network).  (With one quad per lane down to 32 of them the re-evaluation of a crowded
+        // 4096 x 4096 field's listed tiles took 95 and 50 us where it takes 89 and 46, that of
+        // the mixed batch 236 where it takes 215, and the first detection the same to 1%.)
+        if (nquads <= NT / 4) {
+            if (tid < 4 * nquads) {
+                const int q = (int)s.quads[tid >> 2];
+                const int pr = q / L::SW, cc = q - pr * L::SW + (tid & 1);
+                const int rr = 2 * pr + (tid >> 1 & 1);
+                float v[5 * 5], m5[1];
 #pragma unroll
-                    for (int i = 0; i < 6; ++i)
+                for (int i = 0; i < 5; ++i)
 #pragma unroll
-                        for (int j = 0; j < 6; ++j)
-                            v[i * 6 + j] = sJ[(r0 + i) * L::JWP + cc + j];
-                    float m5[4];
-                    med5_t2x2(v, m5);
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        constexpr int P = 6;
-                        const int pc = (i + 2) * P + 2;
-                        exact_row(r0 + i, cc, v[pc - P], v[pc + 1 - P], v[pc - 1], v[pc],
-                                  v[pc + 1], v[pc + 2], v[pc + P], v[pc + 1 + P], m5[2 * i],
-                                  m5[2 * i + 1]);
-                    }
-                }
-            } else if (lane < 2 * left) {
-                const int q = (int)s.quads[q0 + (lane >> 1)];
-                const int pr = q / L::SW, cc = q - pr * L::SW, rr = 2 * pr + (lane & 1);
+                    for (int j = 0; j < 5; ++j)
+                        v[i * 5 + j] = sJ[(rr + i) * L::JWP + cc + j];
+                med5_t1x1(v, m5);
+                exact_cell(rr, cc, v[7], v[11], v[12], v[13], v[17], m5[0]);
+            }
+        } else if (nquads <= NT / 2) {
+            if (tid < 2 * nquads) {
+                const int q = (int)s.quads[tid >> 1];
+                const int pr = q / L::SW, cc = q - pr * L::SW, rr = 2 * pr + (tid & 1);
                 float v[5 * 6];
 #pragma unroll
                 for (int i = 0; i < 5; ++i)
@@ -817,6 +829,28 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
                 constexpr int P = 6, pc = 2 * P + 2;
                 exact_row(rr, cc, v[pc - P], v[pc + 1 - P], v[pc - 1], v[pc], v[pc + 1],
                           v[pc + 2], v[pc + P], v[pc + 1 + P], m5[0], m5[1]);
+            }
+        } else {
+#pragma unroll 1
+            for (int qi = tid; qi < nquads; qi += NT) {
+                const int q = (int)s.quads[qi];
+                const int pr = q / L::SW, cc = q - pr * L::SW, r0 = 2 * pr;
+                float v[6 * 6];
+#pragma unroll
+                for (int i = 0; i < 6; ++i)
+#pragma unroll
+                    for (int j = 0; j < 6; ++j)
+                        v[i * 6 + j] = sJ[(r0 + i) * L::JWP + cc + j];
+                float m5[4];
+                med5_t2x2(v, m5);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    constexpr int P = 6;
+                    const int pc = (i + 2) * P + 2;
+                    exact_row(r0 + i, cc, v[pc - P], v[pc + 1 - P], v[pc - 1], v[pc],
+                              v[pc + 1], v[pc + 2], v[pc + P], v[pc + 1 + P], m5[2 * i],
+                              m5[2 * i + 1]);
+                }
             }
         }
         // non-negative floats order as their bit patterns: the device library's
