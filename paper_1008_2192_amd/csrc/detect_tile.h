@@ -193,9 +193,9 @@ __device__ __forceinline__ bool dense_bounds(const float (&v)[6 * 9], const SEst
 
 // S exactly as the definition evaluates it (binary64, in its operation order), at the
 // in-frame pixel whose staged J cell is p (pitch jp; the staged plane holds J at clamped
-// positions, so the cells around p are the clamped 5 x 5 window).
+// positions, so the cells around p are the clamped 5 x 5 window), and the N it is formed with.
 __device__ __forceinline__ double s_exact(const float *p, int jp, double gain, double sky,
-                                          double rn2) {
+                                          double rn2, double &N) {
     float w[25], m5[1];
 #pragma unroll
     for (int i = 0; i < 5; ++i)
@@ -207,16 +207,8 @@ __device__ __forceinline__ double s_exact(const float *p, int jp, double gain, d
     double m = (double)m5[0] + sky;
     if (m <= 0.0)
         m = 1e-4;
-    const double N = sqrt(gain * m + rn2) / gain;
+    N = sqrt(gain * m + rn2) / gain;
     return lp / (2.0 * N);
-}
-
-// N of the definition (binary64) from med5(J).
-__device__ __forceinline__ double noise_exact(float m5, double gain, double sky, double rn2) {
-    double m = (double)m5 + sky;
-    if (m <= 0.0)
-        m = 1e-4;
-    return sqrt(gain * m + rn2) / gain;
 }
 
 // med3(J) at the pixel whose staged J cell is p (pitch jp).  The staged plane holds
@@ -245,26 +237,21 @@ __device__ __forceinline__ const float *med3_cell(const float *sJ, int jp, int y
 }
 
 // The contrast test S'/F^ > objlim in binary64 at tile pixel (r, c), med3 taken from the
-// staged J, F^ = max((med3 - med7(med3)) / N, 0.01).  The test, evaluated in the
-// definition's operations with a value x in place of med7, is monotone in x (every step
-// and every rounding is), and med7 is the 25th of the 49 window values, with 24 on
-// either side; so the test holds at med7 iff it holds at 25 or more of them.
+// staged J, F^ = max((med3 - med7(med3)) / N, 0.01), by the calling wave (all lanes active,
+// arguments uniform).  The test, evaluated in the definition's operations with a value x in
+// place of med7, is monotone in x (every step and every rounding is), and med7 is the 25th of
+// the 49 window values, with 24 on either side; so the test holds at med7 iff it holds at 25 or
+// more of them.  Lane l < 49 takes window cell (l / 7 - 3, l % 7 - 3).
 __device__ __forceinline__ bool contrast_exact(const float *sJ, int jp, int y0, int x0, int H,
                                                int W, int r, int c, double spr, double N,
-                                               double objlim) {
-    const double m3 = (double)med3_at(med3_cell(sJ, jp, y0, x0, H, W, r, c, 0, 0), jp);
-    int n = 0;
-#pragma unroll 1
-    for (int i = 0; i < 7; ++i) {
-#pragma unroll
-        for (int j = 0; j < 7; ++j) {
-            const double x = (double)med3_at(med3_cell(sJ, jp, y0, x0, H, W, r, c, i - 3, j - 3), jp);
-            double fh = (m3 - x) / N;
-            fh = fh < 0.01 ? 0.01 : fh;
-            n += spr / fh > objlim ? 1 : 0;
-        }
-    }
-    return n >= 25;
+                                               double objlim, int lane) {
+    const int l49 = lane < 49 ? lane : 24;
+    const float xf = med3_at(med3_cell(sJ, jp, y0, x0, H, W, r, c, l49 / 7 - 3, l49 % 7 - 3), jp);
+    const double m3 = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(xf), 24));
+    const double x = (double)xf;
+    double fh = (m3 - x) / N;
+    fh = fh < 0.01 ? 0.01 : fh;
+    return __popcll(__ballot(lane < 49 && spr / fh > objlim)) >= 25;
 }
 
 // N at a pixel from its FP32 estimate s = l4 R of S (s_estimate; R = (g/8) rsq(t), and l4
@@ -461,7 +448,7 @@ struct DetectLds : DetectMaps<TY, SPARSE> {
     static constexpr int kListMax = 8 * TY;
     static_assert(AP >= 4 && NW * 64 == NT && QW == 2, "whole waves; two bitmap words per row");
     static_assert(QW + 1 <= HW, "dilation reads two bitmap words per work word");
-    static_assert(kSPlane * 4 >= kExactBatch * 26 * 8, "re-evaluation buffer in the S plane");
+    static_assert(kSPlane * 4 >= kExactBatch * 27 * 8, "re-evaluation buffer in the S plane");
     static_assert((kTileWords + 1) * 4 <= kListMax * 2, "bitmap prefix in the work list");
     static_assert(SH % 2 == 0 && SW % 2 == 0, "whole quads");
     static_assert(SW == 68 && HW == 3 && NTX == 14, "the sizes of DetectMaps");
@@ -1112,8 +1099,12 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
         __syncthreads();
     }
 
-    // binary64 re-evaluation of the undecided pixels from J, kExactBatch per round:
-    // 25 threads compute the S window of a pixel, then one thread its codes
+    // binary64 re-evaluation of the undecided pixels from J, kExactBatch per round: 25 threads
+    // compute the S window of a pixel, then one wave per pixel its codes, a window cell of the
+    // contrast test per lane.  (With that test in one lane, 49 windows and 98 divisions one
+    // after another, a launch over few tiles waited for a tile with such a pixel: the first
+    // iteration of an 800 x 800 frame took 27 us where it takes 22, of a 1033 x 2047 one 28
+    // where it takes 19, the first detection of the mixed batch 1.25 ms where it takes 1.22.)
     const int nunc = (int)s.uncertain;
     if (nunc) {
         // the binary64 parameters (read here, on this rare path only)
@@ -1121,6 +1112,8 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
         const double rn2 = rn * rn, sigclip = f.sigclip, objlim = f.objlim;
         const double lowlim = (double)f.sigfrac * (double)f.sigclip;
         uint32_t *const upre = reinterpret_cast<uint32_t *>(s.list);
+        // medians and N of a round's pixels
+        double *const sMed = sX + kExactBatch * 25, *const sN = sMed + kExactBatch;
         if (tid < 64)
             bitmap_prefix<L::kTileWords>(s.u, upre);
         __syncthreads();
@@ -1133,8 +1126,11 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
                 const int i = cell / 5, j = cell - i * 5;
                 // window cell in frame coordinates, clamped
                 const int gy = clampi(y0 + r + i - 2, H), gx = clampi(x0 + c + j - 2, W);
+                double N;
                 sX[slot * 25 + cell] = s_exact(&sJ[(gy - y0 + 4) * L::JWP + gx - x0 + 4],
-                                               L::JWP, gain, sky, rn2);
+                                               L::JWP, gain, sky, rn2, N);
+                if (cell == 12)
+                    sN[slot] = N;
             }
             __syncthreads();
             // med5 of the window by ranks: the value with at most 12 smaller and at
@@ -1149,28 +1145,23 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
                     le += u <= v ? 1 : 0;
                 }
                 if (lt <= 12 && le >= 13)
-                    sX[kExactBatch * 25 + slot] = v;
+                    sMed[slot] = v;
             }
             __syncthreads();
-            if (tid < kExactBatch && base + tid < nunc) {
-                const int pos = bitmap_select<L::kTileWords>(s.u, upre, base + tid);
+            const int n = min(kExactBatch, nunc - base);
+            for (int it = __builtin_amdgcn_readfirstlane(tid >> 6); it < n; it += L::NW) {
+                const int pos = bitmap_select<L::kTileWords>(s.u, upre, base + it);
                 const int r = pos / TX, c = pos - r * TX;
-                const double spr = sX[tid * 25 + 12] - sX[kExactBatch * 25 + tid];
+                const double spr = sX[it * 25 + 12] - sMed[it];
                 const bool hbit = spr > sigclip, lbit = spr > lowlim;
                 bool first = false;
                 if (hbit) {
-                    float w5[25], m5[1];
-#pragma unroll
-                    for (int i = 0; i < 5; ++i)
-#pragma unroll
-                        for (int j = 0; j < 5; ++j)
-                            w5[i * 5 + j] = sJ[(r + 2 + i) * L::JWP + c + 2 + j];
-                    med5_t1x1(w5, m5);
-                    first = contrast_exact(sJ, L::JWP, y0, x0, H, W, r, c, spr,
-                                           noise_exact(m5[0], gain, sky, rn2), objlim);
-                    ++ncontrast;
+                    first = contrast_exact(sJ, L::JWP, y0, x0, H, W, r, c, spr, sN[it], objlim,
+                                           lane);
+                    ncontrast += lane == 0 ? 1u : 0u;
                 }
-                set_code(s, pos, first, hbit, lbit);
+                if (lane == 0)
+                    set_code(s, pos, first, hbit, lbit);
             }
             __syncthreads();
         }
