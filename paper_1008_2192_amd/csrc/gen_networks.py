@@ -424,6 +424,7 @@ def generate(path: str, verify: bool = True) -> None:
         parts.append(emit_tile_function(name, tm))
         parts.append("")
     parts.append(emit_sort_function("sort25", 25))
+    parts.append(emit_sort_function("sort13", 13))
     parts.append("")
     text = "\n".join(parts)
     tmp = path + ".tmp"

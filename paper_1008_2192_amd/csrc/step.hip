@@ -118,6 +118,60 @@ __device__ __forceinline__ bool window_median(const float *p, int jp, uint32_t f
     return true;
 }
 
+// The same by the lanes of a pair (2 i, 2 i + 1; h: which of them), each with half of the
+// window: rows 0 and 1 and the first three of row 2, or rows 3 and 4 and the last two of row 2.
+// The flagged values take +inf and -inf in turn, so that the middle is that of the 25 whatever
+// their number: value 12, or for an odd number the mean of values 11 and 12.  (A third of row 2
+// that the second lane does not have is a 26th value +inf, behind both.)  Each lane sorts its
+// 13; the n-th smallest of two sorted lists is the least over i of max(a_i, b_{n - i}), the
+// larger of the ends when i are taken from one list and n - i from the other.  nan: the
+// window's unflagged values hold a NaN, whose place the two networks do not agree on.
+__device__ __forceinline__ bool window_median_half(const float *p, int jp, uint32_t fl, int h,
+                                                   float &out, bool &nan) {
+    float v[13], o[13];
+    const float *rows = p + (h ? jp : -2 * jp) - 2, *mid = p + (h ? 1 : -2);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+            v[i * 5 + j] = rows[i * jp + j];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        v[10 + j] = mid[j];
+    uint32_t odd = fl;                   // an odd number of flags up to and with the bit
+#pragma unroll
+    for (int s = 1; s < 32; s *= 2)
+        odd ^= odd << s;
+    const uint32_t neg = fl & ~odd;
+    const uint32_t f = h ? fl >> 15 | (fl >> 13 & 3u) << 10 | 1u << 12 : fl;
+    const uint32_t n = h ? neg >> 15 | (neg >> 13 & 3u) << 10 : neg;
+    uint32_t top = 0u;
+#pragma unroll
+    for (int i = 0; i < 13; ++i) {
+        const uint32_t inf = (n << (31 - i) & 0x80000000u) | 0x7f800000u;
+        const uint32_t m = (uint32_t)((int32_t)(f << (31 - i)) >> 31);
+        const uint32_t b = (m & inf) | (~m & __float_as_uint(v[i]));
+        top = max(top, b & 0x7fffffffu);
+        v[i] = __uint_as_float(b);
+    }
+    sort13(v);
+    top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0xB1, 0xf, 0xf, false));
+    nan = top > 0x7f800000u;
+#pragma unroll
+    for (int i = 0; i < 13; ++i)         // the other lane's
+        o[i] = __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v[i]), 0xB1,
+                                                                  0xf, 0xf, false));
+    float a = fminf(v[11], o[11]), b = fminf(v[12], o[12]);
+#pragma unroll
+    for (int i = 1; i < 12; ++i)
+        a = fminf(a, fmaxf(v[i - 1], o[11 - i]));
+#pragma unroll
+    for (int i = 1; i < 13; ++i)
+        b = fminf(b, fmaxf(v[i - 1], o[12 - i]));
+    out = __popc(fl) & 1 ? (float)(((double)a + (double)b) * 0.5) : b;
+    return fl != 0x1FFFFFFu;
+}
+
 // Appends tile g to the list of iteration k.
 __device__ __forceinline__ void list_tile(const StepLists &l, int k, int g) {
     const int seg = g & (l.nseg - 1);
@@ -268,8 +322,11 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
     // place), and meanwhile, by the other waves, the list of the 2 x 5 cell tiles of S that a
     // re-evaluated code reads
     const bool listed = nrep <= kRepMax;
-    for (int i = tid; i < (listed ? nrep : 48 * 80); i += L::NT) {
-        const int pos = listed ? (int)rep[i] : i;
+    // (up to NT / 2 of them by pairs of lanes: 240 instructions where one lane takes 430, and most
+    // tiles leave half of the lanes idle; the first iteration of the mixed batch 1.11 -> 1.08 ms)
+    const bool pairs = nrep <= L::NT / 2;
+    for (int i = tid; i < (pairs ? 2 * nrep : (listed ? nrep : 48 * 80)); i += L::NT) {
+        const int pos = pairs ? (int)rep[i >> 1] : (listed ? (int)rep[i] : i);
         const int r = pos / 80, c = pos - r * 80;
         if (!listed && !(sh.r[r][c >> 5] >> (c & 31) & 1u))
             continue;
@@ -283,7 +340,15 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
         const int jr = r - 2, jc = c - 2;
         float nv;
         const bool mine = r >= 8 && r < 40 && c >= 8 && c < 72;
-        if (window_median(&s.J[jr * L::JWP + jc], L::JWP, fl, nv)) {
+        const float *const pj = &s.J[jr * L::JWP + jc];
+        bool some, nan = !pairs;
+        if (pairs)
+            some = window_median_half(pj, L::JWP, fl, tid & 1, nv, nan);
+        if (nan)
+            some = window_median(pj, L::JWP, fl, nv);
+        if (pairs && (tid & 1))
+            continue;
+        if (some) {
             s.J[jr * L::JWP + jc] = nv;
             // the staged cells past the frame's edges that repeat this pixel
             if (y == 0 || y == H - 1 || x == 0 || x == W - 1) {
