@@ -784,9 +784,9 @@ __device__ __forceinline__ void detect_staged(DetectLds<TY, AP, SPARSE> &s, cons
         // takes as long as a full one.  Up to NT / 4 quads: four lanes per quad, a cell each (the
         // 1 x 1 network).  Up to NT / 2: two lanes per quad, a row each (the 1 x 2 network and
         // two estimates, about 60% of a quad's instructions).  Else one quad per lane (the 2 x 2
-        // network).  (With one quad per lane down to 32 of them the re-evaluation of a crowded
-        // 4096 x 4096 field's listed tiles took 95 and 50 us where it takes 89 and 46, that of
-        // the mixed batch 236 where it takes 215, and the first detection the same to 1%.)
+        // network).  (With one quad per lane down to 32 of them the listed iterations of a
+        // crowded 4096 x 4096 field took 95 and 50 us against 89 and 46, the first of the mixed
+        // batch 236 us against 215, and the first detection the same to 1%.)
         if (nquads <= NT / 4) {
             if (tid < 4 * nquads) {
                 const int q = (int)s.quads[tid >> 2];

@@ -11,13 +11,15 @@
 // of the tile, from J staged within 6; the codes of the tile's pixels within 4 of those.
 //
 // Measured on one MI355X, four iterations: the mixed batch (64 frames, 295 Mpx) 4.48 -> 3.06
-// ms, a 256 x 256 frame 84 -> 51 us, 61 x 67 68 -> 32 us, a 4096 x 4096 crowded field 0.43 ->
-// 0.38 ms, against three or four launches an iteration that each passed over the frame
-// (detection of every pixel, grow over code bytes, flagged list, replacement by gathers).
-// A tile is bound by the latency of its chain (waves wait 71% of their cycles, VALU issue is
+// ms when this kernel came (2.60 now), a 256 x 256 frame 84 -> 51 us (42 now), 61 x 67 68 -> 32
+// us (25 now), a 4096 x 4096 crowded field 0.43 -> 0.38 ms (0.33 now), against three or four
+// launches an iteration that each passed over the frame (detection of every pixel, grow over
+// code bytes, flagged list, replacement by gathers).  A single tile is bound by the latency of
+// its chain, many of them by that and by issue (waves wait 71% of their cycles, VALU issue is
 // at half its rate): with J's loads in flight during the grow, rows in 32-bit words and no
 // pass over the staged cells past the frame's edges, the first iteration of the batch took
-// 1.48 -> 1.11 ms; the second, on the listed tiles, takes 0.24 ms.
+// 1.48 -> 1.11 ms, and with pairs of lanes for a replacement 1.08; the second, on the listed
+// tiles, takes 0.20 ms.
 //
 // Blocks share their halos without ordering.  Codes are double-buffered per tile.  The mask
 // bitmap of a neighbour may be read before or after its owner ORs G2 into it: the reader ORs
