@@ -1058,30 +1058,20 @@ static PlanLayout plan_layout(const crb_frame *frames, int32_t n) {
     return L;
 }
 
-// A plan on `mem` (layout.bytes bytes that outlive it), or on memory of its own (mem null).
-// On memory of its own the tables have been written on return; else they are on the stream.
-static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stream,
-                            bool use_graph, char *mem, crb_plan **out_plan) {
-    crb_status st;
-    size_t all_pix = 0, max_pix = 0, init_pix = 0;
-    int kmax = 0;
+// The frames of a plan or a batched call, before any memory is taken for them.
+static crb_status plan_check(const crb_frame *frames, int32_t n) {
+    size_t ntiles = 0;
     for (int i = 0; i < n; ++i) {
         const crb_frame &f = frames[i];
-        st = check_frame_args(f.H, f.W, f.gain, f.readnoise, f.sky, f.sigclip, f.sigfrac,
-                              f.objlim, f.niter);
+        crb_status st = check_frame_args(f.H, f.W, f.gain, f.readnoise, f.sky, f.sigclip,
+                                         f.sigfrac, f.objlim, f.niter);
+        if (st == CRB_OK)
+            st = check_buffers(f.img, f.out_clean, f.out_mask, (size_t)f.H * (size_t)f.W);
         if (st != CRB_OK)
             return fail(st, "frame %d: %s", i, crb_last_error());
-        const size_t npix = (size_t)f.H * (size_t)f.W;
-        if ((st = check_buffers(f.img, f.out_clean, f.out_mask, npix)) != CRB_OK)
-            return fail(st, "frame %d: %s", i, crb_last_error());
-        max_pix = npix > max_pix ? npix : max_pix;
-        if (f.niter == 0)      // the init kernel copies these frames
-            init_pix = npix > init_pix ? npix : init_pix;
-        all_pix += npix;
-        kmax = f.niter > kmax ? f.niter : kmax;
+        ntiles += (size_t)detect_tiles(f.H, f.W, kTileHeights[0]);
     }
-    const PlanLayout L = plan_layout(frames, n);
-    if (L.ntiles[0] > (size_t)INT32_MAX)
+    if (ntiles > (size_t)INT32_MAX)
         return fail(CRB_ETOOBIG, "batch too large");
     // also guard against buffers shared between frames
     for (int i = 0; i < n; ++i)
@@ -1093,6 +1083,26 @@ static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stre
                 ranges_overlap(frames[j].out_clean, nj * 4, frames[i].img, ni * 4))
                 return fail(CRB_EINVAL, "frames %d and %d share output memory", i, j);
         }
+    return CRB_OK;
+}
+
+// A plan of checked frames on `mem` (layout.bytes bytes that outlive it), or on memory of its
+// own (mem null).  On memory of its own the tables have been written on return; else they are on
+// the stream.
+static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stream,
+                            bool use_graph, char *mem, crb_plan **out_plan) {
+    crb_status st;
+    size_t all_pix = 0, max_pix = 0, init_pix = 0;
+    int kmax = 0;
+    for (int i = 0; i < n; ++i) {
+        const size_t npix = (size_t)frames[i].H * (size_t)frames[i].W;
+        max_pix = npix > max_pix ? npix : max_pix;
+        if (frames[i].niter == 0)      // the init kernel copies these frames
+            init_pix = npix > init_pix ? npix : init_pix;
+        all_pix += npix;
+        kmax = frames[i].niter > kmax ? frames[i].niter : kmax;
+    }
+    const PlanLayout L = plan_layout(frames, n);
     crb_plan *p = new (std::nothrow) crb_plan();
     if (!p)
         return fail(CRB_ENOMEM, "host allocation failed");
@@ -1237,7 +1247,10 @@ crb_status crb_plan_create(const crb_frame *frames, int32_t n, void *hip_stream,
     *out_plan = nullptr;
     if (!frames || n < 1)
         return fail(CRB_EINVAL, "need at least one frame");
-    return plan_make(frames, n, (hipStream_t)hip_stream, use_graph != 0, nullptr, out_plan);
+    const crb_status st = plan_check(frames, n);
+    return st != CRB_OK
+               ? st
+               : plan_make(frames, n, (hipStream_t)hip_stream, use_graph != 0, nullptr, out_plan);
 }
 
 crb_status crb_plan_run(crb_plan *p) {
@@ -1444,18 +1457,12 @@ crb_status crb_plan_kernel_times(crb_plan *p, double *ms, int64_t *launches) {
 crb_status crb_lacosmic_batched(crb_frame *frames, int32_t n, void *hip_stream) {
     if (!frames || n < 1)
         return fail(CRB_EINVAL, "need at least one frame");
-    for (int i = 0; i < n; ++i) {        // (the sizes, before anything is measured by them)
-        const crb_status st = check_frame_args(frames[i].H, frames[i].W, frames[i].gain,
-                                               frames[i].readnoise, frames[i].sky,
-                                               frames[i].sigclip, frames[i].sigfrac,
-                                               frames[i].objlim, frames[i].niter);
-        if (st != CRB_OK)
-            return fail(st, "frame %d: %s", i, crb_last_error());
-    }
+    crb_status st = plan_check(frames, n);
+    if (st != CRB_OK)
+        return st;
     hipStream_t s = (hipStream_t)hip_stream;
     CallMemory mem;
-    crb_status st = mem.reserve(s, plan_layout(frames, n).bytes);
-    if (st != CRB_OK)
+    if ((st = mem.reserve(s, plan_layout(frames, n).bytes)) != CRB_OK)
         return st;
     crb_plan *p = nullptr;
     if ((st = plan_make(frames, n, s, false, mem.mem, &p)) != CRB_OK)
@@ -1547,6 +1554,8 @@ extern "C" crb_status crb_lacosmic_partitioned(const float *img, int32_t H, int3
         frames[q].out_clean = r.sub_clean;
         frames[q].out_mask = r.sub_mask;
     }
+    if ((st = plan_check(frames.data(), nsub)) != CRB_OK)
+        return st;
     SubRect *d_subs = reinterpret_cast<SubRect *>(mem.mem + o_tab);
     crb_plan *plan = nullptr;
     // everything on the launch stream, which is waited for before `subs`, the plan's host
