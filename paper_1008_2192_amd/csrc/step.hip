@@ -417,24 +417,27 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
     }
 }
 
-// The (frame, tile) g of a launch.
-__device__ __forceinline__ void step_one(const DevFrame *__restrict__ frames,
-                                         const TileRef *__restrict__ tiles,
-                                         const DevFrame &single, int g, int kiter, bool by_mark,
-                                         const StepLists &lists, StepShared &sh, int tid) {
-    DevFrame f;
-    int ty, tx;
+// Tile g of a launch, and its frame in the table (-1: the launch's single one).  The kernels copy
+// the frame's record themselves, in scalar registers: with the copy inside a function that then
+// runs the tile, the compiler held 95 vector registers where it now holds 87, and 11 more
+// dwords in scratch in the listed form (first iterations of the mixed batch 1083 and 206 us
+// against 910 and 162, of the 4096 x 4096 field 97 and 87 against 88 and 77; read in place 957
+// and 170, 91 and 81).
+__device__ __forceinline__ int step_place(const TileRef *__restrict__ tiles, const DevFrame &single,
+                                          int g, int &ty, int &tx) {
     if (tiles) {
         const TileRef r = tiles[g];
-        f = frames[r.frame];
         ty = r.y0 / kSumTY;
         tx = r.x0 / kSumTX;
-    } else {
-        f = single;
-        const int ntx = (single.W + kSumTX - 1) / kSumTX;
-        ty = g / ntx;
-        tx = g - ty * ntx;
+        return r.frame;
     }
+    const int ntx = (single.W + kSumTX - 1) / kSumTX;
+    ty = g / ntx;
+    tx = g - ty * ntx;
+    return -1;
+}
+__device__ __forceinline__ void step_one(const DevFrame &f, int ty, int tx, int kiter, bool by_mark,
+                                         const StepLists &lists, StepShared &sh, int tid) {
     const int k = kiter ? kiter : f.k;
     if (k > f.niter)
         return;
@@ -463,7 +466,14 @@ void k_step(const DevFrame *__restrict__ frames, const TileRef *__restrict__ til
             for (int i = tid; i < kTicketWords; i += 256)
                 tickets[i] = 0u;
     }
-    step_one(frames, tiles, single, (int)blockIdx.x, kiter, true, lists, sh, tid);
+    int ty, tx;
+    DevFrame f;
+    const int fi = step_place(tiles, single, (int)blockIdx.x, ty, tx);
+    if (tiles)
+        f = frames[fi];
+    else
+        f = single;
+    step_one(f, ty, tx, kiter, true, lists, sh, tid);
 }
 
 // The tiles of a list: block b takes entries b / nseg, b / nseg + stride, ... of segment
@@ -483,7 +493,14 @@ void k_step_listed(const DevFrame *__restrict__ frames, const TileRef *__restric
         asm volatile("" : "+v"(tid));
         // (uniform: the tile and frame records then load into scalar registers)
         const int g = __builtin_amdgcn_readfirstlane((int)list[e]);
-        step_one(frames, tiles, single, g, kiter, false, lists, sh, tid);
+        int ty, tx;
+        DevFrame f;
+        const int fi = step_place(tiles, single, g, ty, tx);
+        if (tiles)
+            f = frames[fi];
+        else
+            f = single;
+        step_one(f, ty, tx, kiter, false, lists, sh, tid);
         __syncthreads();       // the tile is done with the LDS
     }
 }
