@@ -11,15 +11,15 @@
 // of the tile, from J staged within 6; the codes of the tile's pixels within 4 of those.
 //
 // Measured on one MI355X, four iterations: the mixed batch (64 frames, 295 Mpx) 4.48 -> 3.06
-// ms when this kernel came (2.60 now), a 256 x 256 frame 84 -> 51 us (42 now), 61 x 67 68 -> 32
-// us (25 now), a 4096 x 4096 crowded field 0.43 -> 0.38 ms (0.33 now), against three or four
+// ms when this kernel came (2.35 now), a 256 x 256 frame 84 -> 51 us (39 now), 61 x 67 68 -> 32
+// us (24 now), a 4096 x 4096 crowded field 0.43 -> 0.38 ms (0.30 now), against three or four
 // launches an iteration that each passed over the frame (detection of every pixel, grow over
 // code bytes, flagged list, replacement by gathers).  A single tile is bound by the latency of
-// its chain, many of them by that and by issue (waves wait 71% of their cycles, VALU issue is
-// at half its rate): with J's loads in flight during the grow, rows in 32-bit words and no
+// its chain, many of them by that and by issue (waves wait 72% of their cycles, VALU issue is
+// at 43% of its rate): with J's loads in flight during the grow, rows in 32-bit words and no
 // pass over the staged cells past the frame's edges, the first iteration of the batch took
-// 1.48 -> 1.11 ms, and with pairs of lanes for a replacement 1.08; the second, on the listed
-// tiles, takes 0.20 ms.
+// 1.48 -> 1.11 ms, with pairs of lanes for a replacement 1.08 and with fewer registers 0.91; the
+// second, on the listed tiles, takes 0.16 ms.
 //
 // Blocks share their halos without ordering.  Codes are double-buffered per tile.  The mask
 // bitmap of a neighbour may be read before or after its owner ORs G2 into it: the reader ORs
@@ -419,8 +419,8 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
 
 // Tile g of a launch, and its frame in the table (-1: the launch's single one).  The kernels copy
 // the frame's record themselves, in scalar registers: with the copy inside a function that then
-// runs the tile, the compiler held 95 vector registers where it now holds 87, and 11 more
-// dwords in scratch in the listed form (first iterations of the mixed batch 1083 and 206 us
+// runs the tile, the compiler held 95 vector registers where it now holds 87, 11 more dwords in
+// scratch in the listed form, and issued 61 vector instructions a pixel for 47 (first iterations of the mixed batch 1083 and 206 us
 // against 910 and 162, of the 4096 x 4096 field 97 and 87 against 88 and 77; read in place 957
 // and 170, 91 and 81).
 __device__ __forceinline__ int step_place(const TileRef *__restrict__ tiles, const DevFrame &single,
