@@ -17,6 +17,7 @@
 
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -303,8 +304,14 @@ constexpr int kAdmitPerPoll = 4;
 
 static crb_status admit(crb_server *s) {
     // a cap on staged admissions only: direct transfers cost the host nothing
-    for (int staged = 0; !s->waiting.empty() && staged < kAdmitPerPoll;) {
-        Request *r = s->waiting.front();
+    for (int staged = 0; staged < kAdmitPerPoll;) {
+        // (a request with niter == 0 has its results since submit and waits to be reported: a
+        // round has nothing to run for it and would not clear its mask)
+        const auto next = std::find_if(s->waiting.begin(), s->waiting.end(),
+                                       [](const Request *q) { return q->niter > 0; });
+        if (next == s->waiting.end())
+            return CRB_OK;
+        Request *r = *next;
         const int held = (int)(s->active.size() + s->draining.size());
         if (held >= s->max_slots || s->in_use + r->dev_bytes > s->budget)
             return CRB_OK;
@@ -353,7 +360,7 @@ static crb_status admit(crb_server *s) {
         r->need_wait = !r->in_buffers;
         r->k_next = 1;
         r->state = kActive;
-        s->waiting.pop_front();
+        s->waiting.erase(next);
         s->active.push_back(r);
     }
     return CRB_OK;
