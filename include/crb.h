@@ -381,9 +381,11 @@ crb_status crb_release_workspace(void *hip_stream);
  *     outputs are all host memory or all device memory of the server's device
  *     (CRB_EINVAL otherwise).  Device requests are cleaned in the caller's buffers (the
  *     outputs change from admission on; the caller makes the input ready before
- *     submitting, e.g. by synchronizing its stream), or copied in and out where those
- *     overlap each other or another request's, or the calling thread's stream
- *     (crb_set_stream) has unfinished work at submit;
+ *     submitting, e.g. by synchronizing its stream).  They are copied in at admission and
+ *     out at completion where their buffers overlap (in place included), where a buffer
+ *     that one request writes is also another's, and where the calling thread's stream
+ *     (crb_set_stream) has unfinished work at submit; a request that shares a buffer with
+ *     one already being cleaned there is admitted once that one has finished;
  *     page-locked host buffers (hipHostMalloc) are transferred directly; pageable ones
  *     pass through the server's pinned staging buffers.
  *   crb_server_poll: enqueue the next round when the previous one has finished,

@@ -18,6 +18,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -126,6 +127,9 @@ struct Request {
     bool on_device = false;            // caller's buffers are device memory
     bool idle = false;                 // the caller's stream was idle at submit
     bool in_buffers = false;           // cleaned in the caller's device buffers, no copies
+    bool copied = false;               // niter 0: the result is written
+    bool shared = false;               // a buffer that it or another request writes is also
+                                       // that other's (device requests)
     size_t alloc_bytes = 0;            // device memory taken from the server
     float *host_clean = nullptr;
     uint8_t *host_mask = nullptr;
@@ -141,6 +145,14 @@ struct Request {
     bool need_wait = false;            // next round must wait for ev_h2d
 };
 
+// A device buffer of a request in the server, kept by its first byte.
+struct Span {
+    uintptr_t end;
+    Request *r;
+    bool output;
+};
+using Spans = std::multimap<uintptr_t, Span>;
+
 }  // namespace crb
 
 using namespace crb;
@@ -154,6 +166,8 @@ struct crb_server {
     std::deque<Request *> waiting;
     std::vector<Request *> active;     // admitted, state kActive
     std::vector<Request *> draining;   // results being copied back
+    Spans spans;                       // device buffers of the requests not yet reported
+    size_t longest = 0;                // the largest of them so far
     // round in flight
     bool round_busy = false;
     std::vector<Request *> round_members;
@@ -248,7 +262,11 @@ static size_t frame_dev_bytes(int32_t H, int32_t W) {
     return img + msk + ws_layout(H, W).total;
 }
 
+static void leave_spans(crb_server *s, const Request *r);
+
 static void release_request(crb_server *s, Request *r) {
+    if (r->on_device)
+        leave_spans(s, r);
     if (r->dev) {
         s->dev_free.emplace(r->alloc_bytes, r->dev);
         s->in_use -= r->dev_bytes;
@@ -268,33 +286,111 @@ static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
     return pa < pb + nb && pb < pa + na;
 }
 
-// Whether a device request can be cleaned in the caller's own buffers: they must not overlap
-// (in place is fine), no other request in the server may share a buffer that either writes,
-// and no work that the caller's stream still held at submit may use the outputs' memory (an
-// allocator hands a block on as soon as work on its former tensor is enqueued).  Otherwise the
-// request is copied in and out, its outputs written at completion.
-static bool clean_in_buffers(const crb_server *s, const Request *r) {
-    if (!r->on_device || !r->idle)
+struct Buffer {
+    const void *p;
+    size_t bytes;
+    bool output;
+};
+static std::array<Buffer, 3> buffers(const Request *r) {
+    const size_t n = (size_t)r->H * (size_t)r->W;
+    return {{{r->host_img, 4 * n, false}, {r->host_clean, 4 * n, true}, {r->host_mask, n, true}}};
+}
+// Whether an output of q overlaps a buffer of r.
+static bool writes_into(const Request *q, const Request *r) {
+    for (const Buffer &a : buffers(q))
+        for (const Buffer &b : buffers(r))
+            if (a.output && overlap(a.p, a.bytes, b.p, b.bytes))
+                return true;
+    return false;
+}
+
+// Enters a device request's buffers, and marks it and the requests still waiting where one
+// writes what is also the other's.
+static void enter_spans(crb_server *s, Request *r) {
+    for (const Buffer &b : buffers(r)) {
+        const uintptr_t p = (uintptr_t)b.p, e = p + b.bytes;
+        for (auto it = s->spans.lower_bound(p > s->longest ? p - s->longest : 0);
+             it != s->spans.end() && it->first < e; ++it)
+            if (it->second.end > p && it->second.r != r && (b.output || it->second.output))
+                r->shared = it->second.r->shared = true;
+    }
+    for (const Buffer &b : buffers(r)) {
+        s->spans.emplace((uintptr_t)b.p, Span{(uintptr_t)b.p + b.bytes, r, b.output});
+        s->longest = std::max(s->longest, b.bytes);
+    }
+}
+static void leave_spans(crb_server *s, const Request *r) {
+    for (const Buffer &b : buffers(r)) {
+        const auto range = s->spans.equal_range((uintptr_t)b.p);
+        for (auto it = range.first; it != range.second;)
+            it = it->second.r == r ? s->spans.erase(it) : std::next(it);
+    }
+}
+
+// Whether a device request can be cleaned in the caller's own buffers, its outputs written from
+// its first round on: no buffer may overlap another (a request in place would leave neither its
+// input nor its result behind if the server were destroyed), no other request in the server may
+// share a buffer that either writes, and no work that the caller's stream still held at submit
+// may use the outputs' memory (an allocator hands a block on as soon as work on its former
+// tensor is enqueued).  Otherwise the request is copied in at admission and out at completion.
+static bool clean_in_buffers(const Request *r) {
+    if (!r->on_device || !r->idle || r->shared)
         return false;
     const size_t n = (size_t)r->H * (size_t)r->W;
-    if ((r->host_img != r->host_clean && overlap(r->host_img, 4 * n, r->host_clean, 4 * n)) ||
-        overlap(r->host_mask, n, r->host_img, 4 * n) ||
-        overlap(r->host_mask, n, r->host_clean, 4 * n))
+    return !overlap(r->host_img, 4 * n, r->host_clean, 4 * n) &&
+           !overlap(r->host_mask, n, r->host_img, 4 * n) &&
+           !overlap(r->host_mask, n, r->host_clean, 4 * n);
+}
+
+// Whether r has to wait for a request before it that is being cleaned in buffers which r reads
+// or writes too (r was submitted after that one's admission, so neither knew of the other), or
+// for a niter 0 copy that does the same.
+static bool must_wait(const crb_server *s, const Request *r) {
+    if (!r->shared)
         return false;
-    for (const std::vector<Request *> *v : {&s->active, &s->draining})
-        for (const Request *q : *v) {
-            const size_t m = (size_t)q->H * (size_t)q->W;
-            const struct { const void *p; size_t b; } mine[3] = {
-                {r->host_clean, 4 * n}, {r->host_mask, n}, {r->host_img, 4 * n}};
-            const struct { const void *p; size_t b; } theirs[3] = {
-                {q->host_clean, 4 * m}, {q->host_mask, m}, {q->host_img, 4 * m}};
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j)
-                    if ((i < 2 || j < 2) &&      // (both may read one image)
-                        overlap(mine[i].p, mine[i].b, theirs[j].p, theirs[j].b))
-                        return false;
+    for (const Request *q : s->active)
+        if (q->in_buffers && (writes_into(q, r) || (r->niter == 0 && writes_into(r, q))))
+            return true;
+    for (const Request *q : s->waiting) {
+        if (q == r)
+            break;
+        if (q->niter == 0 && !q->copied && (writes_into(q, r) || writes_into(r, q)))
+            return true;
+    }
+    return false;
+}
+
+// The result of a device request with niter == 0, on the copy stream.
+static hipError_t copy_niter0(crb_server *s, const Request *r) {
+    const size_t n = (size_t)r->H * (size_t)r->W;
+    hipError_t e = hipMemcpyAsync(r->host_clean, r->host_img, 4 * n, hipMemcpyDeviceToDevice,
+                                  s->copy);
+    if (e == hipSuccess)
+        e = hipMemsetAsync(r->host_mask, 0, n, s->copy);
+    return e;
+}
+// Enqueues those that had to wait at submit and need not any more.
+static crb_status start_niter0(crb_server *s) {
+    for (auto it = s->waiting.begin(); it != s->waiting.end();) {
+        Request *r = *it;
+        if (r->niter > 0 || r->copied || must_wait(s, r)) {
+            ++it;
+            continue;
         }
-    return true;
+        crb_status st = get_event(s, &r->ev_d2h);
+        if (st != CRB_OK)
+            return st;
+        hipError_t e = copy_niter0(s, r);
+        if (e == hipSuccess)
+            e = hipEventRecord(r->ev_d2h, s->copy);
+        if (e != hipSuccess)
+            return hip_status(e, "niter 0 copy");
+        r->copied = true;
+        r->state = kDraining;
+        s->draining.push_back(r);
+        it = s->waiting.erase(it);
+    }
+    return CRB_OK;
 }
 
 // Admit waiting requests (FIFO) while slots and budget allow, at most a few per
@@ -313,13 +409,13 @@ static crb_status admit(crb_server *s) {
             return CRB_OK;
         Request *r = *next;
         const int held = (int)(s->active.size() + s->draining.size());
-        if (held >= s->max_slots || s->in_use + r->dev_bytes > s->budget)
+        if (held >= s->max_slots || s->in_use + r->dev_bytes > s->budget || must_wait(s, r))
             return CRB_OK;
         const size_t n = (size_t)r->H * (size_t)r->W;
         const size_t img = (4 * n + 255) / 256 * 256;
         const size_t msk = (n + 255) / 256 * 256;
         const FrameWs L = ws_layout(r->H, r->W);
-        r->in_buffers = clean_in_buffers(s, r);
+        r->in_buffers = clean_in_buffers(r);
         r->alloc_bytes = r->in_buffers ? L.lists : r->dev_bytes;
         char *dev = nullptr;
         crb_status st = dev_alloc(s, r->alloc_bytes, &dev);
@@ -650,21 +746,26 @@ crb_status crb_server_submit(crb_server *s, const float *host_img, int32_t H, in
                   cap == hipStreamCaptureStatusNone && hipStreamQuery(ts) == hipSuccess;
         (void)hipGetLastError();
     }
+    if (r->on_device)
+        enter_spans(s, r);
     if (niter == 0 && r->on_device) {
-        // nothing to compute: the result is the input, copied on the device
-        hipError_t e = hipMemcpyAsync(host_clean, host_img, 4 * npx, hipMemcpyDeviceToDevice,
-                                      s->copy);
-        if (e == hipSuccess)
-            e = hipMemsetAsync(host_mask, 0, npx, s->copy);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(s->copy);
-        if (e != hipSuccess) {
-            delete r;
-            return hip_status(e, "niter 0 copy");
+        // nothing to compute: the result is the input, copied on the device (at once, unless
+        // a request in the server is being cleaned in one of these buffers)
+        if (!must_wait(s, r)) {
+            hipError_t e = copy_niter0(s, r);
+            if (e == hipSuccess)
+                e = hipStreamSynchronize(s->copy);
+            if (e != hipSuccess) {
+                leave_spans(s, r);
+                delete r;
+                return hip_status(e, "niter 0 copy");
+            }
+            r->copied = true;
         }
     } else if (niter == 0) {       // nothing to compute: the result is the input
         memcpy(host_clean, host_img, 4 * npx);
         memset(host_mask, 0, npx);
+        r->copied = true;
     }
     r->id = s->next_id++;
     *out_id = r->id;
@@ -681,7 +782,7 @@ crb_status crb_server_poll(crb_server *s, int64_t *done_ids, double *done_latenc
     // requests with niter == 0 complete at once
     for (auto it = s->waiting.begin(); it != s->waiting.end();) {
         Request *r = *it;
-        if (r->niter == 0 && *n_done < max_done) {
+        if (r->copied && *n_done < max_done) {
             done_ids[*n_done] = r->id;
             done_latency[*n_done] = now_s() - r->t_submit;
             ++*n_done;
@@ -703,7 +804,7 @@ crb_status crb_server_poll(crb_server *s, int64_t *done_ids, double *done_latenc
         }
         if (q != hipSuccess)
             return hip_status(q, "round event");
-        if ((st = finish_round(s)) != CRB_OK ||
+        if ((st = finish_round(s)) != CRB_OK || (st = start_niter0(s)) != CRB_OK ||
             (st = collect(s, done_ids, done_latency, max_done, n_done)) != CRB_OK)
             return st;
     }
