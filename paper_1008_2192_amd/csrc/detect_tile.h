@@ -456,10 +456,11 @@ struct DetectLds : DetectMaps<TY, SPARSE> {
     __align__(16) float J[JH * JWP];            // J at clamped positions
     // S; after the work set, med3 near the contrast pixels; then the re-evaluation buffer
     __align__(16) float S[kSPlane];
+    // (these two are also read as 64-bit rows)
     __align__(8) uint32_t code[3 * kTileWords]; // code planes A, [S' > sigclip], [S' > low]
+    __align__(8) uint32_t con_map[kTileWords];  // pixels listed for the contrast phase
     uint32_t hotp[HR * HWP + 1];                // H', apron 2, in-frame
     uint32_t u[kTileWords];                     // pixels left to binary64
-    uint32_t con_map[kTileWords];               // pixels listed for the contrast phase
     // tile cells where S may exceed sigfrac*sigclip; after the work-set build, Q' itself
     uint32_t low[kTileWords];
     unsigned int err_bits, contrast, uncertain, qcount, need, exact_cells, con_count, any_hot;
