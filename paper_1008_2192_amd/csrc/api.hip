@@ -88,19 +88,28 @@ crb_status check_buffers(const float *img, const float *clean, const uint8_t *ma
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-FrameWs ws_layout(int32_t H, int32_t W) {
-    const size_t n = (size_t)H * (size_t)W;
-    const size_t ntiles = (size_t)((H + kSumTY - 1) / kSumTY) *
-                          (size_t)((W + kSumTX - 1) / kSumTX);
+// The pieces of a frame whose bit rows are stored as `narrow` says (DevFrame).
+static FrameWs ws_pieces(size_t ntiles, int narrow, int nseg) {
+    const size_t plane = narrow == 0 ? kSumTY * 8
+                                     : (narrow < 0 ? (size_t)-narrow * 8 : (size_t)narrow * 4);
     FrameWs L;
+    L.narrow = narrow;
+    L.nseg = nseg;
     L.bits = 0;
-    L.mbits = align_up(L.bits + ntiles * (2 * 3 * kSumTY * 8), 256);
-    L.state = align_up(L.mbits + ntiles * (kSumTY * 8), 256);
+    L.mbits = align_up(L.bits + ntiles * 2 * 3 * plane, 256);
+    L.state = align_up(L.mbits + ntiles * plane, 256);
     L.mark = align_up(L.state + 4 * ntiles, 256);
     L.count = align_up(L.mark + 4 * ntiles, 256);
     L.any_new = align_up(L.count + 8 * (size_t)kCountSlots * kCountStride, 256);
     L.lists = align_up(L.any_new + 4 * (size_t)kMaxIter, 256);
-    const size_t end = align_up(L.lists + 4 * list_words(ntiles), 256);
+    L.total = align_up(L.lists + 4 * list_words(ntiles, nseg), 256);
+    return L;
+}
+
+FrameWs ws_layout(int32_t H, int32_t W) {
+    const size_t n = (size_t)H * (size_t)W;
+    const size_t ntiles = (size_t)((H + kSumTY - 1) / kSumTY) *
+                          (size_t)((W + kSumTX - 1) / kSumTX);
     // Callers size budgets and refuse frames by the reported size, which stays what it was
     // when a frame's workspace held a code byte and a 4-byte list entry per pixel (about
     // five times what is used now): what fits a budget or the fixed scratch does not change.
@@ -108,7 +117,17 @@ FrameWs ws_layout(int32_t H, int32_t W) {
                             align_up(8 * (size_t)kMaxIter, 256) +
                             align_up(4 * (size_t)kMaxIter, 256) + align_up(ntiles, 256) +
                             2 * align_up(4 * ntiles, 256);
-    L.total = end > reported ? end : reported;
+    FrameWs L = ws_pieces(ntiles, 0, list_segments(ntiles));
+    if (L.total > reported) {
+        // Whole planes of 32 rows of 64 bits (1,800 bytes a tile with the rest) exceed it for
+        // frames at most 13 pixels wide or 6 high: these store the columns or rows they have,
+        // with a list segment per four tiles.
+        int p = 1;
+        while (p < 16 && p < W)
+            p *= 2;
+        L = ws_pieces(ntiles, W <= 16 ? p : -H, list_segments(ntiles / 4));
+    }
+    L.total = L.total > reported ? L.total : reported;
     return L;
 }
 
@@ -128,6 +147,7 @@ DevFrame make_devframe(const float *img, float *J, uint8_t *mask, char *ws, cons
         f.mark = reinterpret_cast<unsigned int *>(ws + L.mark);
         f.count = reinterpret_cast<unsigned long long *>(ws + L.count);
         f.any_new = reinterpret_cast<unsigned int *>(ws + L.any_new);
+        f.narrow = L.narrow;
     }
     f.H = H;
     f.W = W;
@@ -226,19 +246,21 @@ static LaunchCfg single_cfg() {
 
 // the lists of a frame run by itself on workspace ws
 static StepLists frame_lists(char *ws, const FrameWs &L, int32_t H, int32_t W) {
-    return make_lists(ws + L.lists, (size_t)detect_tiles(H, W, kSumTY));
+    return make_lists(ws + L.lists, (size_t)detect_tiles(H, W, kSumTY), L.nseg);
 }
 
 // enqueue niter iterations for one frame whose DevFrame is complete
-static crb_status enqueue_single(const DevFrame &f, const LaunchCfg &cfg, const StepLists &lists,
+static crb_status enqueue_single(const DevFrame &f, const LaunchCfg &c, const StepLists &lists,
                                  hipStream_t s) {
     hipError_t e = hipSuccess;
+    const bool narrow = f.narrow != 0;
+    const LaunchCfg cfg = narrow ? LaunchCfg() : c;
     if (f.niter == 0)
         e = launch_init(nullptr, 1, f, (size_t)f.H * (size_t)f.W, s);
     else
-        e = launch_detect(nullptr, nullptr, 0, f, cfg, lists, nullptr, s);
+        e = launch_detect(nullptr, nullptr, 0, f, cfg, narrow, lists, nullptr, s);
     for (int k = 1; e == hipSuccess && k <= f.niter; ++k)
-        e = launch_step(nullptr, nullptr, 0, f, k, false, lists, nullptr, s);
+        e = launch_step(nullptr, nullptr, 0, f, k, false, narrow, lists, nullptr, s);
     return hip_status(e, "kernel launch");
 }
 
@@ -610,7 +632,8 @@ static crb_status debug_detect(const float *J, const crb_frame *p, uint8_t *out_
                                p->sigfrac, p->objlim, 1, kNoEarlyStop | flags);
     f.codes = out_codes;
     const StepLists none = {};
-    return hip_status(launch_detect(nullptr, nullptr, 0, f, single_cfg(), none, nullptr, t_stream),
+    return hip_status(launch_detect(nullptr, nullptr, 0, f, single_cfg(), false, none, nullptr,
+                                    t_stream),
                       "kernel launch") == CRB_OK
                ? ok()
                : CRB_EDEVICE;
@@ -726,6 +749,7 @@ struct crb_plan {
     size_t max_pix = 0;
     size_t init_pix = 0;                // largest frame with niter == 0
     bool any_copy = false;              // some frame has niter == 0
+    bool narrow = false;                // some frame stores its bit rows in a narrow form
     size_t all_pix = 0;
     char *dmem = nullptr;
     bool own_mem = true;                // dmem is the plan's (else a stream's workspace)
@@ -784,7 +808,7 @@ static crb_status plan_enqueue(crb_plan *p) {
     hipStream_t s = p->stream;
     DevFrame none;
     memset(&none, 0, sizeof(none));
-    const LaunchCfg &cfg = p->cfg;
+    const LaunchCfg cfg = p->narrow ? LaunchCfg() : p->cfg;
     const int ti = tile_h_index(cfg.tile_h);
     if (ti < 0)
         return fail(CRB_EINVAL, "detection tile height %d", cfg.tile_h);
@@ -805,13 +829,13 @@ static crb_status plan_enqueue(crb_plan *p) {
             e = tmark_end(p);
     }
     if (e == hipSuccess && p->kmax > 0 && (e = tmark_begin(p, kKindDetect)) == hipSuccess &&
-        (e = launch_detect(df, tdet, p->ntdet[ti], f, cfg, p->lists, p->d_tickets, s)) ==
-            hipSuccess)
+        (e = launch_detect(df, tdet, p->ntdet[ti], f, cfg, p->narrow, p->lists, p->d_tickets,
+                           s)) == hipSuccess)
         e = tmark_end(p);
     for (int k = 1; e == hipSuccess && k <= p->kmax; ++k)
         if ((e = tmark_begin(p, kKindStep)) == hipSuccess &&
-            (e = launch_step(df, tstep, nstep, f, k, p->counting, p->lists, p->d_tickets, s)) ==
-                hipSuccess)
+            (e = launch_step(df, tstep, nstep, f, k, p->counting, p->narrow, p->lists,
+                             p->d_tickets, s)) == hipSuccess)
             e = tmark_end(p);
     if (e == hipSuccess)
         e = launch_stats(p->d_frames, p->n, p->d_stats, s);
@@ -1051,7 +1075,8 @@ static PlanLayout plan_layout(const crb_frame *frames, int32_t n) {
     L.o_tdet[1] = L.o_tdet[0] + al256(L.ntiles[0] * sizeof(TileRef));
     L.o_tdet[2] = L.o_tdet[1] + al256(L.ntiles[1] * sizeof(TileRef));
     L.o_lists = L.o_tdet[2] + al256(L.ntiles[2] * sizeof(TileRef));
-    L.o_stats = L.o_lists + al256(4 * list_words(L.ntiles[tile_h_index(kSumTY)]));
+    const size_t nstep = L.ntiles[tile_h_index(kSumTY)];
+    L.o_stats = L.o_lists + al256(4 * list_words(nstep, list_segments(nstep)));
     L.o_work = L.o_stats + al256(2 * n * sizeof(long long));
     L.o_tickets = L.o_work + al256(kWorkCounters * n * sizeof(unsigned long long));
     L.bytes = L.o_tickets + al256((size_t)kTicketWords * 4);
@@ -1144,7 +1169,8 @@ static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stre
         p->d_tdet[t] = reinterpret_cast<TileRef *>(p->dmem + L.o_tdet[t]);
         p->ntdet[t] = (int)L.ntiles[t];
     }
-    p->lists = make_lists(p->dmem + L.o_lists, L.ntiles[tile_h_index(kSumTY)]);
+    const size_t nstep = L.ntiles[tile_h_index(kSumTY)];
+    p->lists = make_lists(p->dmem + L.o_lists, nstep, list_segments(nstep));
     p->d_stats = reinterpret_cast<long long *>(p->dmem + L.o_stats);
     p->d_work = reinterpret_cast<unsigned long long *>(p->dmem + L.o_work);
     p->d_tickets = reinterpret_cast<unsigned int *>(p->dmem + L.o_tickets);
@@ -1161,6 +1187,7 @@ static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stre
                                   (f.flags & CRB_FLAG_INCREMENTAL ? kIncremental : 0) |
                                   kFreshMask);
         hf[i].work = p->d_work + kWorkCounters * (size_t)i;
+        p->narrow = p->narrow || hf[i].narrow != 0;
         hf[i].tile_base = base[tile_h_index(kSumTY)];
         for (int t = 0; t < 3; ++t) {
             hf[i].list_base[t] = base[t];

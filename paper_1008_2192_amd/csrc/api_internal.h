@@ -12,6 +12,8 @@ struct FrameWs {
     size_t bits, mbits, state, mark, count, any_new;
     size_t lists;        // lists of a frame run by itself; the end of the pieces of any frame
     size_t total;        // what crb_workspace_bytes reports: at least the end of the lists
+    int narrow;          // DevFrame::narrow
+    int nseg;            // segments of the lists
 };
 
 hipStream_t thread_stream();       // set by crb_set_stream

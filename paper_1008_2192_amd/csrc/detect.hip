@@ -23,7 +23,8 @@ constexpr int kRun3 = 14;
 // block: the codes of the input frame, and the state every later launch starts from -- J (a
 // copy of the input), a cleared mask and its bitmap, the tile's code buffer and list mark, the
 // frame's counters.  Every early return is taken by all threads alike.
-template <int TY>
+// NARROW: the frame may store its bit rows in a narrow form (DevFrame::narrow).
+template <int TY, bool NARROW>
 __device__ __forceinline__ void detect_tile(const DevFrame &f, int y0, int x0, int tid) {
     using L = DetectLds<TY, 4, false>;
     constexpr int TX = L::TX, NT = L::NT;
@@ -85,19 +86,40 @@ __device__ __forceinline__ void detect_tile(const DevFrame &f, int y0, int x0, i
                     dst[j] = 0;
             }
         }
-        if (f.mbits) {
+        if (f.mbits && !(NARROW && f.narrow)) {
             const int t = (y0 + r) / kSumTY * ntx + x0 / kSumTX;
             if (y0 + r < (H + kSumTY - 1) / kSumTY * kSumTY)
                 reinterpret_cast<uint8_t *>(f.mbits + (size_t)t * kSumTY +
                                             ((y0 + r) & (kSumTY - 1)))[cs >> 3] = (uint8_t)mbyte;
         }
     }
+    if (NARROW && f.narrow && f.mbits)
+#pragma unroll 1
+        for (int r = 0; r < TY && y0 + r < H; r += kSumTY)
+            narrow_store(f, f.mbits, (size_t)((y0 + r) / kSumTY * ntx + x0 / kSumTX),
+                         (y0 + r) & (kSumTY - 1), min(TY, kSumTY), tid, NT, [&](int i) {
+                             unsigned long long m = 0ull;
+                             if (!(f.flags & kFreshMask) && y0 + r + i < H)
+#pragma unroll 1
+                                 for (int c = 0; c < TX && x0 + c < W; ++c)
+                                     m |= f.mask[(size_t)(y0 + r + i) * W + x0 + c] ? 1ull << c
+                                                                                   : 0ull;
+                             return m;
+                         });
     detect_staged(s, f, y0, x0, tid);
 
     // the code planes of the summary tiles the block covers (buffer 0), their state words
     const unsigned long long *code = reinterpret_cast<const unsigned long long *>(s.code);
+    if (NARROW && f.narrow && f.bits)
+#pragma unroll 1
+        for (int r = 0; r < TY && y0 + r < H; r += kSumTY)
+#pragma unroll 1
+            for (int p = 0; p < 3; ++p)
+                narrow_store(f, f.bits, ((size_t)(y0 + r) / kSumTY * ntx + x0 / kSumTX) * 6 + p,
+                             (y0 + r) & (kSumTY - 1), min(TY, kSumTY), tid, NT,
+                             [&](int i) { return code[p * TY + r + i]; });
     if (f.bits) {
-        for (int i = tid; i < 3 * TY; i += NT) {
+        for (int i = tid; i < 3 * TY && !(NARROW && f.narrow); i += NT) {
             const int p = i / TY, r = i - p * TY;
             if (y0 + (r & ~(kSumTY - 1)) < H)
                 f.bits[((size_t)((y0 + r) / kSumTY * ntx + x0 / kSumTX) * 2 * 3 + p) * kSumTY +
@@ -141,7 +163,7 @@ __device__ __forceinline__ void tile_of(const DevFrame *__restrict__ frames,
 }
 
 // One block per tile.
-template <int TY>
+template <int TY, bool NARROW>
 __global__ __launch_bounds__(8 * TY) __attribute__((amdgpu_waves_per_eu(TY == 16 ? 4 : 6)))
 void k_detect(const DevFrame *__restrict__ frames, const TileRef *__restrict__ tiles,
               DevFrame single, StepLists lists) {
@@ -150,7 +172,7 @@ void k_detect(const DevFrame *__restrict__ frames, const TileRef *__restrict__ t
     tile_of<TY>(frames, tiles, single, (int)blockIdx.x, f, y0, x0);
     if (blockIdx.x == 0)
         lists_start(lists, (int)threadIdx.x);
-    detect_tile<TY>(f, y0, x0, (int)threadIdx.x);
+    detect_tile<TY, NARROW>(f, y0, x0, (int)threadIdx.x);
 }
 
 // Persistent blocks over a (frame, tile) work list: the grid holds about as many
@@ -211,7 +233,7 @@ void k_detect_persistent(const DevFrame *__restrict__ frames, const TileRef *__r
             // across the loop
             int tid = (int)threadIdx.x;
             asm volatile("" : "+v"(tid));
-            detect_tile<TY>(f, r.y0, r.x0, tid);
+            detect_tile<TY, false>(f, r.y0, r.x0, tid);
         }
     }
 }
@@ -398,16 +420,24 @@ static hipError_t launch_detect_ty(const DevFrame *d_frames, const TileRef *d_ti
         k_detect_persistent<TY><<<grid, 8 * TY, 0, s>>>(d_frames, d_tiles, lists, ntiles,
                                                            tickets);
     } else {
-        k_detect<TY><<<ntiles, 8 * TY, 0, s>>>(d_frames, d_tiles, single, lists);
+        k_detect<TY, false><<<ntiles, 8 * TY, 0, s>>>(d_frames, d_tiles, single, lists);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_detect(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
-                         const DevFrame &single, const LaunchCfg &cfg, const StepLists &lists,
-                         unsigned int *tickets, hipStream_t s) {
+                         const DevFrame &single, const LaunchCfg &cfg, bool narrow,
+                         const StepLists &lists, unsigned int *tickets, hipStream_t s) {
     if (!d_tiles)
         ntiles = detect_tiles(single.H, single.W, cfg.tile_h);
+    if (narrow) {
+        if (cfg.tile_h != kDetectTYDefault || cfg.persistent)
+            return hipErrorInvalidValue;
+        if (ntiles > 0)
+            k_detect<kDetectTYDefault, true><<<ntiles, 8 * kDetectTYDefault, 0, s>>>(
+                d_frames, d_tiles, single, lists);
+        return hipGetLastError();
+    }
     switch (cfg.tile_h) {
     case 16:
         return launch_detect_ty<16>(d_frames, d_tiles, ntiles, single, lists,

@@ -90,7 +90,11 @@ struct DevFrame {
     float olim_lo, olim_hi, inv_olim;
     float g8, inv_gain, rn2f;
     int est_ok;
-    int pad2;
+    // How the tiles' bit rows are stored.  0: 32 rows of 64 bits a plane.  Frames that cover
+    // little of their tiles keep what they cover, so that their workspace is not larger than
+    // reported (ws_layout): -H, for one row of tiles, H rows of 64 bits; p = 1, 2, 4, 8 or 16,
+    // for one column of tiles, 32 rows of p bits in units of 16 bits, the first in the low bits.
+    int narrow;
 };
 
 // Fills the detection constants of f from its parameters (every DevFrame passes through
@@ -109,7 +113,6 @@ inline void derive_detect_consts(DevFrame &f) {
     f.inv_gain = 1.0f / f.gain;
     f.rn2f = f.readnoise * f.readnoise;
     f.est_ok = (f.gain >= 0x1p-100f && f.gain <= 0x1p100f) ? 1 : 0;
-    f.pad2 = 0;
 }
 
 struct TileRef {                  // one (frame, tile origin) work item
@@ -126,25 +129,21 @@ struct StepLists {
     unsigned int *count;
     int nseg, cap;
 };
-// Segments and words of the lists of ntiles tiles.
+// Segments of the lists of ntiles tiles (a power of two), and their words.
 inline int list_segments(size_t ntiles) {
     int n = 1;
     while (n < kListSegments && (size_t)(2 * n) <= ntiles)
         n *= 2;
     return n;
 }
-inline size_t list_cap(size_t ntiles) {
-    const size_t n = (size_t)list_segments(ntiles);
-    return (ntiles + n - 1) / n;
+inline size_t list_words(size_t ntiles, int nseg) {
+    const size_t n = (size_t)nseg;
+    return 2 * n * ((ntiles + n - 1) / n) + 3 * n * kTicketStride;
 }
-inline size_t list_words(size_t ntiles) {
-    const size_t n = (size_t)list_segments(ntiles);
-    return 2 * n * list_cap(ntiles) + 3 * n * kTicketStride;
-}
-inline StepLists make_lists(void *p, size_t ntiles) {
+inline StepLists make_lists(void *p, size_t ntiles, int nseg) {
     StepLists l;
-    l.nseg = list_segments(ntiles);
-    l.cap = (int)list_cap(ntiles);
+    l.nseg = nseg;
+    l.cap = (int)((ntiles + (size_t)nseg - 1) / (size_t)nseg);
     l.list[0] = static_cast<unsigned int *>(p);
     l.list[1] = l.list[0] + (size_t)l.nseg * l.cap;
     l.count = l.list[1] + (size_t)l.nseg * l.cap;
@@ -189,10 +188,11 @@ struct LaunchCfg {
 
 // The first iteration's detection for one frame (d_tiles == null: tiles over `single`) or a
 // work list of (frame, tile) built for cfg.tile_h.  Persistent launches take kTicketWords
-// zeroed words of ticket counters.
+// zeroed words of ticket counters.  narrow, here and below: some frame has f.narrow != 0 (these
+// launches take the default shape).
 hipError_t launch_detect(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
-                         const DevFrame &single, const LaunchCfg &cfg, const StepLists &lists,
-                         unsigned int *tickets, hipStream_t s);
+                         const DevFrame &single, const LaunchCfg &cfg, bool narrow,
+                         const StepLists &lists, unsigned int *tickets, hipStream_t s);
 // Number of detection tiles of an H x W frame at tile height tile_h.
 __host__ __device__ inline int detect_tiles(int H, int W, int tile_h) {
     return ((H + tile_h - 1) / tile_h) * ((W + kDetectTX - 1) / kDetectTX);
@@ -203,11 +203,11 @@ __host__ __device__ inline int detect_tiles(int H, int W, int tile_h) {
 // tile at every iteration (frames that re-evaluate every pixel).  tickets, if not null:
 // kTicketWords words that iteration 1 zeroes.
 hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
-                       const DevFrame &single, int k, bool all, const StepLists &lists,
-                       unsigned int *tickets, hipStream_t s);
+                       const DevFrame &single, int k, bool all, bool narrow,
+                       const StepLists &lists, unsigned int *tickets, hipStream_t s);
 // Each frame's own iteration f.k on the tiles of a list built by launch_tiles.
 hipError_t launch_step_active(const DevFrame *d_frames, const TileRef *d_tiles, size_t ntiles,
-                              const TileList &active, hipStream_t s);
+                              bool narrow, const TileList &active, hipStream_t s);
 // Per-frame (iters_run, n_flagged) into d_stats[2 * i].
 hipError_t launch_stats(const DevFrame *d_frames, int nframes, long long *d_stats,
                         hipStream_t s);

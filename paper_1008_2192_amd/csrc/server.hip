@@ -527,8 +527,10 @@ static crb_status launch_round(crb_server *s) {
         return st;
     DevFrame *hf = reinterpret_cast<DevFrame *>(s->h_tab + t.o_frames);
     size_t inew = 0, iold = 0;
+    bool narrow = false;
     for (int i = 0; i < n; ++i) {
         Request *r = s->active[i];
+        narrow = narrow || r->df.narrow != 0;
         hf[i] = r->df;
         hf[i].k = r->k_next;
         const size_t nt = (size_t)detect_tiles(r->H, r->W, kSumTY);
@@ -566,11 +568,11 @@ static crb_status launch_round(crb_server *s) {
         e = launch_tiles(dfr, n, t.max_tiles, nullptr, dnew, nullptr, dold, active, nullptr, 0,
                          s->compute);
     if (e == hipSuccess && t.nnew)
-        e = launch_detect(dfr, dnew, (int)t.nnew, none, cfg, lists, nullptr, s->compute);
+        e = launch_detect(dfr, dnew, (int)t.nnew, none, cfg, narrow, lists, nullptr, s->compute);
     if (e == hipSuccess && t.nnew)
-        e = launch_step(dfr, dnew, (int)t.nnew, none, 1, false, lists, nullptr, s->compute);
+        e = launch_step(dfr, dnew, (int)t.nnew, none, 1, false, narrow, lists, nullptr, s->compute);
     if (e == hipSuccess && t.nold)
-        e = launch_step_active(dfr, dold, t.nold, active, s->compute);
+        e = launch_step_active(dfr, dold, t.nold, narrow, active, s->compute);
     if (e == hipSuccess)
         e = launch_round_stats(dfr, n, dst, active, s->compute);
     if (e == hipSuccess)

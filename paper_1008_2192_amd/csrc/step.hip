@@ -182,7 +182,9 @@ __device__ __forceinline__ void list_tile(const StepLists &l, int k, int g) {
         l.list[k & 1][(size_t)seg * l.cap + at] = (unsigned int)g;
 }
 
-// Iteration k of frame f on its summary tile (ty, tx), by the whole block.
+// Iteration k of frame f on its summary tile (ty, tx), by the whole block.  NARROW: the frame
+// may store its bit rows in a narrow form (DevFrame::narrow).
+template <bool NARROW>
 __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int k,
                                           const StepLists &lists, StepShared &sh, int tid) {
     using L = StepLds;
@@ -221,12 +223,20 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
                     const unsigned int st = f.state[t];
                     buf = (st & 1u) ^ ((st >> 1) == (unsigned int)(k + 1) ? 1u : 0u);
                 }
-                const unsigned long long *b = f.bits + (t * 2 + buf) * (3 * kSumTY) + rr;
-                w[0][d] = b[0];
-                w[1][d] = b[kSumTY];
-                w[2][d] = b[2 * kSumTY];
-                if (k > 1 || !(f.flags & kFreshMask))
-                    w[3][d] = f.mbits[t * kSumTY + rr];
+                const bool mask = k > 1 || !(f.flags & kFreshMask);
+                if (!(NARROW && f.narrow)) {
+                    const unsigned long long *b = f.bits + (t * 2 + buf) * (3 * kSumTY) + rr;
+                    w[0][d] = b[0];
+                    w[1][d] = b[kSumTY];
+                    w[2][d] = b[2 * kSumTY];
+                    if (mask)
+                        w[3][d] = f.mbits[t * kSumTY + rr];
+                } else {
+                    for (int p = 0; p < 3; ++p)
+                        w[p][d] = narrow_row(f, f.bits, (t * 2 + buf) * 3 + p, rr);
+                    if (mask)
+                        w[3][d] = narrow_row(f, f.mbits, t, rr);
+                }
                 own_buf = d == 1 ? buf : own_buf;
             }
         }
@@ -236,8 +246,17 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
         Row80 m = row_or(mp, g2);
         const bool tile_row = lane >= 8 && lane < 40;
         const unsigned long long nw = tile_row && y < H ? own64(g2) & ~w[3][1] : 0ull;
-        if (nw)
-            f.mbits[((size_t)ty * ntx + tx) * kSumTY + rr] = own64(m);
+        if (nw) {
+            const size_t t = (size_t)ty * ntx + tx;
+            if (!(NARROW && f.narrow))
+                f.mbits[t * kSumTY + rr] = own64(m);
+            else if (f.narrow < 0)
+                f.mbits[t * (size_t)-f.narrow + rr] = own64(m);
+            else          // (other rows of the word are other lanes')
+                atomicOr(reinterpret_cast<uint32_t *>(f.mbits) + t * (size_t)f.narrow +
+                             (rr * f.narrow >> 5),
+                         (uint32_t)nw << (rr * f.narrow & 31));
+        }
         const unsigned int n = __ockl_wfred_add_u32((unsigned int)__popcll(nw));
         if (n && lane == 0) {
             // (a sum that all of a frame's blocks add to would serialise them: 8192 blocks
@@ -385,10 +404,17 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
         const size_t t = (size_t)ty * ntx + tx;
         const unsigned int buf = sh.buf ^ 1u;
         const unsigned long long *code = reinterpret_cast<const unsigned long long *>(s.code);
-        unsigned long long *o = f.bits + (t * 2 + buf) * (3 * kSumTY);
-        o[lane] = code[lane];
-        if (lane < kSumTY)
-            o[64 + lane] = code[64 + lane];
+        if (!(NARROW && f.narrow)) {
+            unsigned long long *o = f.bits + (t * 2 + buf) * (3 * kSumTY);
+            o[lane] = code[lane];
+            if (lane < kSumTY)
+                o[64 + lane] = code[64 + lane];
+        } else {
+#pragma unroll 1
+            for (int p = 0; p < 3; ++p)
+                narrow_store(f, f.bits, (t * 2 + buf) * 3 + p, 0, kSumTY, lane, 64,
+                             [&](int i) { return code[p * kSumTY + i]; });
+        }
         // where A lies: bit 3 (dy + 1) + dx + 1 when it is within 8 pixels (an iteration's
         // reach) of the neighbour in direction (dy, dx)
         const unsigned long long a = lane < kSumTY ? code[lane] : 0ull;
@@ -436,6 +462,7 @@ __device__ __forceinline__ int step_place(const TileRef *__restrict__ tiles, con
     tx = g - ty * ntx;
     return -1;
 }
+template <bool NARROW>
 __device__ __forceinline__ void step_one(const DevFrame &f, int ty, int tx, int kiter, bool by_mark,
                                          const StepLists &lists, StepShared &sh, int tid) {
     const int k = kiter ? kiter : f.k;
@@ -450,10 +477,11 @@ __device__ __forceinline__ void step_one(const DevFrame &f, int ty, int tx, int 
     if (by_mark && k >= 2 && !((f.flags & kCountWork) && !(f.flags & kIncremental)) &&
         f.mark[(size_t)ty * ((f.W + kSumTX - 1) / kSumTX) + tx] < (unsigned int)k)
         return;
-    step_tile(f, ty, tx, k, lists, sh, tid);
+    step_tile<NARROW>(f, ty, tx, k, lists, sh, tid);
 }
 
 // Iteration k on every tile of the launch (k == 0: each frame's own).
+template <bool NARROW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
 void k_step(const DevFrame *__restrict__ frames, const TileRef *__restrict__ tiles,
             DevFrame single, int kiter, StepLists lists, unsigned int *__restrict__ tickets) {
@@ -473,11 +501,12 @@ void k_step(const DevFrame *__restrict__ frames, const TileRef *__restrict__ til
         f = frames[fi];
     else
         f = single;
-    step_one(f, ty, tx, kiter, true, lists, sh, tid);
+    step_one<NARROW>(f, ty, tx, kiter, true, lists, sh, tid);
 }
 
 // The tiles of a list: block b takes entries b / nseg, b / nseg + stride, ... of segment
 // b % nseg.  kiter: the iteration (0: each frame's own).
+template <bool NARROW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
 void k_step_listed(const DevFrame *__restrict__ frames, const TileRef *__restrict__ tiles,
                    DevFrame single, int kiter, TileList in, StepLists lists) {
@@ -500,7 +529,7 @@ void k_step_listed(const DevFrame *__restrict__ frames, const TileRef *__restric
             f = frames[fi];
         else
             f = single;
-        step_one(f, ty, tx, kiter, false, lists, sh, tid);
+        step_one<NARROW>(f, ty, tx, kiter, false, lists, sh, tid);
         __syncthreads();       // the tile is done with the LDS
     }
 }
@@ -511,31 +540,40 @@ static int listed_grid(size_t ntiles, int nseg) {
     return (int)(per < most ? per : most) * nseg;
 }
 
-hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
-                       const DevFrame &single, int k, bool all, const StepLists &lists,
-                       unsigned int *tickets, hipStream_t s) {
-    if (!d_tiles)
-        ntiles = detect_tiles(single.H, single.W, kSumTY);
-    if (ntiles <= 0)
-        return hipSuccess;
+template <bool NARROW>
+static hipError_t launch_step_as(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
+                                 const DevFrame &single, int k, bool all, const StepLists &lists,
+                                 unsigned int *tickets, hipStream_t s) {
     if (k <= 1 || all || !lists.list[0]) {
-        k_step<<<ntiles, 256, 0, s>>>(d_frames, d_tiles, single, k, lists, tickets);
+        k_step<NARROW><<<ntiles, 256, 0, s>>>(d_frames, d_tiles, single, k, lists, tickets);
     } else {
         const TileList in = {lists.list[k & 1],
                              lists.count + (size_t)(k % 3) * lists.nseg * kTicketStride,
                              lists.nseg, lists.cap};
-        k_step_listed<<<listed_grid((size_t)ntiles, in.nseg), 256, 0, s>>>(d_frames, d_tiles,
-                                                                           single, k, in, lists);
+        k_step_listed<NARROW><<<listed_grid((size_t)ntiles, in.nseg), 256, 0, s>>>(
+            d_frames, d_tiles, single, k, in, lists);
     }
     return hipGetLastError();
 }
 
+hipError_t launch_step(const DevFrame *d_frames, const TileRef *d_tiles, int ntiles,
+                       const DevFrame &single, int k, bool all, bool narrow,
+                       const StepLists &lists, unsigned int *tickets, hipStream_t s) {
+    if (!d_tiles)
+        ntiles = detect_tiles(single.H, single.W, kSumTY);
+    if (ntiles <= 0)
+        return hipSuccess;
+    const auto as = narrow ? launch_step_as<true> : launch_step_as<false>;
+    return as(d_frames, d_tiles, ntiles, single, k, all, lists, tickets, s);
+}
+
 hipError_t launch_step_active(const DevFrame *d_frames, const TileRef *d_tiles, size_t ntiles,
-                              const TileList &active, hipStream_t s) {
+                              bool narrow, const TileList &active, hipStream_t s) {
     DevFrame none = {};
     const StepLists lists = {};
-    k_step_listed<<<listed_grid(ntiles, active.nseg), 256, 0, s>>>(d_frames, d_tiles, none, 0,
-                                                                   active, lists);
+    const auto kernel = narrow ? k_step_listed<true> : k_step_listed<false>;
+    kernel<<<listed_grid(ntiles, active.nseg), 256, 0, s>>>(d_frames, d_tiles, none, 0, active,
+                                                            lists);
     return hipGetLastError();
 }
 
