@@ -16,7 +16,7 @@ def test_outputs_are_written_at_completion(kind):
     want = solo(a, 4)
     srv = serving.Server(1 << 30, max_slots=8)
     clean, mask = torch.full_like(a, -1.0), new_mask()
-    waits = torch.full((1, 100), 1000.0, device="cuda")       # one actor, 100 ms in all
+    waits = torch.full((1, 64 * 100), 1000.0, device="cuda")  # one actor of 64 lanes: 100 ms
     _lib.work_run(_lib.CRB_WORK_WAITER, waits[:, :1].contiguous(), workers=1)   # (first call)
     tick = torch.zeros(4, device="cuda")
     torch.cuda.synchronize()
