@@ -38,8 +38,8 @@
  *   - image pointers are DEVICE pointers on the current HIP device, row-major,
  *     contiguous, pitch == W; masks are uint8 0/1;
  *   - the caller owns every buffer it passes; the library owns only internal
- *     workspace (device memory it allocates and keeps per stream until
- *     crb_release_workspace or process exit);
+ *     workspace (device memory it allocates and keeps per stream, and between synchronous
+ *     calls, until crb_release_workspace or process exit);
  *   - calls are stream-ordered and asynchronous unless stated otherwise; the
  *     returned status covers argument validation and launch errors only;
  *   - on any status other than CRB_OK nothing has been enqueued, and
@@ -147,9 +147,11 @@ typedef struct {
  * Each frame's outputs are bit-identical to a crb_lacosmic call with the same
  * parameters (Section 5 for the method).  Synchronous, unlike the other cleaning
  * calls: it writes the host fields iters_run and n_flagged of frames[] at completion,
- * so it waits for the batch on hip_stream (NULL: default stream).  Its workspace is the
- * stream's (kept until crb_release_workspace), or freed before returning above 1 GiB.  The stream-ordered, asynchronous form is the
- * batch plan below (crb_plan_run, then crb_plan_stats for the per-frame results).
+ * so it waits for the batch on hip_stream (NULL: default stream).  Its memory is kept for
+ * the next synchronous call on the device, whatever its stream and thread (at most 1 GiB in
+ * all, until crb_release_workspace; what is above is freed before returning).  The
+ * stream-ordered, asynchronous form is the batch plan below (crb_plan_run, then
+ * crb_plan_stats for the per-frame results).
  */
 crb_status crb_lacosmic_batched(crb_frame *frames, int32_t n, void *hip_stream);
 
@@ -257,8 +259,8 @@ crb_status crb_plan_autotune(crb_plan *plan, int32_t reps, int32_t use_cache, cr
  * dependency radius is 8 pixels); smaller borders show the subimage edge effects
  * the paper's 6-pixel border trades against overlap.  border = -1 takes the declared
  * radius of the cleaning pass, 8 * niter (crb_work_radius of CRB_WORK_LACOSMIC).
- * Synchronous on the calling thread's stream, whose workspace holds the subimages (above
- * 1 GiB: memory allocated and freed by the call).
+ * Synchronous on the calling thread's stream; the subimages are in memory kept between such
+ * calls (see crb_lacosmic_batched).
  *   ny, nx >= 1 with ny <= H and nx <= W; border >= -1; other arguments as crb_lacosmic.
  */
 crb_status crb_lacosmic_partitioned(const float *img, int32_t H, int32_t W, float gain,
@@ -364,7 +366,9 @@ const char *crb_last_error(void);
 /* Device workspace to provide for a frame of H x W beyond its input and outputs (bytes):
  * about 5 bytes per pixel (a frame uses less; budgets and limits go by this number). */
 size_t crb_workspace_bytes(int32_t H, int32_t W);
-/* Free the workspace cached for hip_stream (waits for the stream first). */
+/* Free the workspace cached for hip_stream (waits for the stream first; call it before the
+ * stream is destroyed) and the memory that the synchronous calls on the current device left
+ * for the next one. */
 crb_status crb_release_workspace(void *hip_stream);
 
 /*

@@ -230,6 +230,100 @@ static crb_status ws_reserve(Workspace *ws, size_t bytes) {
     return CRB_OK;
 }
 
+// ---------------------------------------------------------------------------
+// memory that synchronous calls leave for the next one
+// ---------------------------------------------------------------------------
+
+struct IdleBlock {
+    int device;
+    char *p;
+    size_t bytes;
+};
+constexpr size_t kIdleBytes = (size_t)1 << 30;      // kept per device at most
+constexpr int kIdleBlocks = 16;                     // kept in all at most
+static std::mutex g_idle_mu;
+static IdleBlock g_idle[kIdleBlocks];
+static int g_nidle = 0;
+
+// Takes the smallest idle block of the device with at least `bytes` bytes, or else its largest
+// one; p null if there is none.  (caller holds g_idle_mu)
+static IdleBlock idle_pick(int device, size_t bytes) {
+    int best = -1;
+    for (int i = 0; i < g_nidle; ++i) {
+        if (g_idle[i].device != device)
+            continue;
+        const bool fits = g_idle[i].bytes >= bytes;
+        if (best < 0 || (fits ? g_idle[best].bytes < bytes || g_idle[i].bytes < g_idle[best].bytes
+                              : g_idle[i].bytes > g_idle[best].bytes))
+            best = i;
+    }
+    if (best < 0)
+        return IdleBlock{device, nullptr, 0};
+    const IdleBlock b = g_idle[best];
+    g_idle[best] = g_idle[--g_nidle];
+    return b;
+}
+
+static void idle_free_device(int device) {
+    for (;;) {
+        IdleBlock b;
+        {
+            std::lock_guard<std::mutex> g(g_idle_mu);
+            b = idle_pick(device, 0);
+        }
+        if (!b.p)
+            return;
+        (void)hipFree(b.p);
+    }
+}
+
+// At least `bytes` bytes of the current device: an idle block, or one allocated in place of the
+// largest idle one, which was too small.
+static crb_status idle_take(size_t bytes, IdleBlock *out) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return hip_status(e, "hipGetDevice");
+    {
+        std::lock_guard<std::mutex> g(g_idle_mu);
+        *out = idle_pick(dev, bytes);
+    }
+    if (out->p && out->bytes >= bytes)
+        return CRB_OK;
+    if (out->p)
+        (void)hipFree(out->p);
+    *out = IdleBlock{dev, nullptr, align_up(bytes, (size_t)1 << 20)};
+    e = hipMalloc((void **)&out->p, out->bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        idle_free_device(dev);
+        e = hipMalloc((void **)&out->p, out->bytes);
+    }
+    if (e != hipSuccess) {
+        out->p = nullptr;
+        (void)hipGetLastError();
+        return fail(CRB_ENOMEM, "%zu bytes: %s", out->bytes, hipGetErrorString(e));
+    }
+    return CRB_OK;
+}
+
+// Gives a block back (p null: nothing); what does not fit the limits is freed.
+static void idle_give(const IdleBlock &b) {
+    if (!b.p)
+        return;
+    {
+        std::lock_guard<std::mutex> g(g_idle_mu);
+        size_t kept = b.bytes;
+        for (int i = 0; i < g_nidle; ++i)
+            kept += g_idle[i].device == b.device ? g_idle[i].bytes : 0;
+        if (kept <= kIdleBytes && g_nidle < kIdleBlocks) {
+            g_idle[g_nidle++] = b;
+            return;
+        }
+    }
+    (void)hipFree(b.p);
+}
+
 // launch shapes of the single-frame entry points (CRB_OPT_TILE_H, CRB_OPT_FUSED,
 // CRB_OPT_GROW_H; every shape gives identical results)
 static std::atomic<int> g_single_tile_h{kDetectTYDefault};
@@ -361,6 +455,7 @@ crb_status crb_release_workspace(void *hip_stream) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess)
         return fail(CRB_EDEVICE, "no HIP device");
+    idle_free_device(dev);
     Workspace *w = nullptr;
     {
         std::lock_guard<std::mutex> g(g_ws_mu);
@@ -752,7 +847,7 @@ struct crb_plan {
     bool narrow = false;                // some frame stores its bit rows in a narrow form
     size_t all_pix = 0;
     char *dmem = nullptr;
-    bool own_mem = true;                // dmem is the plan's (else a stream's workspace)
+    bool own_mem = true;                // dmem is the plan's (else a synchronous call's)
     DevFrame *d_frames = nullptr;
     TileRef *d_tdet[3] = {nullptr, nullptr, nullptr};   // per detection tile height
     int ntdet[3] = {0, 0, 0};
@@ -1230,37 +1325,20 @@ static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stre
     return ok();
 }
 
-// Memory of a synchronous call: the stream's workspace (kept until crb_release_workspace, so
-// that a call after the first allocates nothing), or, above this size, freed by the call.
-constexpr size_t kKeepBytes = (size_t)1 << 30;
-
+// Memory of a synchronous call, which has waited for its stream when it gives it back, so that
+// any thread's next call on any stream of the device may take it (idle_take): calls after the
+// first allocate nothing, hold no lock while they wait, and leave the streams' workspaces, which
+// a captured crb_lacosmic or crb_farm_run refers to, as they are.
 struct CallMemory {
-    Workspace *ws = nullptr;
-    std::unique_lock<std::mutex> lock;
+    IdleBlock block = {0, nullptr, 0};
     char *mem = nullptr;
 
-    crb_status reserve(hipStream_t s, size_t bytes) {
-        if (bytes > kKeepBytes) {
-            const hipError_t e = hipMalloc((void **)&mem, bytes);
-            if (e == hipSuccess)
-                return CRB_OK;
-            mem = nullptr;
-            (void)hipGetLastError();
-            return fail(CRB_ENOMEM, "%zu bytes: %s", bytes, hipGetErrorString(e));
-        }
-        crb_status st = ws_get(s, &ws);
-        if (st != CRB_OK)
-            return st;
-        lock = std::unique_lock<std::mutex>(ws->mu);
-        if ((st = ws_reserve(ws, bytes)) == CRB_OK)
-            mem = ws->buf;
+    crb_status reserve(size_t bytes) {
+        const crb_status st = idle_take(bytes, &block);
+        mem = block.p;
         return st;
     }
-    // (the caller has waited for the stream)
-    ~CallMemory() {
-        if (mem && !ws)
-            (void)hipFree(mem);
-    }
+    ~CallMemory() { idle_give(block); }
 };
 
 }  // namespace crb
@@ -1489,7 +1567,7 @@ crb_status crb_lacosmic_batched(crb_frame *frames, int32_t n, void *hip_stream) 
         return st;
     hipStream_t s = (hipStream_t)hip_stream;
     CallMemory mem;
-    if ((st = mem.reserve(s, plan_layout(frames, n).bytes)) != CRB_OK)
+    if ((st = mem.reserve(plan_layout(frames, n).bytes)) != CRB_OK)
         return st;
     crb_plan *p = nullptr;
     if ((st = plan_make(frames, n, s, false, mem.mem, &p)) != CRB_OK)
@@ -1569,7 +1647,7 @@ extern "C" crb_status crb_lacosmic_partitioned(const float *img, int32_t H, int3
     const size_t o_tab = total;
     const size_t o_plan = o_tab + al(nsub * sizeof(SubRect));
     CallMemory mem;
-    if ((st = mem.reserve(s, o_plan + plan_layout(frames.data(), nsub).bytes)) != CRB_OK)
+    if ((st = mem.reserve(o_plan + plan_layout(frames.data(), nsub).bytes)) != CRB_OK)
         return st;
     for (int q = 0; q < nsub; ++q) {
         SubRect &r = subs[q];
