@@ -337,7 +337,7 @@ int32_t crb_work_radius(const crb_work *w);
  *     was truncated and a rerun with a larger list returns all.  out_image must be null.
  * Tiles are handed out through 32 ticket counters, each over a contiguous range of
  * tiles, in runs of several tiles; an actor drains its own range first and then
- * helps with the others.  Asynchronous on the calling thread's stream; uses 32 bytes
+ * helps with the others.  Asynchronous on the calling thread's stream; uses 4 KiB
  * of that stream's workspace, so calls on one stream are ordered and calls on
  * different streams are independent.
  */
@@ -348,7 +348,7 @@ crb_status crb_farm_run(const crb_work *w, const float *in, int32_t H, int32_t W
 /* Copies the n records of a SOURCES list of an H x W frame (on distinct pixels; records
  * outside the frame are left out) to out in raster order (device, 8-byte aligned, no
  * overlap).  Asynchronous on the calling thread's stream; uses 3/16 byte per frame pixel of
- * that stream's workspace. */
+ * that stream's workspace, in an allocation of its own. */
 crb_status crb_sources_order(const crb_source *list, int64_t n, int32_t H, int32_t W,
                              crb_source *out);
 

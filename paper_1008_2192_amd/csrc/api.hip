@@ -176,10 +176,16 @@ crb_status hip_status(hipError_t e, const char *what) {
 // per-(device, stream) workspace
 // ---------------------------------------------------------------------------
 
-struct Workspace {
-    std::mutex mu;
+// One growing allocation.
+struct WsMemory {
     char *buf = nullptr;
     size_t cap = 0;
+};
+struct Workspace {
+    std::mutex mu;
+    WsMemory main;                // frame state and farm tickets
+    WsMemory order;               // crb_sources_order's (reading a list back does not
+                                  // reallocate what a captured call refers to)
     int device = 0;
     hipStream_t stream = nullptr;
 };
@@ -208,25 +214,32 @@ static crb_status ws_get(hipStream_t s, Workspace **out) {
 }
 
 // caller holds ws->mu
-static crb_status ws_reserve(Workspace *ws, size_t bytes) {
-    if (ws->cap >= bytes)
-        return CRB_OK;
-    if (ws->buf) {
+static crb_status ws_free(Workspace *ws, WsMemory *m) {
+    if (m->buf) {
         hipError_t e = hipStreamSynchronize(ws->stream);
         if (e != hipSuccess)
             return hip_status(e, "hipStreamSynchronize");
-        (void)hipFree(ws->buf);
-        ws->buf = nullptr;
-        ws->cap = 0;
+        (void)hipFree(m->buf);
+        *m = WsMemory();
     }
+    return CRB_OK;
+}
+
+// caller holds ws->mu
+static crb_status ws_reserve(Workspace *ws, WsMemory *m, size_t bytes) {
+    if (m->cap >= bytes)
+        return CRB_OK;
+    crb_status st = ws_free(ws, m);
+    if (st != CRB_OK)
+        return st;
     const size_t want = align_up(bytes, (size_t)1 << 20);
-    hipError_t e = hipMalloc((void **)&ws->buf, want);
+    hipError_t e = hipMalloc((void **)&m->buf, want);
     if (e != hipSuccess) {
-        ws->buf = nullptr;
+        m->buf = nullptr;
         (void)hipGetLastError();
         return fail(CRB_ENOMEM, "workspace of %zu bytes: %s", want, hipGetErrorString(e));
     }
-    ws->cap = want;
+    m->cap = want;
     return CRB_OK;
 }
 
@@ -465,15 +478,10 @@ crb_status crb_release_workspace(void *hip_stream) {
         w = it->second;
     }
     std::lock_guard<std::mutex> g(w->mu);
-    if (w->buf) {
-        hipError_t e = hipStreamSynchronize(w->stream);
-        if (e != hipSuccess)
-            return hip_status(e, "hipStreamSynchronize");
-        (void)hipFree(w->buf);
-        w->buf = nullptr;
-        w->cap = 0;
-    }
-    return ok();
+    crb_status st = ws_free(w, &w->main);
+    if (st == CRB_OK)
+        st = ws_free(w, &w->order);
+    return st == CRB_OK ? ok() : st;
 }
 
 crb_status crb_lacosmic_noalloc(const float *img, int32_t H, int32_t W, float gain,
@@ -519,13 +527,13 @@ crb_status crb_lacosmic(const float *img, int32_t H, int32_t W, float gain, floa
         return st;
     std::lock_guard<std::mutex> g(ws->mu);
     const FrameWs L = ws_layout(H, W);
-    if ((st = ws_reserve(ws, L.total)) != CRB_OK)
+    if ((st = ws_reserve(ws, &ws->main, L.total)) != CRB_OK)
         return st;
     const int flags = (g_early_stop.load() ? 0 : kNoEarlyStop) |
                       (g_incremental.load() ? kIncremental : 0) | kFreshMask;
-    DevFrame f = make_devframe(img, out_clean, out_mask, ws->buf, L, H, W, gain, readnoise, sky,
+    DevFrame f = make_devframe(img, out_clean, out_mask, ws->main.buf, L, H, W, gain, readnoise, sky,
                                sigclip, sigfrac, objlim, niter, flags);
-    if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->buf, L, H, W), s)) != CRB_OK)
+    if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->main.buf, L, H, W), s)) != CRB_OK)
         return st;
     return ok();
 }
@@ -625,9 +633,9 @@ crb_status crb_farm_run(const crb_work *w, const float *in, int32_t H, int32_t W
     if ((st = ws_get(s, &ws)) != CRB_OK)
         return st;
     std::lock_guard<std::mutex> g(ws->mu);
-    if ((st = ws_reserve(ws, kFarmTicketWords * 4)) != CRB_OK)
+    if ((st = ws_reserve(ws, &ws->main, kFarmTicketWords * 4)) != CRB_OK)
         return st;
-    unsigned int *tickets = reinterpret_cast<unsigned int *>(ws->buf);
+    unsigned int *tickets = reinterpret_cast<unsigned int *>(ws->main.buf);
     unsigned long long *count = reinterpret_cast<unsigned long long *>(out_count);
     const hipError_t e =
         launch_farm(w->kind, a2, in, H, W, workers, tile_h, tile_w, out_image,
@@ -669,10 +677,10 @@ crb_status crb_sources_order(const crb_source *list, int64_t n, int32_t H, int32
     if ((st = ws_get(s, &ws)) != CRB_OK)
         return st;
     std::lock_guard<std::mutex> g(ws->mu);
-    if ((st = ws_reserve(ws, order_bytes(H, W))) != CRB_OK)
+    if ((st = ws_reserve(ws, &ws->order, order_bytes(H, W))) != CRB_OK)
         return st;
     st = hip_status(launch_order(reinterpret_cast<const SourceRec *>(list), n, H, W,
-                                 reinterpret_cast<SourceRec *>(out), ws->buf, s),
+                                 reinterpret_cast<SourceRec *>(out), ws->order.buf, s),
                     "kernel launch");
     return st == CRB_OK ? ok() : st;
 }
@@ -697,16 +705,16 @@ crb_status crb_debug_iterate(const float *J, const uint8_t *M_prev, int32_t H, i
         return st;
     std::lock_guard<std::mutex> g(ws->mu);
     const FrameWs L = ws_layout(H, W);
-    if ((st = ws_reserve(ws, L.total)) != CRB_OK)
+    if ((st = ws_reserve(ws, &ws->main, L.total)) != CRB_OK)
         return st;
-    DevFrame f = make_devframe(J, out_J_next, out_M, ws->buf, L, H, W, p->gain,
+    DevFrame f = make_devframe(J, out_J_next, out_M, ws->main.buf, L, H, W, p->gain,
                                p->readnoise, p->sky, p->sigclip, p->sigfrac, p->objlim, 1,
                                kNoEarlyStop);
     f.g2 = out_G2;
     hipError_t e = hipMemcpyAsync(out_M, M_prev, npix, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess)
         return hip_status(e, "hipMemcpyAsync");
-    if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->buf, L, H, W), s)) != CRB_OK)
+    if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->main.buf, L, H, W), s)) != CRB_OK)
         return st;
     e = launch_count(f, reinterpret_cast<long long *>(out_n_new), s);
     if (e != hipSuccess)

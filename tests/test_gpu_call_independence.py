@@ -93,6 +93,34 @@ def test_captured_calls_keep_their_workspace():
             assert got.tobytes() == want_s.tobytes(), rep
 
 
+def test_reading_a_list_keeps_captured_workspaces():
+    s = torch.cuda.Stream()
+    small, sky = item(64, 70, 5), torch.zeros(3000, 3000, device=DEV)   # 1.7 MB to order
+    sky.view(-1)[::7001] = 50.0
+    want = _lib.lacosmic(small["img"], **P)
+    out = dict(out_clean=small["out_clean"], out_mask=small["out_mask"], stream=s)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        assert _lib.lib().crb_release_workspace(s.cuda_stream) == 0
+        _lib.lacosmic(small["img"], **P, **out)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            _lib.lacosmic(small["img"], **P, **out)
+        for rep in range(3):
+            rec = _lib.farm_sources(sky, 10.0, stream=s).numpy()
+            assert len(rec) == -(-sky.numel() // 7001)
+            p = rec["y"].astype(np.int64) * 3000 + rec["x"]
+            np.testing.assert_array_equal(p, np.arange(len(rec)) * 7001)
+            torch.full((1 << 22,), 77, dtype=torch.int32, device=DEV)   # (memory that was freed)
+            small["out_clean"].fill_(-1.0)
+            small["out_mask"].fill_(7)
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(small["out_clean"], want[0]) and torch.equal(small["out_mask"],
+                                                                            want[1])
+
+
 def taken():
     """Device memory in use beyond what torch's allocator holds."""
     free, total = torch.cuda.mem_get_info()
