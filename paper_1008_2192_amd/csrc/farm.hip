@@ -66,6 +66,24 @@ __device__ __forceinline__ double poisson_limit(float mean_f) {
     return exp_neg(mean);
 }
 
+// The deviate of pixel i with that limit (uniform j from word j % 4 of the generator at counter
+// (i_lo, i_hi, j / 4, 0)).
+__device__ __forceinline__ float poisson_draw(size_t i, double limit, uint32_t k0, uint32_t k1) {
+    double prod = 1.0;
+    unsigned int k = 0;
+    for (uint32_t blk = 0;; ++blk) {
+        const uint4 w = philox4x32_10(make_uint4((uint32_t)i, (uint32_t)(i >> 32), blk, 0u), k0, k1);
+        const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            prod = prod * (((double)words[q] + 0.5) * (1.0 / 4294967296.0));
+            if (!(prod > limit))
+                return (float)k;
+            ++k;
+        }
+    }
+}
+
 // A float in the global address space: loads through it are global (not flat) loads.
 typedef __attribute__((address_space(1))) const float GFloat;
 // Fourth word of a raw buffer resource on gfx9-family GPUs: 32-bit data format,
@@ -101,12 +119,24 @@ struct WorkPoisson {
         const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
         const int q = 64 / tw, rem = 64 - q * tw;     // a step of 64 pixels
         int ly = lane / tw, lx = lane - ly * tw;
+        // (a pixel per lane at most: no lane has a second one to go on to, and the chunk's passes
+        // over the limits, most of them empty, cost an actor 0.9 us a tile: 256 tiles of one
+        // pixel on one actor took 782 us with them)
+        if (n <= 64) {
+            if (lane < n) {
+                const size_t i = (size_t)(y0 + ly) * W + x0 + lx;
+                out[i] = poisson_draw(i, poisson_limit(in[i]), k0, k1);
+            }
+            return;
+        }
         for (long long j0 = 0; j0 < n; j0 += 64 * kChunk) {
             int my = 0;                               // the lane's pixels of the chunk
             int y = ly, x = lx;                       // (the first of them)
             float mean[kChunk];
 #pragma unroll
             for (int p = 0; p < kChunk; ++p) {
+                if (j0 + 64 * p >= n)                 // (uniform)
+                    break;
                 const bool on = j0 + 64 * p + lane < n;
                 my += on ? 1 : 0;
                 mean[p] = on ? in[(size_t)(y0 + ly) * W + x0 + lx] : 0.0f;
@@ -118,9 +148,11 @@ struct WorkPoisson {
                 }
             }
 #pragma unroll
-            for (int p = 0; p < kChunk; ++p)
-                if (j0 + 64 * p < n)                  // (uniform)
-                    limits[p * 64 + lane] = poisson_limit(mean[p]);
+            for (int p = 0; p < kChunk; ++p) {
+                if (j0 + 64 * p >= n)
+                    break;
+                limits[p * 64 + lane] = poisson_limit(mean[p]);
+            }
             // (each lane reads only what it wrote)
             size_t i = (size_t)(y0 + y) * W + x0 + x;
             double limit = limits[lane], prod = 1.0;
