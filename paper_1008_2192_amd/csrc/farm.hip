@@ -366,16 +366,27 @@ struct WorkSources {
     }
 };
 
+// Queues in use, nq: no more than waves, a power of two (an actor that walks through queues nobody
+// else takes from pays an atomic for each: with 32 queues for 16 actors, 64 rows of 128 pixels at
+// mean 0.5 took 43 us, with 16 they take 29).
+__host__ __device__ inline int queues_log2(int waves) {
+    int l = 0;
+    while (2 << l <= waves && 2 << l <= kFarmQueues)
+        ++l;
+    return l;
+}
+
 // A queue's line of tickets: [0] the tiles handed out, [1] a copy of the mask of drained
-// queues.  The first run of each wave needs no ticket (wave g takes run g / kFarmQueues of queue
-// g % kFarmQueues), so the counters start behind these runs.
+// queues.  The first run of each wave needs no ticket (wave g takes run g / nq of queue g % nq),
+// so the counters start behind these runs.
 __global__ void k_farm_reset(unsigned int *tickets, long long ntiles, int waves, int chunk,
                              unsigned long long *count) {
     const int q = (int)threadIdx.x;               // one wave
-    const long long size = ntiles * (q + 1) / kFarmQueues - ntiles * q / kFarmQueues;
-    const long long start = (long long)((waves - q + kFarmQueues - 1) / kFarmQueues) * chunk;
-    const unsigned int drained = (unsigned int)__ballot(q < kFarmQueues && start >= size);
-    if (q < kFarmQueues) {
+    const int lq = queues_log2(waves), nq = 1 << lq;
+    const long long size = (ntiles * (q + 1) >> lq) - (ntiles * q >> lq);
+    const long long start = (long long)((waves - q + nq - 1) >> lq) * chunk;
+    const unsigned int drained = (unsigned int)__ballot(q < nq && start >= size);
+    if (q < nq) {
         tickets[q * kFarmStride] = (unsigned int)start;
         tickets[q * kFarmStride + 1] = drained;
     }
@@ -403,12 +414,13 @@ __device__ __forceinline__ float lane_after(float v) {
 // frame took 206 us on 4096 actors and POISSON on 750 x 750 pixels in rows 49 on 1024; with a
 // line for each, the first runs without tickets and the masks, 59 and 33.)
 __device__ __forceinline__ void next_tiles(unsigned int *__restrict__ tickets, long long ntiles,
-                                           int chunk, int &first, unsigned int &drained,
-                                           int &queue, long long &t0, long long &t1) {
+                                           int chunk, int lq, int &first,
+                                           unsigned int &drained, int &queue, long long &t0,
+                                           long long &t1) {
     const int lane = __lane_id();
     for (;;) {
-        const long long q0 = ntiles * queue / kFarmQueues;
-        const long long q1 = ntiles * (queue + 1) / kFarmQueues;
+        const long long q0 = ntiles * queue >> lq;
+        const long long q1 = ntiles * (queue + 1) >> lq;
         unsigned int *const line = tickets + queue * kFarmStride;
         const bool ticket = first < 0;
         unsigned int got = ticket ? 0u : (unsigned int)first * (unsigned int)chunk;
@@ -421,7 +433,7 @@ __device__ __forceinline__ void next_tiles(unsigned int *__restrict__ tickets, l
             t1 = min(q1, t0 + chunk);
             return;
         }
-        if (ticket && q0 + got - chunk < q1 && lane < kFarmQueues)
+        if (ticket && q0 + got - chunk < q1 && lane < 1 << lq)
             atomicOr(&tickets[lane * kFarmStride + 1], 1u << queue);
         unsigned int seen = 0u;
         if (lane == 0)
@@ -461,8 +473,8 @@ __device__ __forceinline__ void flush_records(const SourceRec *__restrict__ buf,
 }
 
 // The farm.  Every wave is an actor: it takes runs of `chunk` tiles from the tickets
-// (tiles numbered row-major, split into kFarmQueues contiguous ranges; a wave starts
-// on the queue of its global wave index modulo kFarmQueues -- workgroups are dealt
+// (tiles numbered row-major, split into nq contiguous ranges, up to kFarmQueues; a wave starts
+// on the queue of its global wave index modulo nq -- workgroups are dealt
 // round-robin to the XCDs, so a queue's tiles mostly stay in one XCD's L2) and works
 // through each tile 64 pixels at a time, with no workgroup barrier.
 //   Image work functions compute every pixel of the tile.
@@ -505,15 +517,17 @@ __global__ __launch_bounds__(256) void k_farm(const float *__restrict__ in, int 
     int nrec = 0;
     const int ntx = (W - 1) / tile_w + 1;
     const long long ntiles = (long long)ntx * ((H - 1) / tile_h + 1);
-    int queue = gwave % kFarmQueues, first = gwave / kFarmQueues;
-    unsigned int drained = 0u;
+    const int lq = queues_log2(waves);
+    int queue = gwave & ((1 << lq) - 1), first = gwave >> lq;
+    unsigned int drained = lq == 5 ? 0u : ~0u << (1 << lq);      // the queues not in use
+    static_assert(kFarmQueues == 32, "a mask of 32 queues");
     FarmCtx c;
     c.in = in;
     c.H = H;
     c.W = W;
     for (;;) {
         long long t0, t1;
-        next_tiles(tickets, ntiles, chunk, first, drained, queue, t0, t1);
+        next_tiles(tickets, ntiles, chunk, lq, first, drained, queue, t0, t1);
         if (t0 < 0)
             break;
         for (long long t = t0; t < t1; ++t) {
