@@ -558,23 +558,22 @@ class SourceList:
         if n > self.capacity:
             raise OverflowError(f"{n} sources found, capacity {self.capacity}")
         rec = self.records[: n * SOURCE_DTYPE.itemsize]
-        sorted_rec = self._sorted(rec, n)
-        if sorted_rec is not None:
-            return sorted_rec.cpu().numpy().view(SOURCE_DTYPE)
+        # short lists are the host's: the device's five launches take longer (reading 256 records
+        # of a 4096 x 4096 frame takes 36 us by the host and 43 by the device, 512 take 54 to 56
+        # and 50 to 67 from run to run, 1024 take 83 and 51, 43,000 take 5201 and 150; of a
+        # 16384 x 16384 frame, whose pixel bitmap takes another 25 us, 1024 take 80 and 76)
+        if n > 640 and self.shape is not None and n > 640 + (self.shape[0] * self.shape[1] >> 20):
+            in_order = self._by_device(rec, n, *self.shape)
+            if in_order is not None:
+                return in_order.cpu().numpy().view(SOURCE_DTYPE)
         rec = rec.cpu().numpy().view(SOURCE_DTYPE)
         return rec[np.lexsort((rec["x"], rec["y"]))]
 
-    def _sorted(self, rec: torch.Tensor, n: int) -> Optional[torch.Tensor]:
-        """The n records in raster order by the device, or None where the host sorts them:
-        records of no known frame or in host memory, no device memory left to sort in, and
-        short lists, for which the five launches take longer (reading 256 records of a
-        4096 x 4096 frame takes 36 us by the host and 43 by the device, 512 take 54 and 50,
-        43,000 take 5201 and 150; of a 16384 x 16384 frame, whose pixel bitmap takes another
-        25 us, 512 take 53 and 75, 1024 take 80 and 76)."""
-        if self.shape is None or not rec.is_cuda:
-            return None
-        H, W = self.shape
-        if n <= 384 + (H * W >> 20):
+    @staticmethod
+    def _by_device(rec: torch.Tensor, n: int, H: int, W: int) -> Optional[torch.Tensor]:
+        """The n records in raster order, or None: records in host memory, or no device memory
+        left to sort them in."""
+        if not rec.is_cuda:
             return None
         try:
             with torch.cuda.device(rec.device):

@@ -33,7 +33,7 @@ def test_records_in_host_memory(n):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [1, 383, 384, 385, 5000])
+@pytest.mark.parametrize("n", [1, 639, 640, 641, 5000])
 def test_either_side_of_the_line(n):
     rec, want = records(n)
     assert source_list(rec, "cuda").numpy().tobytes() == want
