@@ -531,8 +531,8 @@ crb_status crb_lacosmic(const float *img, int32_t H, int32_t W, float gain, floa
         return st;
     const int flags = (g_early_stop.load() ? 0 : kNoEarlyStop) |
                       (g_incremental.load() ? kIncremental : 0) | kFreshMask;
-    DevFrame f = make_devframe(img, out_clean, out_mask, ws->main.buf, L, H, W, gain, readnoise, sky,
-                               sigclip, sigfrac, objlim, niter, flags);
+    DevFrame f = make_devframe(img, out_clean, out_mask, ws->main.buf, L, H, W, gain, readnoise,
+                               sky, sigclip, sigfrac, objlim, niter, flags);
     if ((st = enqueue_single(f, single_cfg(), frame_lists(ws->main.buf, L, H, W), s)) != CRB_OK)
         return st;
     return ok();
@@ -849,11 +849,9 @@ struct crb_plan {
     bool own_stream = false;
     int n = 0;
     int kmax = 0;
-    size_t max_pix = 0;
     size_t init_pix = 0;                // largest frame with niter == 0
     bool any_copy = false;              // some frame has niter == 0
     bool narrow = false;                // some frame stores its bit rows in a narrow form
-    size_t all_pix = 0;
     char *dmem = nullptr;
     bool own_mem = true;                // dmem is the plan's (else a synchronous call's)
     DevFrame *d_frames = nullptr;
@@ -1220,14 +1218,12 @@ static crb_status plan_check(const crb_frame *frames, int32_t n) {
 static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stream,
                             bool use_graph, char *mem, crb_plan **out_plan) {
     crb_status st;
-    size_t all_pix = 0, max_pix = 0, init_pix = 0;
+    size_t init_pix = 0;
     int kmax = 0;
     for (int i = 0; i < n; ++i) {
         const size_t npix = (size_t)frames[i].H * (size_t)frames[i].W;
-        max_pix = npix > max_pix ? npix : max_pix;
         if (frames[i].niter == 0)      // the init kernel copies these frames
             init_pix = npix > init_pix ? npix : init_pix;
-        all_pix += npix;
         kmax = frames[i].niter > kmax ? frames[i].niter : kmax;
     }
     const PlanLayout L = plan_layout(frames, n);
@@ -1263,10 +1259,8 @@ static crb_status plan_make(const crb_frame *frames, int32_t n, hipStream_t stre
     }
     p->n = n;
     p->kmax = kmax;
-    p->max_pix = max_pix;
     p->init_pix = init_pix;
     p->any_copy = init_pix > 0;
-    p->all_pix = all_pix;
     p->d_frames = reinterpret_cast<DevFrame *>(p->dmem + L.o_frames);
     for (int t = 0; t < 3; ++t) {
         p->d_tdet[t] = reinterpret_cast<TileRef *>(p->dmem + L.o_tdet[t]);
