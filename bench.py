@@ -36,8 +36,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Mpix/s per L.A.Cosmic iteration (batched vs per-frame); p99 frame latency"
 UNIT = "Mpix/s per iteration"
-# algorithmic HBM bytes per pixel and iteration of the whole pass: read J (4), write
-# J_{k+1} (4), the mask (1)
+# algorithmic HBM bytes per pixel and iteration of a whole pass over the frame: read J (4), write
+# J_{k+1} (4), the mask (1).  A fixed denominator, not bytes moved: iterations 2 to 4 visit only
+# the tiles they can change, and a step of the batch moves about 7 of these 10.6 GB.
 STEP_BYTES_PER_PIXEL = 9
 # the detection's algorithmic lane operations per pixel counted on the mixed batch when
 # this figure was frozen; a fraction against it does not move when pruning changes the
@@ -79,7 +80,8 @@ def describe(name, frames):
             "frames": 1, "pixels": px, "niter": 4}
 
 
-KERNEL_SOURCES = ("csrc/detect.hip", "csrc/detect_tile.h", "csrc/device_common.h", "csrc/kernels.h", "csrc/medtile.inc")
+KERNEL_SOURCES = ("csrc/detect.hip", "csrc/step.hip", "csrc/detect_tile.h", "csrc/device_common.h",
+                  "csrc/kernels.h", "csrc/medtile.inc")
 
 
 def kernel_source_hash():
@@ -139,7 +141,8 @@ def time_steps(run, steps, warmup):
 def roofline_record(total_px, det_avg_s, work, step_s, valu_per_launch, traffic):
     """The detection kernel against the lane-op peak (algorithmic ops counted by the
     kernel's own counters), beside two fixed-denominator fractions: ops at a frozen
-    per-pixel count, and the whole step's algorithmic HBM bytes against 8 TB/s."""
+    per-pixel count, and a whole pass over the frame per iteration (STEP_BYTES_PER_PIXEL)
+    against 8 TB/s."""
     from paper_1008_2192_amd import roofline
     work_px = float(work["work_pixels"])
     contrast = float(work["contrast_tests"])
