@@ -206,9 +206,9 @@ crb_status crb_plan_work_counts(crb_plan *plan, int64_t *counts);
  * (Section 6.3.1: a 6 x 6 split beats 1 x 36, and the slowest subimage sets the pace);
  * here the same trade-offs are the halo share of a tile or strip and how tiles are
  * handed to the compute units.  Every shape computes identical results.
- *   tile_h      tile rows of the first iteration's detection, 16, 32 or 64 (64 columns; the halo is 4 rows and
- *               columns of J, 2 of S): taller tiles re-read less halo per pixel, shorter
- *               ones fit more blocks per compute unit;
+ *   tile_h      tile rows of the first iteration's detection, 16, 32 or 64 (64 columns; the
+ *               halo is 4 rows and columns of J, 2 of S): taller tiles re-read less halo per
+ *               pixel, shorter ones fit more blocks per compute unit;
  *   persistent  0: one block per (frame, tile); 1: about as many blocks as are resident
  *               at once, each taking tiles from 8 atomic ticket counters (one per XCD,
  *               each over a contiguous part of the tile list, a block helping the others
@@ -216,7 +216,8 @@ crb_status crb_plan_work_counts(crb_plan *plan, int64_t *counts);
  *   fused       0 or 1 and
  *   grow_h      0, 8, 16 or 32: accepted, without effect (everything after the first
  *               detection is one launch per iteration).
- * The default is {32, 0, 0, 0}.
+ * The default is {32, 0, 0, 0}.  A plan with a long frame of at most 13 columns or 6 rows
+ * runs at the default, whatever is set.
  */
 typedef struct {
     int32_t tile_h;
@@ -233,9 +234,8 @@ crb_status crb_plan_get_tuning(crb_plan *plan, crb_tuning *tuning);
 
 /*
  * Autotune a plan: time whole runs (median of reps runs each, HIP events on the plan's
- * stream, after one untimed run) first over the six detection shapes (tile_h x
- * persistent), then over the four grow shapes (three launches with grow_h 8, 16 or 32,
- * or fused) under the best detection shape, keep the fastest and apply it to the plan.
+ * stream, after one untimed run) over the six detection shapes (tile_h x persistent), keep
+ * the fastest and apply it to the plan.
  * The runs write the frames' outputs, so no frame may be cleaned in place (out_clean
  * == img gives CRB_EINVAL).  With use_cache != 0 and an entry for the plan's batch
  * layout in the tune cache, that entry is applied without timing (then *ms and
@@ -335,8 +335,8 @@ int32_t crb_work_radius(const crb_work *w);
  *     8-byte aligned; null only when list_capacity is 0) in no particular order --
  *     sort by (y, x) for raster order; a count above list_capacity means the list
  *     was truncated and a rerun with a larger list returns all.  out_image must be null.
- * Tiles are handed out through 32 ticket counters, each over a contiguous range of
- * tiles, in runs of several tiles; an actor drains its own range first and then
+ * Tiles are handed out through up to 32 ticket counters (no more than actors), each over a
+ * contiguous range of tiles, in runs of several tiles; an actor drains its own range first and then
  * helps with the others.  Asynchronous on the calling thread's stream; uses 4 KiB
  * of that stream's workspace, so calls on one stream are ordered and calls on
  * different streams are independent.

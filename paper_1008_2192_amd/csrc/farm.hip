@@ -72,7 +72,8 @@ __device__ __forceinline__ float poisson_draw(size_t i, double limit, uint32_t k
     double prod = 1.0;
     unsigned int k = 0;
     for (uint32_t blk = 0;; ++blk) {
-        const uint4 w = philox4x32_10(make_uint4((uint32_t)i, (uint32_t)(i >> 32), blk, 0u), k0, k1);
+        const uint4 w = philox4x32_10(make_uint4((uint32_t)i, (uint32_t)(i >> 32), blk, 0u), k0,
+                                      k1);
         const uint32_t words[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
