@@ -93,31 +93,26 @@ __device__ __forceinline__ void detect_tile(const DevFrame &f, int y0, int x0, i
                                             ((y0 + r) & (kSumTY - 1)))[cs >> 3] = (uint8_t)mbyte;
         }
     }
-    if (NARROW && f.narrow && f.mbits)
-#pragma unroll 1
-        for (int r = 0; r < TY && y0 + r < H; r += kSumTY)
-            narrow_store(f, f.mbits, (size_t)((y0 + r) / kSumTY * ntx + x0 / kSumTX),
-                         (y0 + r) & (kSumTY - 1), min(TY, kSumTY), tid, NT, [&](int i) {
-                             unsigned long long m = 0ull;
-                             if (!(f.flags & kFreshMask) && y0 + r + i < H)
-#pragma unroll 1
-                                 for (int c = 0; c < TX && x0 + c < W; ++c)
-                                     m |= f.mask[(size_t)(y0 + r + i) * W + x0 + c] ? 1ull << c
-                                                                                   : 0ull;
-                             return m;
-                         });
     detect_staged(s, f, y0, x0, tid);
 
     // the code planes of the summary tiles the block covers (buffer 0), their state words
     const unsigned long long *code = reinterpret_cast<const unsigned long long *>(s.code);
-    if (NARROW && f.narrow && f.bits)
-#pragma unroll 1
-        for (int r = 0; r < TY && y0 + r < H; r += kSumTY)
-#pragma unroll 1
-            for (int p = 0; p < 3; ++p)
-                narrow_store(f, f.bits, ((size_t)(y0 + r) / kSumTY * ntx + x0 / kSumTX) * 6 + p,
-                             (y0 + r) & (kSumTY - 1), min(TY, kSumTY), tid, NT,
-                             [&](int i) { return code[p * TY + r + i]; });
+    if constexpr (NARROW) {
+        static_assert(!NARROW || (TY == kSumTY && NT == 256), "a summary tile, four waves");
+        if (f.narrow && f.bits) {
+            // a plane per wave: the codes, and the mask's bits
+            const int p = __builtin_amdgcn_readfirstlane(tid >> 6), row = tid & 63;
+            const size_t t = (size_t)(y0 / kSumTY * ntx + x0 / kSumTX);
+            unsigned long long v = 0ull;
+            if (p < 3) {
+                v = row < TY ? code[p * TY + row] : 0ull;
+            } else if (row < TY && y0 + row < H && !(f.flags & kFreshMask)) {
+                for (int c = 0; c < TX && x0 + c < W; ++c)
+                    v |= f.mask[(size_t)(y0 + row) * W + x0 + c] ? 1ull << c : 0ull;
+            }
+            narrow_store(f, p < 3 ? f.bits : f.mbits, p < 3 ? t * 6 + p : t, row, v);
+        }
+    }
     if (f.bits) {
         for (int i = tid; i < 3 * TY && !(NARROW && f.narrow); i += NT) {
             const int p = i / TY, r = i - p * TY;

@@ -32,37 +32,45 @@ __device__ __forceinline__ void lists_start(const StepLists &l, int tid) {
 // The bit rows of a frame with f.narrow != 0 (DevFrame), planes of a tile at `base` by number.
 typedef uint16_t __attribute__((may_alias)) bit_unit;
 
-__device__ __forceinline__ unsigned long long narrow_row(const DevFrame &f,
-                                                         const unsigned long long *base,
-                                                         size_t plane, int row) {
-    if (f.narrow < 0)
-        return base[plane * (size_t)-f.narrow + row];
-    const int p = f.narrow, b = row * p;
-    const bit_unit *u = reinterpret_cast<const bit_unit *>(base) + plane * (size_t)(2 * p);
-    return (unsigned long long)((uint32_t)u[b >> 4] >> (b & 15) & ((1u << p) - 1u));
-}
-// Stores n rows of a plane from row r0 on (16 rows or a multiple) by a block's threads, row(i)
-// being row r0 + i; rows past the frame are left out or empty.
-template <class F>
-__device__ __forceinline__ void narrow_store(const DevFrame &f, unsigned long long *base,
-                                             size_t plane, int r0, int n, int tid, int nthreads,
-                                             F row) {
+// Rows `row` of the three code planes from number `plane` on.
+__device__ __forceinline__ void narrow_codes(const DevFrame &f, size_t plane, int row,
+                                             unsigned long long (&v)[3]) {
     if (f.narrow < 0) {
-#pragma unroll 1
-        for (int i = tid; i < n && r0 + i < -f.narrow; i += nthreads)
-            base[plane * (size_t)-f.narrow + r0 + i] = row(i);
+        const unsigned long long *b = f.bits + plane * (size_t)-f.narrow + row;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            v[i] = b[i * -f.narrow];
+    } else {
+        const int p = f.narrow, at = row * p;
+        const bit_unit *u =
+            reinterpret_cast<const bit_unit *>(f.bits) + plane * (size_t)(2 * p) + (at >> 4);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            v[i] = (uint32_t)u[i * 2 * p] >> (at & 15) & ((1u << p) - 1u);
+    }
+}
+__device__ __forceinline__ unsigned long long narrow_mask(const DevFrame &f, size_t tile, int row) {
+    if (f.narrow < 0)
+        return f.mbits[tile * (size_t)-f.narrow + row];
+    const int p = f.narrow, at = row * p;
+    const bit_unit *u = reinterpret_cast<const bit_unit *>(f.mbits) + tile * (size_t)(2 * p);
+    return (uint32_t)u[at >> 4] >> (at & 15) & ((1u << p) - 1u);
+}
+// Stores a plane by a whole wave, lane l < 32 holding row l in v (empty past the frame).
+__device__ __forceinline__ void narrow_store(const DevFrame &f, unsigned long long *base,
+                                             size_t plane, int lane, unsigned long long v) {
+    if (f.narrow < 0) {
+        if (lane < -f.narrow)
+            base[plane * (size_t)-f.narrow + lane] = v;
         return;
     }
-    const int p = f.narrow, per = 16 / p;              // rows of a unit
-    bit_unit *u = reinterpret_cast<bit_unit *>(base) + plane * (size_t)(2 * p) + r0 / per;
-#pragma unroll 1
-    for (int i = tid; i < n / per; i += nthreads) {
-        uint32_t v = 0u;
-#pragma unroll 1
-        for (int q = 0; q < per; ++q)
-            v |= ((uint32_t)row(i * per + q) & ((1u << p) - 1u)) << (q * p);
-        u[i] = (bit_unit)v;
-    }
+    const int p = f.narrow, per = 16 / p;              // rows of a unit, gathered by their lanes
+    uint32_t b = ((uint32_t)v & ((1u << p) - 1u)) << ((lane & (per - 1)) * p);
+    for (int s = 1; s < per; s *= 2)
+        b |= (uint32_t)__shfl_xor((int)b, s);
+    if (lane < kSumTY && (lane & (per - 1)) == 0)
+        reinterpret_cast<bit_unit *>(base)[plane * (size_t)(2 * p) + (lane * p >> 4)] =
+            (bit_unit)b;
 }
 
 }  // namespace crb

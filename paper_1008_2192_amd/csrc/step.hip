@@ -232,10 +232,13 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
                     if (mask)
                         w[3][d] = f.mbits[t * kSumTY + rr];
                 } else {
-                    for (int p = 0; p < 3; ++p)
-                        w[p][d] = narrow_row(f, f.bits, (t * 2 + buf) * 3 + p, rr);
+                    unsigned long long v[3];
+                    narrow_codes(f, (t * 2 + buf) * 3, rr, v);
                     if (mask)
-                        w[3][d] = narrow_row(f, f.mbits, t, rr);
+                        w[3][d] = narrow_mask(f, t, rr);
+                    w[0][d] = v[0];
+                    w[1][d] = v[1];
+                    w[2][d] = v[2];
                 }
                 own_buf = d == 1 ? buf : own_buf;
             }
@@ -410,10 +413,10 @@ __device__ __forceinline__ void step_tile(const DevFrame &f, int ty, int tx, int
             if (lane < kSumTY)
                 o[64 + lane] = code[64 + lane];
         } else {
-#pragma unroll 1
+#pragma unroll
             for (int p = 0; p < 3; ++p)
-                narrow_store(f, f.bits, (t * 2 + buf) * 3 + p, 0, kSumTY, lane, 64,
-                             [&](int i) { return code[p * kSumTY + i]; });
+                narrow_store(f, f.bits, (t * 2 + buf) * 3 + p, lane,
+                             lane < kSumTY ? code[p * kSumTY + lane] : 0ull);
         }
         // where A lies: bit 3 (dy + 1) + dx + 1 when it is within 8 pixels (an iteration's
         // reach) of the neighbour in direction (dy, dx)
